@@ -18,11 +18,14 @@
 
 #include "direct.hpp"
 #include "fold.hpp"
+#include "lines_plan.hpp"
 #include "plan.hpp"
 
 namespace omni {
 hipError_t launch_fused_fp32(int fmt, int cpt, const void* src, int64_t T, int64_t tps, const float2* tw,
                              double* partial, const FusedP& P, int grid, size_t lds, hipStream_t st);
+hipError_t launch_lines_fp32(const void* src, int64_t T, int64_t tps, const float2* tw, const uint16_t* tab,
+                             double* partial, const LineP& P, int grid, int threads, size_t lds, hipStream_t st);
 hipError_t launch_reduce_scatter(const double* partial, const int32_t* kmap, double* A, int n_slices, int F,
                                  int n_split, int cells_wg, int64_t M, int accumulate, hipStream_t st);
 hipError_t launch_fill_f64(double* p, int64_t n, double v, hipStream_t st);
@@ -127,6 +130,8 @@ struct FusedSetup {
   std::vector<int32_t> kmap; // cell of (split residue, work-group cell) -> natural frequency index
   int F = 0;                 // channels seen by the kernel
   int64_t N = 0, M = 0;      // samples and Fourier cells per channel tile
+  bool lines = false;        // general kernel: the line kernel's schedule `ls` (n_split, cells_wg and kmap are its)
+  omni::LineSetup ls;
 };
 
 struct ArrayPlan {
@@ -170,6 +175,7 @@ struct ArrayPlan {
   float2* d_tw32 = nullptr;
   double2* d_tw64 = nullptr;
   int32_t* d_kmap = nullptr;
+  uint16_t* d_ltab = nullptr;  // line kernel: offset table
   double* d_A = nullptr;
   double* d_partial = nullptr;
   float2* d_ws[2] = {nullptr, nullptr};  // inverse-transform intermediates (complex float32)
@@ -588,6 +594,29 @@ void plan_grid_small(ArrayPlan& ap, int kernel) {
     fs.kmap[(size_t)cell] = kernel == 7 ? omni::grid64_cell(cell) : omni::grid32_cell(cell);
 }
 
+// The general kernel's schedule for the axes after the front passes: the line kernel where it has one (axes whose
+// prime factors are at most 13, cells divisible along the first axis into LDS-sized shares), else the runtime-shape
+// kernel's schedule that is already in ap.fs.  The line kernel is the faster one on every grid measured (kernel
+// times): 16 x 16 floats, one channel, T = 1024: 57 -> 20 us; 5x3 / 3x3 / 3x3 8-bit, 12 channels, T = 333:
+// 5459 -> 649 us; 2x2 / 16x16 8-bit, 16 channels, T = 250: 414 -> 140 us.
+void plan_general(ArrayPlan& ap) {
+  FusedSetup& fs = ap.fs;
+  const int s = ap.n_front, d = (int)ap.n.size() - s;
+  if (!omni::plan_lines(d, ap.n.data() + s, ap.m.data() + s, 64, fs.ls)) return;
+  fs.lines = true;
+  fs.kmap = std::move(fs.ls.kmap);
+  fs.fp.n_split = fs.ls.P.n_split;
+  fs.fp.cells_wg = fs.ls.P.cells;
+  fs.cpt = (fs.ls.P.cells + fs.ls.threads - 1) / fs.ls.threads;
+  fs.lds = fs.ls.lds;
+  for (int k = 0; k < d; ++k) {
+    AxisP& a = fs.fp.ax[k];
+    a.r = a.R = 1;
+    a.L = a.m;
+    a.split = k == 0 ? fs.ls.P.n_split : 1;
+  }
+}
+
 // Front mode: the first s axes are transformed by front passes over HBM, after
 // which every outer Fourier index is a channel of the remaining axes.  A front
 // axis needs a power-of-two padded length of at most 64 (short DFTs of <= 32).
@@ -699,6 +728,7 @@ int build_array_core(ArrayPlan& ap, int levels, const int32_t* dims, const doubl
   }
   // the fixed-shape kernels all assume zero-padded axes: a beam-space plan keeps the general kernel
   if (ap.nbeam > 0) {
+    plan_general(ap);
     ap.max_slices = (int)std::max<size_t>(1, std::min<size_t>(1024, kPartialBudget / ((size_t)ap.F * ap.M * 8)));
     ap.inv_group = (int)std::max<int64_t>(1, std::min<int64_t>(ap.F, (int64_t(1) << 30) / (ap.M * 8)));
     return OMNI_OK;
@@ -734,6 +764,7 @@ int build_array_core(ArrayPlan& ap, int levels, const int32_t* dims, const doubl
     plan_grid_small(ap, 7);
   if (form == OMNI_FORM_MIXED && dtype == OMNI_CI4 && ap.n_front == 0 && ap.n == std::vector<int>{32, 32})
     plan_grid_small(ap, 8);
+  if (ap.kernel == 0) plan_general(ap);
   if (sliced_kernel(ap.kernel)) ap.wg_target = default_wg_target(ap.kernel);
   const size_t per_slice = (size_t)ap.F * (size_t)ap.M * sizeof(double);
   ap.max_slices = (int)std::max<size_t>(1, std::min<size_t>(1024, kPartialBudget / per_slice));
@@ -779,6 +810,7 @@ void free_array(ArrayPlan& ap) {
   hipFree(ap.d_tw32);
   hipFree(ap.d_tw64);
   hipFree(ap.d_kmap);
+  hipFree(ap.d_ltab);
   hipFree(ap.d_A);
   hipFree(ap.d_partial);
   hipFree(ap.d_ws[0]);
@@ -793,6 +825,7 @@ void free_array(ArrayPlan& ap) {
   ap.d_tw32 = nullptr;
   ap.d_tw64 = nullptr;
   ap.d_kmap = nullptr;
+  ap.d_ltab = nullptr;
   ap.d_A = nullptr;
   ap.d_partial = nullptr;
   ap.d_ws[0] = ap.d_ws[1] = nullptr;
@@ -822,6 +855,11 @@ int alloc_array(ArrayPlan& ap) {
       if (ap.y_bytes[b] > 0) HIP_TRY(hipMalloc(&ap.d_y[b], (size_t)ap.y_bytes[b]));
   }
   HIP_TRY(hipMemcpy(ap.d_kmap, ap.fs.kmap.data(), ap.fs.kmap.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+  if (ap.fs.lines) {
+    const std::vector<uint16_t>& tab = ap.fs.ls.tab;
+    HIP_TRY(hipMalloc(&ap.d_ltab, tab.size() * sizeof(uint16_t)));
+    HIP_TRY(hipMemcpy(ap.d_ltab, tab.data(), tab.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
+  }
   int32_t* d_desc = nullptr;
   const size_t nd = std::max(ap.tw_desc_fwd.size(), ap.tw_desc_inv.size());
   HIP_TRY(hipMalloc(&d_desc, nd * sizeof(int32_t)));
@@ -877,6 +915,27 @@ void kmark(omni_plan_s* p, int end, hipStream_t st) {
 // partial sums into ap.d_partial; returns the number of time slices used.
 int launch_general(ArrayPlan& ap, const FusedSetup& fs, int fmt, const void* src, int64_t T, int time_block,
                    const float2* tw, hipStream_t st, int* slices) {
+  if (fs.lines) {
+    omni::LineP L = fs.ls.P;
+    L.F = fs.F;
+    L.fmt = fmt;
+    L.time_block = time_block;
+    L.batch = std::min(L.batch, time_block);
+    L.groups = std::min(L.groups, L.batch);
+    // time slices of whole batches
+    const int64_t per = (int64_t)fs.F * L.n_split;
+    const int64_t batches = (T + L.batch - 1) / L.batch;
+    int64_t ns = std::max<int64_t>(1, (ap.wg_target + per - 1) / per);
+    ns = std::min<int64_t>(std::min<int64_t>(ns, ap.max_slices), batches);
+    const int64_t tps = (batches + ns - 1) / ns * L.batch;
+    ns = (T + tps - 1) / tps;
+    L.xcd_groups = (ns * fs.F) % 8 == 0 ? 1 : 0;
+    if (ns * per > INT32_MAX) return fail(OMNI_E_SHAPE, "grid too large");
+    *slices = (int)ns;
+    HIP_TRY(omni::launch_lines_fp32(src, T, tps, tw, ap.d_ltab, ap.d_partial, L, (int)(ns * per), fs.ls.threads,
+                                    fs.ls.lds, st));
+    return OMNI_OK;
+  }
   FusedP P = fs.fp;
   const int64_t per_slice_groups = (int64_t)fs.F * P.n_split;
   int64_t ns = std::max<int64_t>(1, (ap.wg_target + per_slice_groups - 1) / per_slice_groups);
@@ -1196,10 +1255,11 @@ int tune_sliced(omni_plan_s* p, ArrayPlan& ap) {
 int tune_array(omni_plan_s* p, ArrayPlan& ap) {
   if (sliced_kernel(ap.kernel)) return tune_sliced(p, ap);
   if (ap.kernel != 0 && ap.kernel != 3) return OMNI_OK;
-  const bool ct = ap.kernel == 3;
+  const bool ct = ap.kernel == 3 || ap.fs.lines;  // fixed transforms: only the time slicing is tuned
   const std::string key = tune_key(ap, p->dtype);
   int lc = 0, wg = 0;
   const bool cached = p->tune == OMNI_TUNE_CACHE && tune_cache_lookup(p->tune_cache, key, &lc, &wg);
+  if (ct) lc = ap.lcap;
   const bool front = ap.n_front > 0;
   const std::vector<int> axes = front ? std::vector<int>(ap.n.begin() + ap.n_front, ap.n.end()) : ap.n;
   const int Fk = ap.fs.F;
@@ -1237,7 +1297,7 @@ int tune_array(omni_plan_s* p, ArrayPlan& ap) {
       int rc = OMNI_OK;
       for (int rep = 0; rep < 2 && rc == OMNI_OK; ++rep) {
         HIP_TRY(hipEventRecord(e0, 0));
-        rc = ct ? launch_ct(ap, fmt, zero, Tt, p->time_block, tw, 0, &slices)
+        rc = ap.kernel == 3 ? launch_ct(ap, fmt, zero, Tt, p->time_block, tw, 0, &slices)
                 : launch_general(ap, fs, fmt, zero, Tt, p->time_block, tw, 0, &slices);
         HIP_TRY(hipEventRecord(e1, 0));
         HIP_TRY(hipEventSynchronize(e1));
@@ -1831,7 +1891,10 @@ int omni_plan_describe(omni_plan_t plan, char* buf, size_t len, size_t* needed) 
            ",\"split\":" + std::to_string(a.split) + "}";
     }
     s += "],\"order\":[";
-    for (int p = 0; p < P.d; ++p) s += (p ? "," : "") + std::to_string(P.pass[p].axis);
+    if (ap.fs.lines)
+      for (size_t p = 0; p < ap.fs.ls.order.size(); ++p) s += (p ? "," : "") + std::to_string(ap.fs.ls.order[p]);
+    else
+      for (int p = 0; p < P.d; ++p) s += (p ? "," : "") + std::to_string(P.pass[p].axis);
     s += "]}";
   }
   s += "]}";

@@ -1,0 +1,345 @@
+// Planner of the line kernel (host only): stages of every axis, LDS layout, offset tables, split, batch and
+// work-group size.  See lines.hpp for the schedule.
+#include "lines_plan.hpp"
+
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+
+namespace omni {
+namespace {
+
+constexpr size_t kLds = 160 * 1024;
+constexpr int kMaxBatch = 16;
+
+struct Stage {
+  int axis;
+  int nin, nout;   // inputs and outputs per line
+  bool padded;
+  int done;        // product of the axis' earlier stages' outputs (frequency stride of this stage's digit)
+  int rem;         // index stride of this stage's digit: length still to come after it
+};
+
+template <int K>
+bool has(const int (&set)[K], int v) {
+  return std::find(set, set + K, v) != set + K;
+}
+
+// Factors of a plain transform of length m: fewest stages, then the smallest sum.  False if m has a prime factor
+// without a register transform.
+bool plain_chain(int m, std::vector<int>& out) {
+  out.clear();
+  if (m == 1) return true;
+  if (has(kLinePlain, m)) {
+    out.push_back(m);
+    return true;
+  }
+  std::vector<int> best;
+  for (int f : kLinePlain) {
+    if (m % f) continue;
+    std::vector<int> rest;
+    if (!plain_chain(m / f, rest)) continue;
+    rest.insert(rest.begin(), f);
+    const auto sum = [](const std::vector<int>& v) {
+      int s = 0;
+      for (int x : v) s += x;
+      return s;
+    };
+    if (best.empty() || rest.size() < best.size() || (rest.size() == best.size() && sum(rest) < sum(best))) best = rest;
+  }
+  out = best;
+  return !best.empty();
+}
+
+// Vector instructions of one line's transform, roughly.
+double line_cost(int nout) { return nout * (2.5 * std::log2((double)std::max(2, nout)) + 4.0) + 20.0; }
+
+// Stages of one axis, appended to st.  `first` != 0 forces the inputs of a zero-padded axis' first stage (any
+// divisor of n); 0 takes the cheapest chain of register transforms.
+bool axis_stages(int axis, int n, int m, int first, std::vector<Stage>& st) {
+  std::vector<int> rest;
+  int done = 1, rem = m;
+  if (m == 2 * n) {
+    if (first) {
+      if (n % first || !plain_chain(n / first, rest)) return false;
+    } else {
+      std::vector<int> best;
+      double best_cost = 1e300;
+      for (int a : kLinePadded) {
+        if (n % a || (a == 1 && n > 1) || !plain_chain(n / a, rest)) continue;
+        double cost = (double)m / (2 * a) * line_cost(2 * a);
+        for (int f : rest) cost += (double)m / f * (line_cost(f) + 8.0 * f);
+        if (cost < best_cost) {
+          best_cost = cost;
+          first = a;
+          best = rest;
+        }
+      }
+      if (!first) return false;
+      rest = best;
+    }
+    rem /= 2 * first;
+    st.push_back({axis, first, 2 * first, true, 1, rem});
+    done = 2 * first;
+  } else if (m == n) {
+    if (!plain_chain(m, rest)) return false;
+  } else {
+    return false;
+  }
+  for (int f : rest) {
+    rem /= f;
+    st.push_back({axis, f, f, false, done, rem});
+    done *= f;
+  }
+  return true;
+}
+
+uint32_t magic_of(int64_t d) { return d <= 1 ? 0u : (uint32_t)(((uint64_t(1) << 32) + (uint64_t)d - 1) / (uint64_t)d); }
+
+struct Layout {
+  std::vector<int> order;    // stage of each pass
+  std::vector<int> stride, ext;
+  std::vector<int64_t> lines;
+  int64_t w_size = 0, cells = 0, tab = 0;
+};
+
+// Passes in the order: stage 0, then the other axes' stages (long transforms first: the later passes see more
+// lines), and last the final stage of one axis, a zero-padded one-stage axis where there is one (the working array
+// then holds its inputs, half of its outputs).
+Layout make_layout(const std::vector<Stage>& st, int split) {
+  Layout L;
+  const int n = (int)st.size();
+  auto final_stage = [&](int i) { return i + 1 == n || st[(size_t)i + 1].axis != st[(size_t)i].axis; };
+  int last = -1;
+  for (int i = n - 1; i >= (split > 1 ? 1 : 0); --i) {
+    if (!final_stage(i) || (n > 1 && i == 0)) continue;
+    if (last < 0) {
+      last = i;
+      continue;
+    }
+    const Stage &a = st[(size_t)i], &b = st[(size_t)last];
+    if (a.padded != b.padded ? a.padded : a.nin < b.nin) last = i;
+  }
+  if (last < 0) return L;
+  std::vector<int> mid;
+  for (int i = 1; i < n; ++i)
+    if (i != last) mid.push_back(i);
+  if (last != 0) L.order.push_back(0);
+  // whole axes, by decreasing length of their first stage; the stages of an axis stay in order
+  std::vector<int> axes;
+  for (int i : mid)
+    if (axes.empty() || std::find(axes.begin(), axes.end(), st[(size_t)i].axis) == axes.end()) axes.push_back(st[(size_t)i].axis);
+  std::stable_sort(axes.begin(), axes.end(), [&](int a, int b) {
+    int na = 0, nb = 0;
+    for (const Stage& s : st) {
+      if (s.axis == a) na = std::max(na, s.nout);
+      if (s.axis == b) nb = std::max(nb, s.nout);
+    }
+    return na > nb;
+  });
+  for (int a : axes)
+    for (int i : mid)
+      if (st[(size_t)i].axis == a) L.order.push_back(i);
+  L.order.push_back(last);
+  L.stride.assign((size_t)n, 0);
+  L.ext.assign((size_t)n, 0);
+  int64_t s = 1;
+  L.cells = 1;
+  for (int i = n - 1; i >= 0; --i) {
+    const int out = i == 0 ? st[0].nout / split : st[(size_t)i].nout;
+    L.ext[(size_t)i] = i == last ? st[(size_t)i].nin : out;
+    L.stride[(size_t)i] = (int)std::min<int64_t>(s, 1 << 28);
+    L.w_size = s * L.ext[(size_t)i];
+    s = L.w_size | 1;
+    L.cells *= out;
+    if (L.cells > (int64_t(1) << 26) || s > (int64_t(1) << 26)) return Layout();
+  }
+  std::vector<int> cur((size_t)n);
+  for (int i = 0; i < n; ++i) cur[(size_t)i] = st[(size_t)i].nin;
+  for (int i : L.order) {
+    int64_t lines = 1;
+    for (int k = 0; k < n; ++k)
+      if (k != i) lines *= cur[(size_t)k];
+    L.lines.push_back(lines);
+    L.tab += lines * (st[(size_t)i].rem > 1 ? 2 : 1);
+    cur[(size_t)i] = i == 0 ? st[0].nout / split : st[(size_t)i].nout;
+  }
+  return L;
+}
+
+}  // namespace
+
+bool plan_lines(int d, const int* n, const int* m, int max_batch, LineSetup& out) {
+  int64_t N = 1;
+  int tw_all = 0;
+  for (int k = 0; k < d; ++k) {
+    N *= n[k];
+    tw_all += m[k];
+  }
+  if (N > (int64_t(1) << 26)) return false;
+  std::vector<Stage> tail;  // the stages of axes 1 ... d - 1
+  for (int k = 1; k < d; ++k)
+    if (!axis_stages(k, n[k], m[k], 0, tail)) return false;
+
+  // Candidates: first stage of axis 0 and its split S (a divisor of the stage's outputs; only a zero-padded
+  // stage, which the split form sums directly, so its length is free), threads, batch.  The cost of one sample of
+  // a channel on a CU is the larger of its vector issue and its latency chain over the work-groups that fit a CU.
+  double best = 1e300;
+  int bS = 0, bB = 0, bNT = 0, bG = 0;
+  bool bTw = false;
+  Layout bL;
+  std::vector<Stage> bst, st;
+  std::vector<std::pair<int, int>> cands = {{0, 1}};  // (inputs of stage 1 or 0, split)
+  if (m[0] == 2 * n[0])
+    for (int a = 1; a <= std::min(n[0], 128); ++a)
+      for (int S = 2; S <= 2 * a; ++S)
+        if (n[0] % a == 0 && (2 * a) % S == 0) cands.push_back({a, S});
+  for (const auto& cand : cands) {
+    const int S = cand.second;
+    st.clear();
+    if (!axis_stages(0, n[0], m[0], cand.first, st)) continue;
+    st.insert(st.end(), tail.begin(), tail.end());
+    if ((int)st.size() > kLineMaxPass || (S > 1 && st.size() < 2)) continue;
+    bool twiddled = false;
+    for (const Stage& s : st) twiddled = twiddled || s.rem > 1;
+    const Stage s0 = st[0];
+    const Layout L = make_layout(st, S);
+    if (L.order.empty()) continue;
+    const int64_t n_tw = (twiddled || S > 1) && tw_all <= 1024 ? tw_all : 0;
+    const int64_t load_lines = N / s0.nin, k_out = s0.nout / S;
+    for (int NT = 256; NT <= 1024; NT *= 2) {
+      for (int B = 1; B <= std::min(kMaxBatch, std::max(1, max_batch)); B *= 2) {
+        const int G = (int)std::max<int64_t>(1, std::min<int64_t>(B, NT / L.lines.back()));
+        const size_t lds = (size_t)(B * L.w_size * 8 + n_tw * 8 + G * L.cells * 4 + L.tab * 2);
+        if (lds > kLds) continue;
+        if (B * N >= 65536 && S == 1) continue;
+        if (S > 1 && B * load_lines * k_out >= 65536) continue;
+        bool ok = L.w_size < 65536;
+        double issue = 0, chain = 0;
+        auto add = [&](int64_t jobs, double instr) {
+          ok = ok && jobs < 65536;
+          issue += std::ceil(jobs / 64.0) * instr;
+          chain += std::ceil((double)jobs / NT) * instr * 5.0 + 400.0;
+        };
+        if (S == 1)
+          add(B * N, 12.0);
+        else
+          add(B * load_lines * k_out, 20.0 + 12.0 * s0.nin);
+        for (size_t p = S > 1 ? 1 : 0; p < L.order.size(); ++p) {
+          const Stage& s = st[(size_t)L.order[p]];
+          const bool lastp = p + 1 == L.order.size();
+          const double instr = line_cost(s.nout) + (s.rem > 1 ? 8.0 * s.nout : 0.0);
+          if (lastp) {
+            ok = ok && G * L.lines[p] < 65536;
+            const double each = std::ceil((double)B / G);
+            issue += std::ceil(G * L.lines[p] / 64.0) * (instr * each + 4.0 * s.nout);
+            chain += std::ceil((double)G * L.lines[p] / NT) * (instr * each + 4.0 * s.nout) * 5.0 + 400.0;
+          } else {
+            add(B * L.lines[p], instr);
+          }
+        }
+        if (!ok) continue;
+        const double fit = std::max(1.0, std::min(std::floor((double)kLds / (double)lds), 1024.0 / NT));
+        const double cost = S * std::max(issue / B, chain / (fit * B));
+        if (cost < best * 0.98) {
+          best = cost;
+          bS = S;
+          bB = B;
+          bNT = NT;
+          bG = G;
+          bL = L;
+          bst = st;
+          bTw = twiddled || S > 1;
+        }
+      }
+    }
+  }
+  if (!bS) return false;
+  st = bst;
+  const Stage& s0 = st[0];
+  const int ns = (int)st.size();
+  LineP& P = out.P;
+  std::memset(&P, 0, sizeof P);
+  P.n_pass = (int32_t)bL.order.size();
+  P.N = (int32_t)N;
+  P.batch = bB;
+  P.groups = bG;
+  P.w_size = (int32_t)bL.w_size;
+  P.cells = (int32_t)bL.cells;
+  P.n_split = bS;
+  P.n_tw = bTw && tw_all <= 1024 ? tw_all : 0;
+  P.load_lines = (int32_t)(N / s0.nin);
+  P.load_magic = magic_of(P.load_lines);
+  P.n_magic = magic_of(N);
+  P.f1 = s0.nout;
+  P.n1 = s0.nin;
+  P.m0 = m[0];
+  P.k_out = s0.nout / bS;
+  P.k_magic = magic_of((int64_t)P.load_lines * P.k_out);
+  std::vector<int> tw_off((size_t)d, 0);
+  for (int k = 1; k < d; ++k) tw_off[(size_t)k] = tw_off[(size_t)k - 1] + m[k - 1];
+  out.tab.clear();
+  out.order.clear();
+  std::vector<int> cur((size_t)ns);
+  for (int i = 0; i < ns; ++i) cur[(size_t)i] = st[(size_t)i].nin;
+  for (size_t p = 0; p < bL.order.size(); ++p) {
+    const int i = bL.order[p];
+    const Stage& s = st[(size_t)i];
+    LinePass& q = P.pass[p];
+    q.type = s.nin | (s.padded ? 32 : 0);
+    q.stride = bL.stride[(size_t)i];
+    q.lines = (int32_t)bL.lines[p];
+    q.magic = magic_of(q.lines);
+    q.tab = (int32_t)out.tab.size();
+    q.tw = tw_off[(size_t)s.axis];
+    q.tj = -1;
+    std::vector<uint16_t> steps;
+    for (int64_t line = 0; line < bL.lines[p]; ++line) {
+      int64_t r = line, off = 0, j = 0;
+      for (int k = ns - 1; k >= 0; --k) {
+        if (k == i) continue;
+        const int64_t digit = r % cur[(size_t)k];
+        r /= cur[(size_t)k];
+        off += digit * bL.stride[(size_t)k];
+        if (st[(size_t)k].axis == s.axis && k > i) j += digit * st[(size_t)k].rem;
+      }
+      out.tab.push_back((uint16_t)off);
+      steps.push_back((uint16_t)(j * s.done));
+    }
+    if (s.rem > 1) {
+      q.tj = (int32_t)out.tab.size();
+      out.tab.insert(out.tab.end(), steps.begin(), steps.end());
+    }
+    cur[(size_t)i] = i == 0 ? st[0].nout / bS : s.nout;
+    out.order.push_back(s.axis);
+  }
+  P.n_tab = (int32_t)out.tab.size();
+
+  // cell (split residue c, output q of the last pass, line) -> natural frequency index
+  const int last = bL.order.back();
+  std::vector<int64_t> nat((size_t)d, 1);
+  for (int k = d - 2; k >= 0; --k) nat[(size_t)k] = nat[(size_t)k + 1] * m[k + 1];
+  out.kmap.assign((size_t)(bS * bL.cells), 0);
+  const int64_t lines = bL.lines.back();
+  for (int c = 0; c < bS; ++c)
+    for (int64_t cell = 0; cell < bL.cells; ++cell) {
+      int64_t r = cell % lines, at = 0;
+      auto put = [&](int k, int64_t digit) {
+        const Stage& s = st[(size_t)k];
+        if (k == 0) digit = c + digit * bS;
+        at += digit * s.done * nat[(size_t)s.axis];
+      };
+      put(last, cell / lines);
+      for (int k = ns - 1; k >= 0; --k) {
+        if (k == last) continue;
+        put(k, r % cur[(size_t)k]);
+        r /= cur[(size_t)k];
+      }
+      out.kmap[(size_t)(c * bL.cells + cell)] = (int32_t)at;
+    }
+  out.threads = bNT;
+  out.lds = (size_t)(bB * bL.w_size * 8 + (int64_t)P.n_tw * 8 + bG * bL.cells * 4 + (int64_t)P.n_tab * 2);
+  return true;
+}
+
+}  // namespace omni

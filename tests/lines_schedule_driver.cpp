@@ -1,0 +1,201 @@
+// CPU check of the line kernel's schedules: every table, stride and division of lines.hpp executed on the host in
+// float64 with bounds checks, for grids given on stdin ("n_1 ... n_d [b1|b2]", the suffix: that many innermost axes
+// unpadded), against plain zero-padded DFTs.  Prints how many schedules were checked and how many
+// grids have none.
+#include "lines_plan.hpp"
+
+#include <cmath>
+#include <complex>
+#include <cstdio>
+#include <cstdlib>
+#include <iostream>
+#include <sstream>
+#include <string>
+
+using cd = std::complex<double>;
+using omni::LinePass;
+using omni::LineSetup;
+
+#define CHECK(c)                                                              \
+  do {                                                                        \
+    if (!(c)) {                                                               \
+      std::printf("FAILED %s (line %d) on %s\n", #c, __LINE__, name.c_str()); \
+      return 1;                                                               \
+    }                                                                         \
+  } while (0)
+
+static cd w(long long e, int m) { return std::polar(1.0, -2.0 * M_PI * (double)(e % m) / m); }
+static uint32_t fast_div(uint32_t q, uint32_t magic) {
+  return magic ? (uint32_t)(((uint64_t)q * magic) >> 32) : q;
+}
+
+static int check(const std::string& name, const std::vector<int>& n, const std::vector<int>& m, int max_batch,
+                 bool* planned) {
+  LineSetup s;
+  *planned = omni::plan_lines((int)n.size(), n.data(), m.data(), max_batch, s);
+  if (!*planned) return 0;
+  const omni::LineP& P = s.P;
+  const int d = (int)n.size();
+  int64_t N = 1, M = 1;
+  for (int k = 0; k < d; ++k) {
+    N *= n[(size_t)k];
+    M *= m[(size_t)k];
+  }
+  CHECK(P.N == N && (int64_t)P.cells * P.n_split == M && (int64_t)s.kmap.size() == M);
+  CHECK(s.lds <= 160 * 1024 && s.threads >= 64 && s.threads <= 1024 && P.batch >= 1 && P.batch <= max_batch);
+  CHECK(P.groups >= 1 && P.groups <= P.batch && P.n_pass >= 1 && P.n_pass <= omni::kLineMaxPass);
+  CHECK((size_t)P.n_tab == s.tab.size());
+  CHECK(s.lds >= (size_t)P.batch * P.w_size * 8 + P.n_tw * 8 + (size_t)P.groups * P.cells * 4 + P.n_tab * 2);
+  std::vector<int> seen((size_t)M, 0);
+  for (int32_t k : s.kmap) {
+    CHECK(k >= 0 && k < M);
+    CHECK(seen[(size_t)k]++ == 0);
+  }
+  // divisions over every value the kernel forms
+  for (uint32_t q = 0; P.n_split == 1 && q < (uint32_t)(P.batch * N); ++q) CHECK(fast_div(q, P.n_magic) == q / N);
+  CHECK(P.n_split == 1 ? P.batch * N < 65536 : (int64_t)P.batch * P.load_lines * P.k_out < 65536);
+  for (int64_t q = 0; q < (P.n_split == 1 ? N : (int64_t)P.load_lines * P.k_out); ++q)
+    CHECK(fast_div((uint32_t)q, P.load_magic) == q / P.load_lines);
+  for (int64_t q = 0; P.n_split > 1 && q < (int64_t)P.batch * P.load_lines * P.k_out; ++q)
+    CHECK(fast_div((uint32_t)q, P.k_magic) == q / ((int64_t)P.load_lines * P.k_out));
+  // twiddle table as the plan lays it out: per axis w_m^q
+  std::vector<cd> tw;
+  for (int k = 0; k < d; ++k)
+    for (int q = 0; q < m[(size_t)k]; ++q) tw.push_back(w(q, m[(size_t)k]));
+  // one sample per batch slot, reference transform axis by axis
+  std::vector<std::vector<cd>> x((size_t)P.batch);
+  std::vector<std::vector<double>> ref((size_t)P.batch);
+  unsigned seed = 12345;
+  for (int b = 0; b < P.batch; ++b) {
+    for (int64_t i = 0; i < N; ++i) {
+      seed = seed * 1664525u + 1013904223u;
+      x[(size_t)b].push_back(cd((int)(seed >> 28) - 8, (int)((seed >> 24) & 15) - 8));
+    }
+    std::vector<cd> cur = x[(size_t)b];
+    int64_t outer = 1, inner = N;
+    for (int k = 0; k < d; ++k) {
+      const int nk = n[(size_t)k], mk = m[(size_t)k];
+      inner /= nk;
+      std::vector<cd> nx((size_t)(outer * mk * inner));
+      for (int64_t o = 0; o < outer; ++o)
+        for (int q = 0; q < mk; ++q)
+          for (int64_t i = 0; i < inner; ++i) {
+            cd z = 0;
+            for (int j = 0; j < nk; ++j) z += cur[(size_t)((o * nk + j) * inner + i)] * w((long long)j * q, mk);
+            nx[(size_t)((o * mk + q) * inner + i)] = z;
+          }
+      cur.swap(nx);
+      outer *= mk;
+    }
+    for (const cd& v : cur) ref[(size_t)b].push_back(std::norm(v));
+  }
+  const LinePass& p0 = P.pass[0];
+  for (int c = 0; c < P.n_split; ++c) {
+    std::vector<cd> W((size_t)(P.batch * P.w_size), cd(NAN, NAN));
+    std::vector<double> pw((size_t)(P.batch * P.cells), 0.0);
+    for (int b = 0; b < P.batch; ++b) {
+      if (P.n_split == 1) {
+        for (int64_t i = 0; i < N; ++i) {
+          const int64_t j = i / P.load_lines, line = i % P.load_lines;
+          const int64_t at = s.tab[(size_t)(p0.tab + line)] + j * p0.stride;
+          CHECK(at < P.w_size);
+          W[(size_t)(b * P.w_size + at)] = x[(size_t)b][(size_t)i];
+        }
+      } else {
+        for (int k = 0; k < P.k_out; ++k)
+          for (int64_t line = 0; line < P.load_lines; ++line) {
+            const int kap = c + P.n_split * k;
+            cd z = 0;
+            for (int j = 0; j < P.n1; ++j) {
+              CHECK(j * P.load_lines + line < N);
+              z += x[(size_t)b][(size_t)(j * P.load_lines + line)] * w((long long)kap * j, P.f1);
+            }
+            if (p0.tj >= 0) {
+              const int e = kap * s.tab[(size_t)(p0.tj + line)];
+              CHECK(e < m[0]);
+              z *= tw[(size_t)(p0.tw + e)];
+            }
+            const int64_t at = s.tab[(size_t)(p0.tab + line)] + (int64_t)k * p0.stride;
+            CHECK(at < P.w_size);
+            W[(size_t)(b * P.w_size + at)] = z;
+          }
+      }
+    }
+    for (int pi = P.n_split == 1 ? 0 : 1; pi < P.n_pass; ++pi) {
+      const LinePass& p = P.pass[pi];
+      const int nin = p.type & 31, nout = (p.type & 32) ? 2 * nin : nin;
+      const bool last = pi + 1 == P.n_pass;
+      CHECK((int64_t)P.batch * p.lines < 65536 && p.tab + p.lines <= P.n_tab);
+      for (uint32_t q = 0; q < (uint32_t)(P.batch * p.lines); ++q) CHECK(fast_div(q, p.magic) == q / p.lines);
+      std::vector<char> owner(W.size(), 0);
+      for (int b = 0; b < P.batch; ++b)
+        for (int line = 0; line < p.lines; ++line) {
+          const int64_t base = (int64_t)b * P.w_size + s.tab[(size_t)(p.tab + line)];
+          std::vector<cd> in, outv;
+          for (int j = 0; j < nin; ++j) {
+            const int64_t at = base + (int64_t)j * p.stride;
+            CHECK(at < (int64_t)(b + 1) * P.w_size);
+            CHECK(!owner[(size_t)at]);  // not yet written by another line of this pass
+            CHECK(!std::isnan(W[(size_t)at].real()));
+            in.push_back(W[(size_t)at]);
+          }
+          for (int k = 0; k < nout; ++k) {
+            cd z = 0;
+            for (int j = 0; j < nin; ++j) z += in[(size_t)j] * w((long long)j * k, nout);
+            if (!last && p.tj >= 0) {
+              const int e = k * s.tab[(size_t)(p.tj + line)];
+              CHECK(p.tw + e < (int)tw.size());
+              z *= tw[(size_t)(p.tw + e)];
+            }
+            outv.push_back(z);
+          }
+          CHECK(!last || p.tj < 0);
+          for (int k = 0; k < nout; ++k) {
+            if (last) {
+              CHECK((int64_t)k * p.lines + line < P.cells);
+              pw[(size_t)((int64_t)b * P.cells + (int64_t)k * p.lines + line)] += std::norm(outv[(size_t)k]);
+            } else {
+              const int64_t at = base + (int64_t)k * p.stride;
+              CHECK(at < (int64_t)(b + 1) * P.w_size);
+              CHECK(!owner[(size_t)at]);
+              owner[(size_t)at] = 1;
+              W[(size_t)at] = outv[(size_t)k];
+            }
+          }
+        }
+    }
+    for (int b = 0; b < P.batch; ++b)
+      for (int cell = 0; cell < P.cells; ++cell) {
+        const double want = ref[(size_t)b][(size_t)s.kmap[(size_t)((int64_t)c * P.cells + cell)]];
+        CHECK(std::fabs(pw[(size_t)((int64_t)b * P.cells + cell)] - want) <= 1e-9 * (1.0 + 128.0 * N * N));
+      }
+  }
+  return 0;
+}
+
+int main() {
+  std::string line;
+  int done = 0, none = 0;
+  while (std::getline(std::cin, line)) {
+    std::istringstream is(line);
+    std::string tok;
+    std::vector<int> n;
+    int beams = 0;
+    while (is >> tok) {
+      if (tok[0] == 'b')
+        beams = std::atoi(tok.c_str() + 1);
+      else
+        n.push_back(std::atoi(tok.c_str()));
+    }
+    std::vector<int> m;
+    for (size_t k = 0; k < n.size(); ++k) m.push_back((int)(n.size() - k) <= beams ? n[k] : 2 * n[k]);
+    for (int max_batch : {64, 3}) {
+      bool planned = false;
+      if (check(line, n, m, max_batch, &planned)) return 1;
+      planned ? ++done : ++none;
+      if (!planned) std::printf("no schedule: %s\n", line.c_str());
+    }
+  }
+  std::printf("schedules checked: %d\nnot planned: %d\n", done, none);
+  return 0;
+}
