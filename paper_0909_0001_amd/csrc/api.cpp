@@ -18,6 +18,7 @@
 
 #include "direct.hpp"
 #include "fold.hpp"
+#include "inverse.hpp"
 #include "lines_plan.hpp"
 #include "plan.hpp"
 
@@ -31,6 +32,9 @@ hipError_t launch_reduce_scatter(const double* partial, const int32_t* kmap, dou
 hipError_t launch_fill_f64(double* p, int64_t n, double v, hipStream_t st);
 hipError_t launch_inverse_axis(bool real_in, bool last, const void* src, void* dst, const double2* twi,
                                int64_t outer, int m, int n, int64_t inner, double scale, hipStream_t st);
+hipError_t launch_inverse_group(int src_kind, const void* src, void* dst, const double2* twi, const uint16_t* tab,
+                                int64_t outer, int64_t inner, double scale, const InvP& P, size_t lds,
+                                hipStream_t st);
 hipError_t launch_twiddles(const int32_t* desc_dev, int n_tables, float2* tw32, double2* tw64, hipStream_t st);
 hipError_t launch_fused8x4_fp32(int fmt, const void* src, int64_t T, int64_t tps, const float2* tw16, double* partial,
                                 int F, int n_slices, int time_block, hipStream_t st);
@@ -66,7 +70,6 @@ hipError_t launch_fengine(const void* raw, int64_t N, int64_t T, int F, const vo
                           hipStream_t st);
 hipError_t launch_xengine(const float2* Y, int64_t Tc, int F, int P, int64_t Mp, double2* S, int accumulate,
                           hipStream_t st);
-hipError_t launch_narrow(const double2* src, float2* dst, int64_t n, hipStream_t st);
 bool xengine_fused_ok(int P, int ny);
 hipError_t launch_xengine_fused(const float2* Y1, int64_t Tc, int F, int P, int mx, int ny, const float2* twy,
                                 double2* S, int accumulate, hipStream_t st);
@@ -171,11 +174,13 @@ struct ArrayPlan {
   int max_slices = 1;
   int last_slices = 1;
   int inv_group = 1;         // channels per inverse-transform group
+  std::vector<omni::InvGroup> inv;  // groups of axes of the inverse (made with the device resources)
   // device resources
   float2* d_tw32 = nullptr;
   double2* d_tw64 = nullptr;
   int32_t* d_kmap = nullptr;
   uint16_t* d_ltab = nullptr;  // line kernel: offset table
+  uint16_t* d_inv_tab = nullptr;  // the inverse groups' offset tables
   double* d_A = nullptr;
   double* d_partial = nullptr;
   float2* d_ws[2] = {nullptr, nullptr};  // inverse-transform intermediates (complex float32)
@@ -811,6 +816,7 @@ void free_array(ArrayPlan& ap) {
   hipFree(ap.d_tw64);
   hipFree(ap.d_kmap);
   hipFree(ap.d_ltab);
+  hipFree(ap.d_inv_tab);
   hipFree(ap.d_A);
   hipFree(ap.d_partial);
   hipFree(ap.d_ws[0]);
@@ -825,7 +831,7 @@ void free_array(ArrayPlan& ap) {
   ap.d_tw32 = nullptr;
   ap.d_tw64 = nullptr;
   ap.d_kmap = nullptr;
-  ap.d_ltab = nullptr;
+  ap.d_ltab = ap.d_inv_tab = nullptr;
   ap.d_A = nullptr;
   ap.d_partial = nullptr;
   ap.d_ws[0] = ap.d_ws[1] = nullptr;
@@ -839,6 +845,48 @@ void free_array(ArrayPlan& ap) {
       return fail(e_ == hipErrorOutOfMemory ? OMNI_E_NOMEM : OMNI_E_HIP,                  \
                   std::string(#expr) + ": " + hipGetErrorString(e_));                      \
   } while (0)
+
+// The inverse's groups along the axes n[0 .. d) (`inner` values behind them) and their tables on the device.
+int alloc_inverse(int d, const int* n, const int* m, int64_t channels, int64_t inner, const int* tw_off,
+                  std::vector<omni::InvGroup>& groups, uint16_t** d_tab) {
+  groups = omni::plan_inverse(d, n, m, channels, inner, tw_off);
+  std::vector<uint16_t> tab;
+  for (const auto& g : groups) tab.insert(tab.end(), g.tab.begin(), g.tab.end());
+  if (tab.empty()) return OMNI_OK;
+  HIP_TRY(hipMalloc(d_tab, tab.size() * sizeof(uint16_t)));
+  HIP_TRY(hipMemcpy(*d_tab, tab.data(), tab.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
+  return OMNI_OK;
+}
+
+// Inverse transform of `channels` accumulators at src (src_kind as in launch_inverse_group: 0 real, 2 complex
+// float64) into vis; ws: two buffers for the complex float32 values between groups (src may be ws[1]).
+int run_inverse(const std::vector<omni::InvGroup>& groups, const uint16_t* d_tab, const int* n, const int* m,
+                const int* tw_off, const double2* twi, int src_kind, const void* src, void* vis, float2* const* ws,
+                int64_t channels, int64_t inner_last, double scale, hipStream_t st) {
+  int64_t outer = channels, inner = inner_last;
+  for (const auto& g : groups)
+    for (int k = g.axis0; k < g.axis0 + g.axes; ++k) inner *= m[k];
+  for (size_t i = 0; i < groups.size(); ++i) {
+    const omni::InvGroup& g = groups[i];
+    const bool last = i + 1 == groups.size();
+    void* dst = last ? vis : (void*)ws[i & 1];
+    int64_t lags = 1;
+    for (int k = g.axis0; k < g.axis0 + g.axes; ++k) {
+      inner /= m[k];
+      lags *= 2 * n[k] - 1;
+    }
+    if (g.direct)
+      HIP_TRY(omni::launch_inverse_axis(src_kind == 0, last, src, dst, twi + tw_off[g.axis0], outer, m[g.axis0],
+                                        n[g.axis0], inner, scale, st));
+    else
+      HIP_TRY(omni::launch_inverse_group(src_kind, src, dst, twi, d_tab + g.tab_off, outer, inner, last ? scale : 1.0,
+                                         g.P, g.lds, st));
+    src = dst;
+    src_kind = 1;
+    outer *= lags;
+  }
+  return OMNI_OK;
+}
 
 int alloc_array(ArrayPlan& ap) {
   const size_t accA = (size_t)ap.F * ap.M * sizeof(double);
@@ -859,6 +907,14 @@ int alloc_array(ArrayPlan& ap) {
     const std::vector<uint16_t>& tab = ap.fs.ls.tab;
     HIP_TRY(hipMalloc(&ap.d_ltab, tab.size() * sizeof(uint16_t)));
     HIP_TRY(hipMemcpy(ap.d_ltab, tab.data(), tab.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
+  }
+  {
+    const int d = (int)ap.n.size() - ap.nbeam;
+    int64_t inner = 1;
+    for (size_t k = (size_t)d; k < ap.n.size(); ++k) inner *= ap.n[k];
+    const int rc = alloc_inverse(d, ap.n.data(), ap.m.data(), ap.inv_group, inner, ap.inv_off.data(), ap.inv,
+                                 &ap.d_inv_tab);
+    if (rc) return rc;
   }
   int32_t* d_desc = nullptr;
   const size_t nd = std::max(ap.tw_desc_fwd.size(), ap.tw_desc_inv.size());
@@ -1129,17 +1185,11 @@ int correlate_array(omni_plan_s* p, ArrayPlan& ap, const void* volt, int64_t T, 
                                         rows, na, nb, ap.nbeam, st));
         src = ap.d_ws[1];
       }
-      int64_t outer = g;
-      for (int k = 0; k < d; ++k) {
-        int64_t inner = 1;
-        for (int j = k + 1; j < (int)ap.n.size(); ++j) inner *= (ap.beam_sub && j >= d) ? ap.n[j] : ap.m[j];
-        const bool last = (k == d - 1);
-        void* dst = last ? (void*)(static_cast<float2*>(vis) + (size_t)f0 * ap.n_out) : (void*)ap.d_ws[k & 1];
-        HIP_TRY(omni::launch_inverse_axis(k == 0, last, src, dst, ap.d_tw64 + ap.inv_off[k], outer, ap.m[k],
-                                          ap.n[k], inner, 1.0 / m_inv, st));
-        src = dst;
-        outer *= 2 * ap.n[k] - 1;
-      }
+      int64_t inner = 1;
+      for (size_t k = (size_t)d; k < ap.n.size(); ++k) inner *= ap.n[k];
+      const int rc = run_inverse(ap.inv, ap.d_inv_tab, ap.n.data(), ap.m.data(), ap.inv_off.data(), ap.d_tw64, 0, src,
+                                 static_cast<float2*>(vis) + (size_t)f0 * ap.n_out, ap.d_ws, g, inner, 1.0 / m_inv, st);
+      if (rc) return rc;
     }
   }
   return OMNI_OK;
@@ -2009,7 +2059,8 @@ struct omni_hybrid_s {
   double2* d_tw64 = nullptr;       // inverse tables (float64)
   float2* d_y[2] = {nullptr, nullptr};  // the two front passes' outputs for one chunk
   double2* d_S = nullptr;          // [F][P][P][mx][my] cross-power sums
-  float2* d_ws[2] = {nullptr, nullptr};  // inverse intermediates
+  std::vector<omni::InvGroup> inv;  // the inverse's one group of axes
+  uint16_t* d_inv_tab = nullptr;    // its offset table
 };
 
 namespace {
@@ -2022,8 +2073,7 @@ void hybrid_free(omni_hybrid_s* h) {
   hipFree(h->d_y[0]);
   hipFree(h->d_y[1]);
   hipFree(h->d_S);
-  hipFree(h->d_ws[0]);
-  hipFree(h->d_ws[1]);
+  hipFree(h->d_inv_tab);
 }
 
 int hybrid_alloc(omni_hybrid_s* h) {
@@ -2034,8 +2084,11 @@ int hybrid_alloc(omni_hybrid_s* h) {
   HIP_TRY(hipMalloc(&h->d_y[0], (size_t)(tiles * h->P * h->mx * h->ny) * sizeof(float2)));
   if (!h->fused) HIP_TRY(hipMalloc(&h->d_y[1], (size_t)(tiles * h->P * h->Mp) * sizeof(float2)));
   HIP_TRY(hipMalloc(&h->d_S, (size_t)(pairs * h->Mp) * sizeof(double2)));
-  HIP_TRY(hipMalloc(&h->d_ws[0], (size_t)(pairs * h->Mp) * sizeof(float2)));
-  HIP_TRY(hipMalloc(&h->d_ws[1], (size_t)(pairs * (2 * h->nx - 1) * h->my) * sizeof(float2)));
+  // both axes are powers of two of at most 64: one inverse group, no intermediate
+  const int n2[2] = {h->nx, h->ny}, m2[2] = {(int)h->mx, (int)h->my}, off2[2] = {0, (int)h->mx};
+  const int rc = alloc_inverse(2, n2, m2, pairs, 1, off2, h->inv, &h->d_inv_tab);
+  if (rc) return rc;
+  if (h->inv.size() != 1 || h->inv[0].direct) return fail(OMNI_E_SHAPE, "hybrid tiles: no inverse schedule");
   const int32_t desc[12] = {(int32_t)h->mx, -1, 0, (int32_t)h->my, -1, (int32_t)h->mx,
                             (int32_t)h->mx, +1, 0, (int32_t)h->my, +1, (int32_t)h->mx};
   int32_t* d_desc = nullptr;
@@ -2087,7 +2140,11 @@ int omni_hybrid_plan(omni_hybrid_t* out, int32_t P, int32_t nx, int32_t ny, int3
   }
   int rc = check_device(&h->device);
   if (rc) return rc;
-  rc = hybrid_alloc(h.get());
+  try {
+    rc = hybrid_alloc(h.get());
+  } catch (...) {
+    rc = fail(OMNI_E_NOMEM, "host allocation failed");
+  }
   if (rc) {
     hybrid_free(h.get());
     return rc;
@@ -2134,11 +2191,9 @@ int omni_hybrid_correlate(omni_hybrid_t h, const void* volt, int64_t T, void* vi
     HIP_TRY(omni::launch_xengine(h->d_y[1], tc, h->F, h->P, h->Mp, h->d_S, acc, st));
   }
   if (!(flags & OMNI_NO_FINALIZE)) {
-    HIP_TRY(omni::launch_narrow(h->d_S, h->d_ws[0], pairs * h->Mp, st));
-    HIP_TRY(omni::launch_inverse_axis(false, false, h->d_ws[0], h->d_ws[1], h->d_tw64, pairs, (int)h->mx, h->nx,
-                                      h->my, 1.0, st));
-    HIP_TRY(omni::launch_inverse_axis(false, true, h->d_ws[1], vis, h->d_tw64 + h->mx, pairs * (2 * h->nx - 1),
-                                      (int)h->my, h->ny, 1, 1.0 / (double)h->Mp, st));
+    const omni::InvGroup& g = h->inv[0];
+    HIP_TRY(omni::launch_inverse_group(2, h->d_S, vis, h->d_tw64, h->d_inv_tab, pairs, 1, 1.0 / (double)h->Mp, g.P,
+                                       g.lds, st));
   }
   return OMNI_OK;
 }

@@ -9,7 +9,7 @@
 //   V_f[Delta] = (1/M) sum_kappa A_f[kappa] exp(+2 pi i sum_k kappa_k Delta_k / m_k),
 //   Delta_k in [-(n_k-1), n_k-1]  (Sec. II.D, index range after Eq. ProofEq2).
 //
-// Only the 2n_k-1 valid lags of each axis are produced; since every pair
+// The axes are transformed in groups (inverse.hip).  Only the 2n_k-1 valid lags of each axis are produced; since every pair
 // separation along axis k lies in that range and m_k = 2 n_k, no lag wraps.
 #include <hip/hip_runtime.h>
 
@@ -19,20 +19,47 @@
 
 namespace omni {
 
-// A[f][kmap[c][cell]] (+)= sum_s partial[s][f][c][cell], float64, fixed summation order.
-__global__ void reduce_scatter_kernel(const double* __restrict__ partial, const int32_t* __restrict__ kmap,
-                                      double* __restrict__ A, int n_slices, int F, int n_split, int cells_wg,
-                                      int64_t M, int accumulate) {
-  const int64_t per_f = (int64_t)n_split * cells_wg;  // == M
-  const int64_t total = (int64_t)F * per_f;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t f = i / per_f;
-    const int64_t cc = i - f * per_f;  // c * cells_wg + cell
+// A[f][kmap[c][cell]] (+)= sum_s partial[s][f][c][cell], float64, fixed summation order.  A work-group takes
+// 256 / SG consecutive cells; SG threads share a cell, each with every SG-th slice and four loads in flight, their
+// sums combined in LDS in a fixed order.  Small grids have few cells and many slices: one thread a cell then waits
+// for one load after another (1024 cells x 256 slices: 60 us; SG = 16: 6 us).
+template <int SG>
+__global__ __launch_bounds__(256) void reduce_scatter_kernel(const double* __restrict__ partial,
+                                                             const int32_t* __restrict__ kmap, double* __restrict__ A,
+                                                             int n_slices, int F, int64_t per_f, int64_t M,
+                                                             int accumulate) {
+  constexpr int CELLS = 256 / SG;
+  __shared__ double part[SG > 1 ? 256 : 1];
+  const int lane = threadIdx.x % CELLS, sg = threadIdx.x / CELLS;
+  const int64_t total = (int64_t)F * per_f;  // per_f = split residues x cells of a work-group = M
+  for (int64_t i0 = (int64_t)blockIdx.x * CELLS; i0 < total; i0 += (int64_t)gridDim.x * CELLS) {
+    const int64_t i = i0 + lane;
     double s = 0.0;
-    for (int sl = 0; sl < n_slices; ++sl) s += partial[((int64_t)sl * F + f) * per_f + cc];
-    double* dst = A + f * M + kmap[cc];
-    *dst = accumulate ? *dst + s : s;
+    if (i < total) {
+      const double* p = partial + i;
+      int sl = sg;
+      for (; sl + 3 * SG < n_slices; sl += 4 * SG) {
+        const double a = p[(int64_t)sl * total], b = p[(int64_t)(sl + SG) * total];
+        const double c = p[(int64_t)(sl + 2 * SG) * total], d = p[(int64_t)(sl + 3 * SG) * total];
+        s += a;
+        s += b;
+        s += c;
+        s += d;
+      }
+      for (; sl < n_slices; sl += SG) s += p[(int64_t)sl * total];
+    }
+    if constexpr (SG > 1) {
+      __syncthreads();
+      part[threadIdx.x] = s;
+      __syncthreads();
+      if (sg == 0)
+        for (int g = 1; g < SG; ++g) s += part[g * CELLS + lane];
+    }
+    if (sg == 0 && i < total) {
+      const int64_t f = i / per_f;
+      double* dst = A + f * M + kmap[i - f * per_f];
+      *dst = accumulate ? *dst + s : s;
+    }
   }
 }
 
@@ -41,7 +68,8 @@ __global__ void fill_f64_kernel(double* __restrict__ p, int64_t n, double v) {
     p[i] = v;
 }
 
-// One axis of the inverse transform.  Source [outer][m][inner] (the real
+// One axis of the inverse transform by plain sums, for axes without a register transform (the others run in
+// inverse.hip).  Source [outer][m][inner] (the real
 // float64 accumulator if REAL_IN, else complex float32 from the previous axis),
 // destination [outer][2n-1][inner] complex float32 (scaled by `scale` if LAST).
 // Each lag is summed in float64; only the stored intermediates are float32.
@@ -83,129 +111,6 @@ __global__ void inverse_axis_kernel(const void* __restrict__ src, void* __restri
   }
 }
 
-// The same axis transform with the m inputs of TC columns staged in LDS, so
-// that each input is read from HBM once instead of once per output lag.
-// Columns are the flattened (outer, inner) index pairs; a work-group takes TC
-// consecutive columns and produces their (2n - 1) lags.  m <= 256.
-template <bool REAL_IN, bool LAST, int TC>
-__global__ __launch_bounds__(256) void inverse_axis_tiled_kernel(const void* __restrict__ src, void* __restrict__ dst,
-                                                                 const double2* __restrict__ twi, int64_t outer,
-                                                                 int m, int n, int64_t inner, double scale) {
-  using Elem = typename std::conditional<REAL_IN, double, float2>::type;
-  __shared__ Elem a[TC == 32 ? 2048 : 4096];  // m * TC: m <= 64 for TC = 32, m <= 256 for TC = 16
-  __shared__ double2 w[256];
-  const int nout = 2 * n - 1;
-  const int64_t cols = outer * inner;
-  const int64_t col0 = (int64_t)blockIdx.x * TC;
-  const int tid = threadIdx.x;
-  for (int q = tid; q < m; q += 256) w[q] = twi[q];
-  const Elem* s = static_cast<const Elem*>(src);
-  // load order: consecutive threads take consecutive inner indices where the tile has them
-  const int in_run = inner >= TC ? TC : (TC % inner == 0 ? (int)inner : 1);
-  for (int l = tid; l < m * TC; l += 256) {
-    const int r = l % in_run, rest = l / in_run;
-    const int k = rest % m;
-    const int c = (rest / m) * in_run + r;
-    const int64_t col = col0 + c;
-    if (col < cols) {
-      const int64_t ou = col / inner, in = col - ou * inner;
-      a[k * TC + c] = s[(ou * m + k) * inner + in];
-    }
-  }
-  __syncthreads();
-  for (int idx = tid; idx < nout * TC; idx += 256) {
-    const int c = idx % TC, o = idx / TC;
-    const int64_t col = col0 + c;
-    if (col >= cols) continue;
-    const int delta = o - (n - 1);
-    const int dm = ((delta % m) + m) % m;
-    double re = 0.0, im = 0.0;
-    int e = 0;
-    for (int k = 0; k < m; ++k) {
-      const double2 wk = w[e];
-      if constexpr (REAL_IN) {
-        const double v = a[k * TC + c];
-        re = fma(v, wk.x, re);
-        im = fma(v, wk.y, im);
-      } else {
-        const float2 v = a[k * TC + c];
-        const double vx = v.x, vy = v.y;
-        re = fma(vx, wk.x, fma(-vy, wk.y, re));
-        im = fma(vx, wk.y, fma(vy, wk.x, im));
-      }
-      e += dm;
-      if (e >= m) e -= m;
-    }
-    const int64_t ou = col / inner, in = col - ou * inner;
-    const int64_t oi = (ou * nout + o) * inner + in;
-    const double sc = LAST ? scale : 1.0;
-    reinterpret_cast<float2*>(dst)[oi] = make_float2((float)(re * sc), (float)(im * sc));
-  }
-}
-
-// The same axis transform for a power-of-two m <= 32 as a radix-2 FFT in
-// registers: one thread per column (consecutive threads take consecutive inner
-// indices), all m outputs y_j = sum_k a_k exp(+2 pi i k j / m) in float64, of
-// which the 2n - 1 = m - 1 lags Delta = j (j < n) and Delta = j - m (j > n) are
-// stored.  O(m log m) work per column instead of O(m^2).
-template <int M>
-constexpr int bitrev(int k) {
-  int r = 0;
-  for (int b = 1; b < M; b <<= 1) r = (r << 1) | ((k / b) & 1);
-  return r;
-}
-
-template <int M, bool REAL_IN, bool LAST>
-__global__ __launch_bounds__(256) void inverse_axis_fft_kernel(const void* __restrict__ src, void* __restrict__ dst,
-                                                               const double2* __restrict__ twi, int64_t outer,
-                                                               int64_t inner, double scale) {
-  constexpr int NOUT = M - 1, NH = M / 2;
-  __shared__ double2 w[NH];  // exp(+2 pi i q / M), q < M / 2
-  for (int q = threadIdx.x; q < NH; q += blockDim.x) w[q] = twi[q];
-  __syncthreads();
-  const int64_t cols = outer * inner;
-  const double sc = LAST ? scale : 1.0;
-  for (int64_t col = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; col < cols;
-       col += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t ou = col / inner, in = col - ou * inner;
-    double2 x[M];
-#pragma unroll
-    for (int k = 0; k < M; ++k) {
-      const int64_t at = (ou * M + k) * inner + in;
-      if constexpr (REAL_IN) {
-        x[bitrev<M>(k)] = make_double2(static_cast<const double*>(src)[at], 0.0);
-      } else {
-        const float2 v = static_cast<const float2*>(src)[at];
-        x[bitrev<M>(k)] = make_double2(v.x, v.y);
-      }
-    }
-#pragma unroll
-    for (int len = 2; len <= M; len <<= 1) {
-#pragma unroll
-      for (int i = 0; i < M; i += len) {
-#pragma unroll
-        for (int j = 0; j < len / 2; ++j) {
-          const double2 u = x[i + j];
-          double2 v = x[i + j + len / 2];
-          if (j > 0) {
-            const double2 wj = w[j * (M / len)];  // exp(+2 pi i j / len)
-            v = make_double2(fma(v.x, wj.x, -v.y * wj.y), fma(v.x, wj.y, v.y * wj.x));
-          }
-          x[i + j] = make_double2(u.x + v.x, u.y + v.y);
-          x[i + j + len / 2] = make_double2(u.x - v.x, u.y - v.y);
-        }
-      }
-    }
-    float2* d = static_cast<float2*>(dst);
-#pragma unroll
-    for (int o = 0; o < NOUT; ++o) {
-      const int delta = o - (NH - 1);
-      const double2 y = x[delta >= 0 ? delta : delta + M];
-      d[(ou * NOUT + o) * inner + in] = make_float2((float)(y.x * sc), (float)(y.y * sc));
-    }
-  }
-}
-
 // Twiddle generator, float64 on the device: for each table entry (m, q, sign)
 // w = exp(sign * 2 pi i q / m), evaluated with sincospi on the exact reduced
 // ratio 2q/m.  Writes float32 copies for the forward kernels and float64
@@ -234,9 +139,18 @@ static inline int grid_for(int64_t n, int block) {
 
 hipError_t launch_reduce_scatter(const double* partial, const int32_t* kmap, double* A, int n_slices, int F,
                                  int n_split, int cells_wg, int64_t M, int accumulate, hipStream_t st) {
-  const int64_t total = (int64_t)F * M;
-  hipLaunchKernelGGL(reduce_scatter_kernel, dim3(grid_for(total, 256)), dim3(256), 0, st, partial, kmap, A, n_slices,
-                     F, n_split, cells_wg, M, accumulate);
+  const int64_t per_f = (int64_t)n_split * cells_wg, total = (int64_t)F * per_f;
+#define OMNI_REDUCE(SG_)                                                                                           \
+  hipLaunchKernelGGL((reduce_scatter_kernel<SG_>), dim3(grid_for(total, 256 / SG_)), dim3(256), 0, st, partial,    \
+                     kmap, A, n_slices, F, per_f, M, accumulate)
+  // threads per cell: enough to fill the GPU (about 128 K threads) while each still sums two slices
+  if (n_slices >= 32 && total <= 16384)
+    OMNI_REDUCE(16);
+  else if (n_slices >= 8 && total <= 131072)
+    OMNI_REDUCE(4);
+  else
+    OMNI_REDUCE(1);
+#undef OMNI_REDUCE
   return hipGetLastError();
 }
 
@@ -245,58 +159,8 @@ hipError_t launch_fill_f64(double* p, int64_t n, double v, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int M>
-static hipError_t launch_inverse_fft(bool real_in, bool last, const void* src, void* dst, const double2* twi,
-                                     int64_t outer, int64_t inner, double scale, hipStream_t st) {
-  const dim3 g(grid_for(outer * inner, 256)), b(256);
-  if (real_in && last)
-    hipLaunchKernelGGL((inverse_axis_fft_kernel<M, true, true>), g, b, 0, st, src, dst, twi, outer, inner, scale);
-  else if (real_in)
-    hipLaunchKernelGGL((inverse_axis_fft_kernel<M, true, false>), g, b, 0, st, src, dst, twi, outer, inner, scale);
-  else if (last)
-    hipLaunchKernelGGL((inverse_axis_fft_kernel<M, false, true>), g, b, 0, st, src, dst, twi, outer, inner, scale);
-  else
-    hipLaunchKernelGGL((inverse_axis_fft_kernel<M, false, false>), g, b, 0, st, src, dst, twi, outer, inner, scale);
-  return hipGetLastError();
-}
-
 hipError_t launch_inverse_axis(bool real_in, bool last, const void* src, void* dst, const double2* twi,
                                int64_t outer, int m, int n, int64_t inner, double scale, hipStream_t st) {
-  const int64_t cols = outer * inner;
-  if (m == 2 * n) {
-    if (m == 4) return launch_inverse_fft<4>(real_in, last, src, dst, twi, outer, inner, scale, st);
-    if (m == 8) return launch_inverse_fft<8>(real_in, last, src, dst, twi, outer, inner, scale, st);
-    if (m == 16) return launch_inverse_fft<16>(real_in, last, src, dst, twi, outer, inner, scale, st);
-    if (m == 32) return launch_inverse_fft<32>(real_in, last, src, dst, twi, outer, inner, scale, st);
-  }
-  if (m <= 256 && cols >= (m <= 64 ? 32 : 16) * 256) {
-    // TC columns per work-group (m * TC <= 2048 or 4096 elements of LDS), at least 256 work-groups
-    const dim3 b(256);
-#define OMNI_INV_TILED(TC_)                                                                                          \
-  do {                                                                                                               \
-    const int64_t nb = (cols + TC_ - 1) / TC_;                                                                       \
-    if (nb > INT32_MAX) return hipErrorInvalidValue;                                                                 \
-    const dim3 g((unsigned)nb);                                                                                      \
-    if (real_in && last)                                                                                             \
-      hipLaunchKernelGGL((inverse_axis_tiled_kernel<true, true, TC_>), g, b, 0, st, src, dst, twi, outer, m, n,     \
-                         inner, scale);                                                                              \
-    else if (real_in)                                                                                                \
-      hipLaunchKernelGGL((inverse_axis_tiled_kernel<true, false, TC_>), g, b, 0, st, src, dst, twi, outer, m, n,    \
-                         inner, scale);                                                                              \
-    else if (last)                                                                                                   \
-      hipLaunchKernelGGL((inverse_axis_tiled_kernel<false, true, TC_>), g, b, 0, st, src, dst, twi, outer, m, n,    \
-                         inner, scale);                                                                              \
-    else                                                                                                             \
-      hipLaunchKernelGGL((inverse_axis_tiled_kernel<false, false, TC_>), g, b, 0, st, src, dst, twi, outer, m, n,   \
-                         inner, scale);                                                                              \
-  } while (0)
-    if (m <= 64)
-      OMNI_INV_TILED(32);
-    else
-      OMNI_INV_TILED(16);
-#undef OMNI_INV_TILED
-    return hipGetLastError();
-  }
   const int64_t total = outer * (2 * n - 1) * inner;
   const dim3 g(grid_for(total, 256)), b(256);
   if (real_in && last)

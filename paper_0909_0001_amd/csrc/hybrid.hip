@@ -106,11 +106,6 @@ __global__ __launch_bounds__(kXeThreads) void xengine_kernel(const float2* __res
   half_pairs_store<P>(acc, rb, S + (int64_t)f * P * P * Mp, Mp, kappa, accumulate);
 }
 
-__global__ void narrow_kernel(const double2* __restrict__ src, float2* __restrict__ dst, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    dst[i] = make_float2((float)src[i].x, (float)src[i].y);
-}
-
 template <int P>
 hipError_t launch_xe(const float2* Y, int64_t Tc, int F, int64_t Mp, double2* S, int accumulate, hipStream_t st) {
   constexpr int CELLS = kXeThreads / (P / 2);
@@ -267,12 +262,6 @@ hipError_t launch_xengine(const float2* Y, int64_t Tc, int F, int P, int64_t Mp,
     case 32: return launch_xe<32>(Y, Tc, F, Mp, S, accumulate, st);
     default: return hipErrorInvalidValue;
   }
-}
-
-hipError_t launch_narrow(const double2* src, float2* dst, int64_t n, hipStream_t st) {
-  const int64_t g = std::max<int64_t>(1, std::min<int64_t>(65536, (n + 255) / 256));
-  hipLaunchKernelGGL(narrow_kernel, dim3((unsigned)g), dim3(256), 0, st, src, dst, n);
-  return hipGetLastError();
 }
 
 }  // namespace omni

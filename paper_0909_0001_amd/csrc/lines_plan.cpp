@@ -1,6 +1,8 @@
-// Planner of the line kernel (host only): stages of every axis, LDS layout, offset tables, split, batch and
-// work-group size.  See lines.hpp for the schedule.
+// Planners of the line kernel and of the grouped inverse (host only): stages of every axis, LDS layout, offset
+// tables, split, batch and work-group size.  See lines.hpp and inverse.hpp for the schedules.
 #include "lines_plan.hpp"
+
+#include "inverse.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -25,26 +27,27 @@ bool has(const int (&set)[K], int v) {
   return std::find(set, set + K, v) != set + K;
 }
 
-// Factors of a plain transform of length m: fewest stages, then the smallest sum.  False if m has a prime factor
-// without a register transform.
-bool plain_chain(int m, std::vector<int>& out) {
+// Factors of a plain transform of length m among the lengths `set`: fewest stages, then the smallest sum.  False if
+// m has a prime factor that is not there.
+template <int K>
+bool plain_chain(int m, std::vector<int>& out, const int (&set)[K]) {
   out.clear();
   if (m == 1) return true;
-  if (has(kLinePlain, m)) {
+  if (has(set, m)) {
     out.push_back(m);
     return true;
   }
   std::vector<int> best;
-  for (int f : kLinePlain) {
+  const auto sum = [](const std::vector<int>& v) {
+    int s = 0;
+    for (int x : v) s += x;
+    return s;
+  };
+  for (int f : set) {
     if (m % f) continue;
     std::vector<int> rest;
-    if (!plain_chain(m / f, rest)) continue;
+    if (!plain_chain(m / f, rest, set)) continue;
     rest.insert(rest.begin(), f);
-    const auto sum = [](const std::vector<int>& v) {
-      int s = 0;
-      for (int x : v) s += x;
-      return s;
-    };
     if (best.empty() || rest.size() < best.size() || (rest.size() == best.size() && sum(rest) < sum(best))) best = rest;
   }
   out = best;
@@ -61,12 +64,12 @@ bool axis_stages(int axis, int n, int m, int first, std::vector<Stage>& st) {
   int done = 1, rem = m;
   if (m == 2 * n) {
     if (first) {
-      if (n % first || !plain_chain(n / first, rest)) return false;
+      if (n % first || !plain_chain(n / first, rest, kLinePlain)) return false;
     } else {
       std::vector<int> best;
       double best_cost = 1e300;
       for (int a : kLinePadded) {
-        if (n % a || (a == 1 && n > 1) || !plain_chain(n / a, rest)) continue;
+        if (n % a || (a == 1 && n > 1) || !plain_chain(n / a, rest, kLinePlain)) continue;
         double cost = (double)m / (2 * a) * line_cost(2 * a);
         for (int f : rest) cost += (double)m / f * (line_cost(f) + 8.0 * f);
         if (cost < best_cost) {
@@ -82,7 +85,7 @@ bool axis_stages(int axis, int n, int m, int first, std::vector<Stage>& st) {
     st.push_back({axis, first, 2 * first, true, 1, rem});
     done = 2 * first;
   } else if (m == n) {
-    if (!plain_chain(m, rest)) return false;
+    if (!plain_chain(m, rest, kLinePlain)) return false;
   } else {
     return false;
   }
@@ -340,6 +343,134 @@ bool plan_lines(int d, const int* n, const int* m, int max_batch, LineSetup& out
   out.threads = bNT;
   out.lds = (size_t)(bB * bL.w_size * 8 + (int64_t)P.n_tw * 8 + bG * bL.cells * 4 + (int64_t)P.n_tab * 2);
   return true;
+}
+
+// Groups: axes are taken from the outermost on while a group's cells leave room for several columns (at most
+// kGroupCells; a whole channel of at most kChannelCells cells is one group).  Columns per work-group: as many as fit
+// kTileCells cells, fewer where there would be under two work-groups a CU.
+std::vector<InvGroup> plan_inverse(int d, const int* n, const int* m, int64_t channels, int64_t inner,
+                                   const int* tw_off) {
+  constexpr int64_t kGroupCells = 1024, kChannelCells = 4096, kTileCells = 4096;
+  std::vector<InvGroup> out;
+  std::vector<int> chain;
+  int64_t all = inner;
+  bool whole = inner == 1;
+  for (int k = 0; k < d; ++k) {
+    all *= m[k];
+    whole = whole && plain_chain(m[k], chain, kLinePlain);
+  }
+  whole = whole && all <= kChannelCells;
+  int64_t outer = channels, rest = all;
+  size_t tab_off = 0;
+  for (int k = 0; k < d;) {
+    InvGroup g;
+    g.axis0 = k;
+    g.tab_off = tab_off;
+    if (!plain_chain(m[k], chain, kLinePlain) || m[k] > kTileCells) {
+      g.axes = 1;
+      g.direct = true;
+      rest /= m[k];
+      outer *= 2 * n[k] - 1;
+      ++k;
+      out.push_back(g);
+      continue;
+    }
+    int64_t Mg = 1, Ng = 1;
+    std::vector<Stage> st;
+    while (k < d && plain_chain(m[k], chain, kLinePlain) && (g.axes == 0 || whole || Mg * m[k] <= kGroupCells)) {
+      int done = 1, rem = m[k];
+      std::vector<Stage> one;
+      for (int f : chain) {
+        rem /= f;
+        one.push_back({k, f, f, false, done, rem});
+        done *= f;
+      }
+      if ((int)(st.size() + one.size()) > kInvMaxPass) break;
+      st.insert(st.end(), one.begin(), one.end());
+      Mg *= m[k];
+      Ng *= 2 * n[k] - 1;
+      rest /= m[k];
+      ++g.axes;
+      ++k;
+    }
+    InvP& P = g.P;
+    P.Mg = (int32_t)Mg;
+    P.Ng = (int32_t)Ng;
+    P.m_magic = magic_of(Mg);
+    P.g_magic = magic_of(Ng);
+    P.col_fast = rest > 1 ? 1 : 0;
+    const int64_t columns = outer * rest;
+    int cols = 1, lg = 0;
+    // (neighbouring columns share 64-byte runs of HBM: at least four where they are interleaved)
+    while (cols * 2 * Mg <= kTileCells && cols < 64 && (columns / (2 * cols) >= 512 || (P.col_fast && cols < 4))) {
+      cols *= 2;
+      ++lg;
+    }
+    P.cols = cols;
+    P.lg_cols = lg;
+    const int ns = (int)st.size();
+    std::vector<int> stride((size_t)ns);
+    // strides in slots of one cell (col_fast: of all columns' values of a cell).  An LDS access serves 16 lanes of
+    // 16 bytes at a time: lanes run over the innermost digit, or, in the innermost stage's pass, over the next one,
+    // whose stride is made odd.
+    const int64_t slot = P.col_fast ? cols : 1;
+    int64_t s = 1;
+    for (int i = ns - 1; i >= 0; --i) {
+      stride[(size_t)i] = (int)(s * slot);
+      s *= st[(size_t)i].nout;
+      if (i == ns - 1 && slot < 16) s |= 1;
+    }
+    P.col_stride = P.col_fast ? 1 : (int32_t)(s | 1);
+    g.lds = (size_t)(P.col_fast ? s * slot : (s | 1) * cols) * 16;
+    P.n_pass = ns;
+    P.load_lines = (int32_t)(Mg / st[0].nin);
+    P.load_magic = magic_of(P.load_lines);
+    for (int i = 0; i < ns; ++i) {
+      InvPass& p = P.pass[i];
+      p.f = st[(size_t)i].nin;
+      p.stride = stride[(size_t)i];
+      p.lines = (int32_t)(Mg / p.f);
+      p.magic = magic_of(p.lines);
+      p.tab = (int32_t)g.tab.size();
+      p.tj = -1;
+      p.tw = tw_off[st[(size_t)i].axis];
+      std::vector<uint16_t> steps;
+      for (int64_t line = 0; line < p.lines; ++line) {
+        int64_t r = line, off = 0, j = 0;
+        for (int q = ns - 1; q >= 0; --q) {
+          if (q == i) continue;
+          const int64_t digit = r % st[(size_t)q].nin;
+          r /= st[(size_t)q].nin;
+          off += digit * stride[(size_t)q];
+          if (st[(size_t)q].axis == st[(size_t)i].axis && q > i) j += digit * st[(size_t)q].rem;
+        }
+        g.tab.push_back((uint16_t)off);
+        steps.push_back((uint16_t)(j * st[(size_t)i].done));
+      }
+      if (st[(size_t)i].rem > 1) {
+        p.tj = (int32_t)g.tab.size();
+        g.tab.insert(g.tab.end(), steps.begin(), steps.end());
+      }
+    }
+    // valid lag o (row-major over the group's axes, Delta_k = o_k - (n_k - 1)) -> offset of the output Delta mod m
+    P.out_tab = (int32_t)g.tab.size();
+    for (int64_t o = 0; o < Ng; ++o) {
+      int64_t r = o, off = 0;
+      for (int a = g.axis0 + g.axes - 1; a >= g.axis0; --a) {
+        const int nout = 2 * n[a] - 1;
+        int delta = (int)(r % nout) - (n[a] - 1);
+        r /= nout;
+        if (delta < 0) delta += m[a];
+        for (int q = 0; q < ns; ++q)
+          if (st[(size_t)q].axis == a) off += (int64_t)((delta / st[(size_t)q].done) % st[(size_t)q].nout) * stride[(size_t)q];
+      }
+      g.tab.push_back((uint16_t)off);
+    }
+    tab_off += g.tab.size();
+    outer *= Ng;
+    out.push_back(std::move(g));
+  }
+  return out;
 }
 
 }  // namespace omni

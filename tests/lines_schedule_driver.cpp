@@ -1,7 +1,8 @@
-// CPU check of the line kernel's schedules: every table, stride and division of lines.hpp executed on the host in
+// CPU check of the line kernel's schedules and of the inverse's: every table, stride and division of lines.hpp executed on the host in
 // float64 with bounds checks, for grids given on stdin ("n_1 ... n_d [b1|b2]", the suffix: that many innermost axes
 // unpadded), against plain zero-padded DFTs.  Prints how many schedules were checked and how many
 // grids have none.
+#include "inverse.hpp"
 #include "lines_plan.hpp"
 
 #include <cmath>
@@ -173,6 +174,113 @@ static int check(const std::string& name, const std::vector<int>& n, const std::
   return 0;
 }
 
+// The inverse's groups executed on the host: random complex cells [channels][M][inner] against plain sums.
+static int check_inverse(const std::string& name, const std::vector<int>& n, int channels, int inner_last) {
+  const int d = (int)n.size();
+  std::vector<int> m, off;
+  int64_t M = 1, at = 0;
+  std::vector<cd> tw;
+  for (int v : n) {
+    m.push_back(2 * v);
+    off.push_back((int)at);
+    for (int q = 0; q < 2 * v; ++q) tw.push_back(std::conj(w(q, 2 * v)));
+    at += 2 * v;
+    M *= 2 * v;
+  }
+  const auto groups = omni::plan_inverse(d, n.data(), m.data(), channels, inner_last, off.data());
+  std::vector<cd> cur, ref;
+  unsigned seed = 777;
+  for (int64_t i = 0; i < channels * M * inner_last; ++i) {
+    seed = seed * 1664525u + 1013904223u;
+    cur.push_back(cd((int)(seed >> 24) - 128, (int)((seed >> 16) & 255) - 128));
+  }
+  ref = cur;
+  int64_t outer = channels, inner = M * inner_last, axis = 0;
+  for (const auto& g : groups) {
+    CHECK(g.axis0 == axis && g.axes >= 1);
+    // reference: the group's axes one by one
+    int64_t o2 = outer, i2 = inner, Mg = 1, Ng = 1;
+    for (int k = g.axis0; k < g.axis0 + g.axes; ++k) {
+      const int nk = n[(size_t)k], mk = m[(size_t)k], lags = 2 * nk - 1;
+      i2 /= mk;
+      std::vector<cd> nx((size_t)(o2 * lags * i2));
+      for (int64_t o = 0; o < o2; ++o)
+        for (int l = 0; l < lags; ++l)
+          for (int64_t i = 0; i < i2; ++i) {
+            cd z = 0;
+            for (int q = 0; q < mk; ++q)
+              z += ref[(size_t)((o * mk + q) * i2 + i)] * std::conj(w((long long)q * ((l - (nk - 1) + mk) % mk), mk));
+            nx[(size_t)((o * lags + l) * i2 + i)] = z;
+          }
+      ref.swap(nx);
+      o2 *= lags;
+      Mg *= mk;
+      Ng *= lags;
+    }
+    inner /= Mg;
+    axis += g.axes;
+    if (!g.direct) {
+      const omni::InvP& P = g.P;
+      CHECK(P.Mg == Mg && P.Ng == Ng && P.cols >= 1 && P.cols == 1 << P.lg_cols && (P.col_fast != 0) == (inner > 1));
+      CHECK((int64_t)P.cols * Mg <= 4096 && P.cols <= 64 && g.lds <= 160 * 1024 && P.n_pass >= 1 && P.n_pass <= omni::kInvMaxPass);
+      const int64_t lds_n = (int64_t)g.lds / 16, columns = outer * inner;
+      std::vector<cd> out((size_t)(columns * Ng), cd(NAN, NAN));
+      for (int64_t col0 = 0; col0 < columns; col0 += P.cols) {
+        std::vector<cd> W((size_t)lds_n, cd(NAN, NAN));
+        for (int c = 0; c < P.cols; ++c)
+          for (uint32_t cell = 0; cell < (uint32_t)Mg; ++cell) {
+            const int64_t col = col0 + c, ou = col / inner, in = col % inner;
+            CHECK(fast_div(cell, P.load_magic) == cell / P.load_lines);
+            const int64_t j = cell / P.load_lines, line = cell % P.load_lines;
+            const int64_t a = (int64_t)c * P.col_stride + g.tab[(size_t)(P.pass[0].tab + line)] + j * P.pass[0].stride;
+            CHECK(a < lds_n && std::isnan(W[(size_t)a].real()));
+            W[(size_t)a] = col < columns ? cur[(size_t)((ou * Mg + cell) * inner + in)] : cd(0, 0);
+          }
+        for (int pi = 0; pi < P.n_pass; ++pi) {
+          const omni::InvPass& p = P.pass[pi];
+          for (uint32_t q = 0; q < (uint32_t)(p.lines * P.cols); ++q) {
+            CHECK(fast_div(q, p.magic) == q / p.lines);
+            const int64_t c = q / p.lines, line = q % p.lines;
+            const int64_t b = c * P.col_stride + g.tab[(size_t)(p.tab + line)];
+            std::vector<cd> x;
+            for (int j = 0; j < p.f; ++j) {
+              CHECK(b + (int64_t)j * p.stride < lds_n);
+              x.push_back(W[(size_t)(b + (int64_t)j * p.stride)]);
+              CHECK(!std::isnan(x.back().real()));
+            }
+            for (int k = 0; k < p.f; ++k) {
+              cd z = 0;
+              for (int j = 0; j < p.f; ++j) z += x[(size_t)j] * std::conj(w((long long)j * k, p.f));
+              if (p.tj >= 0) {
+                const int e = p.tw + k * g.tab[(size_t)(p.tj + line)];
+                CHECK(e < (int)tw.size());
+                z *= tw[(size_t)e];
+              }
+              W[(size_t)(b + (int64_t)k * p.stride)] = z;
+            }
+          }
+        }
+        for (int c = 0; c < P.cols && col0 + c < columns; ++c)
+          for (uint32_t o = 0; o < (uint32_t)Ng; ++o) {
+            CHECK(fast_div(o, P.g_magic) == o / Ng);
+            const int64_t ou = (col0 + c) / inner, in = (col0 + c) % inner;
+            const int64_t a = (int64_t)c * P.col_stride + g.tab[(size_t)(P.out_tab + o)];
+            CHECK(a < lds_n);
+            out[(size_t)((ou * Ng + o) * inner + in)] = W[(size_t)a];
+          }
+      }
+      for (uint32_t q = 0; q < (uint32_t)(P.cols * Mg); ++q) CHECK(fast_div(q, P.m_magic) == q / Mg);
+      for (uint32_t q = 0; q < (uint32_t)(P.cols * Ng); ++q) CHECK(fast_div(q, P.g_magic) == q / Ng);
+      CHECK(out.size() == ref.size());
+      for (size_t i = 0; i < out.size(); ++i) CHECK(std::abs(out[i] - ref[i]) <= 1e-9 * 256.0 * M);
+    }
+    cur = ref;
+    outer *= Ng;
+  }
+  CHECK(axis == d && inner == inner_last);
+  return 0;
+}
+
 int main() {
   std::string line;
   int done = 0, none = 0;
@@ -189,6 +297,11 @@ int main() {
     }
     std::vector<int> m;
     for (size_t k = 0; k < n.size(); ++k) m.push_back((int)(n.size() - k) <= beams ? n[k] : 2 * n[k]);
+    int64_t M = 1;
+    for (int v : n) M *= 2 * v;
+    for (int ch : {1, 3, 40})
+      for (int inner : {1, 5})
+        if (M * ch * inner <= 80000 && check_inverse(line, n, ch, inner)) return 1;
     for (int max_batch : {64, 3}) {
       bool planned = false;
       if (check(line, n, m, max_batch, &planned)) return 1;

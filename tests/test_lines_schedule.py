@@ -1,7 +1,8 @@
 """Schedules of the general (line) kernel on the CPU: the planner's tables, strides, splits and divisions executed
 in float64 with bounds checks by tests/lines_schedule_driver.cpp, against plain zero-padded DFTs, for axes of every
 length up to 64 whose prime factors have a register transform, mixed-size grids of one to eight axes, grids that are
-split among work-groups, and beam-space grids (unpadded innermost axes)."""
+split among work-groups, and beam-space grids (unpadded innermost axes); and the inverse's groups for the same
+grids, one to 40 channels, with and without values behind the last axis, against plain inverse sums."""
 
 import os
 import shutil
