@@ -15,16 +15,27 @@
 namespace omni {
 namespace {
 
-constexpr int kInvUnroll = 8;  // cells a thread has in flight while it loads and stores
-
 __device__ __forceinline__ uint32_t fast_div(uint32_t q, uint32_t magic) {
   return magic ? __umulhi(q, magic) : q;
 }
 
-template <int N>
-__device__ __forceinline__ void inv_pass(const InvPass& p, const InvP& P, double2* W, const uint16_t* __restrict__ tab,
-                                         const double2* __restrict__ twi) {
-  const uint32_t jobs = (uint32_t)(p.lines * P.cols);
+struct Ctx {
+  double2* W;
+  const double2* __restrict__ twi;
+  const uint16_t* __restrict__ tab;
+  const void* __restrict__ src;
+  float2* __restrict__ dst;
+  int64_t src0, dst0, inner;  // of this thread's column (interleaved columns) or of the tile (whole columns)
+  double scale;
+  int n_cols;                 // columns of this tile
+  bool mine;                  // this thread's column exists (interleaved columns)
+};
+
+// One pass' lines: FIRST reads them from HBM, otherwise from LDS; LAST writes the valid lags to HBM.
+// SRC: 0 = real float64, 1 = complex float32, 2 = complex float64.
+template <int N, int SRC, bool FIRST, bool LAST>
+__device__ __forceinline__ void inv_pass(const InvPass& p, const InvP& P, const Ctx& x) {
+  const uint32_t jobs = (uint32_t)(p.lines * (P.col_fast ? P.cols : x.n_cols));
   for (uint32_t q = threadIdx.x; q < jobs; q += blockDim.x) {
     uint32_t c, line;
     if (P.col_fast) {
@@ -34,109 +45,106 @@ __device__ __forceinline__ void inv_pass(const InvPass& p, const InvP& P, double
       c = fast_div(q, p.magic);
       line = q - c * p.lines;
     }
-    double2* w = W + c * P.col_stride + tab[p.tab + line];
-    double2 x[N];
+    double2 v[N];
+    if constexpr (FIRST) {
+      const int64_t at = x.src0 + (P.col_fast ? (int64_t)line * x.inner : (int64_t)(c * P.Mg + line));
+      const int64_t step = P.col_fast ? (int64_t)p.lines * x.inner : (int64_t)p.lines;
 #pragma unroll
-    for (int j = 0; j < N; ++j) x[j] = w[j * p.stride];
-    dn::dft<N>(x);
-    if (p.tj >= 0) {
-      const int step = tab[p.tj + line];
-#pragma unroll
-      for (int k = 1; k < N; ++k) {
-        const double2 t = twi[p.tw + k * step];
-        x[k] = dn::mul(x[k], make_double2(t.x, -t.y));
+      for (int j = 0; j < N; ++j) {
+        if (!x.mine) {
+          v[j] = make_double2(0.0, 0.0);
+        } else if constexpr (SRC == 0) {
+          v[j] = make_double2(0.0, static_cast<const double*>(x.src)[at + j * step]);
+        } else if constexpr (SRC == 1) {
+          const float2 t = static_cast<const float2*>(x.src)[at + j * step];
+          v[j] = make_double2(t.y, t.x);
+        } else {
+          const double2 t = static_cast<const double2*>(x.src)[at + j * step];
+          v[j] = make_double2(t.y, t.x);
+        }
       }
     }
+    double2* w = x.W + (FIRST && LAST ? 0 : c * P.col_stride + x.tab[p.tab + line]);
+    if constexpr (!FIRST) {
 #pragma unroll
-    for (int k = 0; k < N; ++k) w[k * p.stride] = x[k];
+      for (int j = 0; j < N; ++j) v[j] = w[j * p.stride];
+    }
+    dn::dft<N>(v);
+    if constexpr (!LAST) {
+      if (p.tj >= 0) {
+        const int step = x.tab[p.tj + line];
+#pragma unroll
+        for (int k = 1; k < N; ++k) {
+          const double2 t = x.twi[p.tw + k * step];
+          v[k] = dn::mul(v[k], make_double2(t.x, -t.y));
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < N; ++k) w[k * p.stride] = v[k];
+    } else if (x.mine) {
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        const uint32_t o = x.tab[P.out_tab + k * p.lines + line];
+        if (o == kInvNoLag) continue;
+        x.dst[x.dst0 + (P.col_fast ? (int64_t)o * x.inner : (int64_t)(c * P.Ng + o))] =
+            make_float2((float)(v[k].y * x.scale), (float)(v[k].x * x.scale));
+      }
+    }
   }
 }
 
-// SRC: 0 = real float64, 1 = complex float32, 2 = complex float64.
+template <int SRC, bool FIRST, bool LAST>
+__device__ __forceinline__ void inv_any(const InvPass& p, const InvP& P, const Ctx& x) {
+  switch (p.f) {
+    case 2: inv_pass<2, SRC, FIRST, LAST>(p, P, x); break;
+    case 3: inv_pass<3, SRC, FIRST, LAST>(p, P, x); break;
+    case 4: inv_pass<4, SRC, FIRST, LAST>(p, P, x); break;
+    case 5: inv_pass<5, SRC, FIRST, LAST>(p, P, x); break;
+    case 6: inv_pass<6, SRC, FIRST, LAST>(p, P, x); break;
+    case 7: inv_pass<7, SRC, FIRST, LAST>(p, P, x); break;
+    case 8: inv_pass<8, SRC, FIRST, LAST>(p, P, x); break;
+    case 11: inv_pass<11, SRC, FIRST, LAST>(p, P, x); break;
+    case 13: inv_pass<13, SRC, FIRST, LAST>(p, P, x); break;
+    case 16: inv_pass<16, SRC, FIRST, LAST>(p, P, x); break;
+    default: break;
+  }
+}
+
 template <int SRC>
-__global__ __launch_bounds__(512) void inverse_group_kernel(const void* __restrict__ src, float2* __restrict__ dst,
+__global__ __launch_bounds__(512, 4) void inverse_group_kernel(const void* __restrict__ src, float2* __restrict__ dst,
                                                             const double2* __restrict__ twi,
                                                             const uint16_t* __restrict__ tab, int64_t columns,
                                                             int64_t inner, double scale, InvP P) {
   extern __shared__ double2 W[];
-  const uint32_t tid = threadIdx.x, nt = blockDim.x;
   // consecutive column tiles on one XCD: where the columns are interleaved, tiles share cache lines
   int64_t blk = blockIdx.x;
   if (gridDim.x % 8 == 0) blk = (blk & 7) * (gridDim.x >> 3) + (blk >> 3);
   const int64_t col0 = blk * P.cols;
-  // interleaved columns: this thread's column is fixed (the thread count is a multiple of cols), cells step through
-  // the source; whole columns: the tile is one contiguous run
-  const uint32_t tc = tid & (uint32_t)(P.cols - 1);
-  const int64_t col = col0 + tc, ou = P.col_fast ? col / inner : 0;
-  const int64_t src0 = P.col_fast ? ou * P.Mg * inner + (col - ou * inner) : col0 * P.Mg;
-  const int64_t dst0 = P.col_fast ? ou * P.Ng * inner + (col - ou * inner) : col0 * P.Ng;
-  const bool mine = !P.col_fast || col < columns;
-  const uint32_t n_in = (uint32_t)(P.col_fast ? P.cols : min<int64_t>(P.cols, columns - col0)) * P.Mg;
-  const uint32_t n_out = (uint32_t)(P.col_fast ? P.cols : min<int64_t>(P.cols, columns - col0)) * P.Ng;
-  for (uint32_t e0 = tid; e0 < n_in; e0 += kInvUnroll * nt) {
-    double2 v[kInvUnroll];
-#pragma unroll
-    for (int u = 0; u < kInvUnroll; ++u) {
-      const uint32_t e = e0 + u * nt;
-      v[u] = make_double2(0.0, 0.0);
-      if (e >= n_in || !mine) continue;
-      const int64_t at = src0 + (P.col_fast ? (int64_t)(e >> P.lg_cols) * inner : (int64_t)e);
-      if constexpr (SRC == 0) {
-        v[u].y = static_cast<const double*>(src)[at];
-      } else if constexpr (SRC == 1) {
-        const float2 t = static_cast<const float2*>(src)[at];
-        v[u] = make_double2(t.y, t.x);
-      } else {
-        const double2 t = static_cast<const double2*>(src)[at];
-        v[u] = make_double2(t.y, t.x);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kInvUnroll; ++u) {
-      const uint32_t e = e0 + u * nt;
-      if (e >= n_in) continue;
-      const uint32_t c = P.col_fast ? tc : fast_div(e, P.m_magic);
-      const uint32_t cell = P.col_fast ? e >> P.lg_cols : e - c * P.Mg;
-      const uint32_t j = fast_div(cell, P.load_magic), line = cell - j * P.load_lines;
-      W[c * P.col_stride + tab[P.pass[0].tab + line] + j * P.pass[0].stride] = v[u];
-    }
+  // interleaved columns: this thread's column is fixed (the thread count is a multiple of cols); whole columns: the
+  // tile is one contiguous run
+  const int64_t col = col0 + (threadIdx.x & (uint32_t)(P.cols - 1)), ou = P.col_fast ? col / inner : 0;
+  const Ctx x{W,
+              twi,
+              tab,
+              src,
+              dst,
+              P.col_fast ? ou * P.Mg * inner + (col - ou * inner) : col0 * P.Mg,
+              P.col_fast ? ou * P.Ng * inner + (col - ou * inner) : col0 * P.Ng,
+              inner,
+              scale,
+              (int)min<int64_t>(P.cols, columns - col0),
+              !P.col_fast || col < columns};
+  if (P.n_pass == 1) {
+    inv_any<SRC, true, true>(P.pass[0], P, x);
+    return;
+  }
+  inv_any<SRC, true, false>(P.pass[0], P, x);
+  for (int i = 1; i + 1 < P.n_pass; ++i) {
+    __syncthreads();
+    inv_any<1, false, false>(P.pass[i], P, x);
   }
   __syncthreads();
-  for (int i = 0; i < P.n_pass; ++i) {
-    const InvPass& p = P.pass[i];
-    switch (p.f) {
-      case 2: inv_pass<2>(p, P, W, tab, twi); break;
-      case 3: inv_pass<3>(p, P, W, tab, twi); break;
-      case 4: inv_pass<4>(p, P, W, tab, twi); break;
-      case 5: inv_pass<5>(p, P, W, tab, twi); break;
-      case 6: inv_pass<6>(p, P, W, tab, twi); break;
-      case 7: inv_pass<7>(p, P, W, tab, twi); break;
-      case 8: inv_pass<8>(p, P, W, tab, twi); break;
-      case 11: inv_pass<11>(p, P, W, tab, twi); break;
-      case 13: inv_pass<13>(p, P, W, tab, twi); break;
-      case 16: inv_pass<16>(p, P, W, tab, twi); break;
-      default: break;
-    }
-    __syncthreads();
-  }
-  for (uint32_t e0 = tid; e0 < n_out; e0 += kInvUnroll * nt) {
-    uint32_t off[kInvUnroll];
-#pragma unroll
-    for (int u = 0; u < kInvUnroll; ++u) {
-      const uint32_t e = min(e0 + u * nt, n_out - 1);
-      const uint32_t c = P.col_fast ? tc : fast_div(e, P.g_magic);
-      const uint32_t o = P.col_fast ? e >> P.lg_cols : e - c * P.Ng;
-      off[u] = c * P.col_stride + tab[P.out_tab + o];
-    }
-#pragma unroll
-    for (int u = 0; u < kInvUnroll; ++u) {
-      const uint32_t e = e0 + u * nt;
-      if (e >= n_out || !mine) continue;
-      const double2 v = W[off[u]];
-      dst[dst0 + (P.col_fast ? (int64_t)(e >> P.lg_cols) * inner : (int64_t)e)] =
-          make_float2((float)(v.y * scale), (float)(v.x * scale));
-    }
-  }
+  inv_any<1, false, true>(P.pass[P.n_pass - 1], P, x);
 }
 
 }  // namespace

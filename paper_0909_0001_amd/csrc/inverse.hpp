@@ -2,9 +2,10 @@
 //
 // The inverse runs along groups of consecutive axes.  A group sees its source as [outer][M_g][inner], M_g the product
 // of its axes' lengths m_k, and gives [outer][N_g][inner], N_g the product of their 2 n_k - 1 valid lags.  A
-// work-group takes a few (outer, inner) columns into LDS as complex float64, transforms every axis there (stages as
-// in lines.hpp, all plain: in place, one thread a line) and writes the valid lags.  The axes of a group need no
-// round trip through HBM between them, and all their sums and intermediates are float64; only the values between
+// work-group transforms a few (outer, inner) columns in LDS as complex float64 (stages as in lines.hpp, all plain: in
+// place, one thread a line); the first pass takes its lines straight from HBM, the last one writes the valid lags
+// straight to it.  The first axis' last stage comes last, so that neighbouring lines of that pass are neighbouring
+// lags of the inner axes.  The axes of a group need no round trip through HBM between them, and all their sums and intermediates are float64; only the values between
 // two groups are stored as complex float32.
 #pragma once
 
@@ -16,6 +17,7 @@
 namespace omni {
 
 constexpr int kInvMaxPass = 16;
+constexpr uint32_t kInvNoLag = 0xffff;
 
 struct InvPass {
   int32_t f;       // values per line
@@ -34,10 +36,7 @@ struct InvP {
   int32_t col_fast;    // 1: neighbouring threads take neighbouring columns (inner > 1); 0: neighbouring cells
   int32_t col_stride;  // double2 elements between columns
   int32_t Mg, Ng;      // cells and valid lags per column
-  uint32_t m_magic, g_magic;  // division by Mg and by Ng
-  int32_t load_lines;  // Mg / f of pass 0: cell i is value i / load_lines of line i % load_lines
-  uint32_t load_magic;
-  int32_t out_tab;     // first entry of the lags' offsets
+  int32_t out_tab;     // last pass: lag of value k of each line at out_tab + k * lines + line (kInvNoLag: none)
   InvPass pass[kInvMaxPass];
 };
 

@@ -385,7 +385,7 @@ std::vector<InvGroup> plan_inverse(int d, const int* n, const int* m, int64_t ch
         one.push_back({k, f, f, false, done, rem});
         done *= f;
       }
-      if ((int)(st.size() + one.size()) > kInvMaxPass) break;
+      if ((int)(st.size() + one.size()) > kInvMaxPass - 1) break;
       st.insert(st.end(), one.begin(), one.end());
       Mg *= m[k];
       Ng *= 2 * n[k] - 1;
@@ -396,8 +396,6 @@ std::vector<InvGroup> plan_inverse(int d, const int* n, const int* m, int64_t ch
     InvP& P = g.P;
     P.Mg = (int32_t)Mg;
     P.Ng = (int32_t)Ng;
-    P.m_magic = magic_of(Mg);
-    P.g_magic = magic_of(Ng);
     P.col_fast = rest > 1 ? 1 : 0;
     const int64_t columns = outer * rest;
     int cols = 1, lg = 0;
@@ -408,6 +406,17 @@ std::vector<InvGroup> plan_inverse(int d, const int* n, const int* m, int64_t ch
     }
     P.cols = cols;
     P.lg_cols = lg;
+    if (!P.col_fast && g.axes > 1 && (st.size() < 2 || st[1].axis != st[0].axis) && m[g.axis0] > 2) {
+      // whole columns: the last pass' lines must be neighbouring lags of the inner axes, so the first axis gets two
+      // stages, one to read with and one to write with
+      const int mm = m[g.axis0];
+      int f = 2;
+      for (int v : kLinePlain)
+        if (mm % v == 0 && v * v <= mm && has(kLinePlain, mm / v)) f = v;
+      st.insert(st.begin(), st[0]);
+      st[0] = {g.axis0, f, f, false, 1, mm / f};
+      st[1] = {g.axis0, mm / f, mm / f, false, f, 1};
+    }
     const int ns = (int)st.size();
     std::vector<int> stride((size_t)ns);
     // strides in slots of one cell (col_fast: of all columns' values of a cell).  An LDS access serves 16 lanes of
@@ -423,10 +432,21 @@ std::vector<InvGroup> plan_inverse(int d, const int* n, const int* m, int64_t ch
     P.col_stride = P.col_fast ? 1 : (int32_t)(s | 1);
     g.lds = (size_t)(P.col_fast ? s * slot : (s | 1) * cols) * 16;
     P.n_pass = ns;
-    P.load_lines = (int32_t)(Mg / st[0].nin);
-    P.load_magic = magic_of(P.load_lines);
-    for (int i = 0; i < ns; ++i) {
-      InvPass& p = P.pass[i];
+    // pass order: stage 0 first, the first axis' last stage last
+    int own = 1;
+    while (own < ns && st[(size_t)own].axis == st[0].axis) ++own;
+    std::vector<int> order;
+    for (int i = 0; i < own - 1; ++i) order.push_back(i);
+    if (own == 1 && ns > 1) {
+      // the first axis has one stage, which reads HBM: another axis' last stage writes
+      order.push_back(0);
+      own = 0;
+    }
+    for (int i = std::max(own, 1); i < ns; ++i) order.push_back(i);
+    if (own > 0) order.push_back(own - 1);
+    for (int at = 0; at < ns; ++at) {
+      const int i = order[(size_t)at];
+      InvPass& p = P.pass[at];
       p.f = st[(size_t)i].nin;
       p.stride = stride[(size_t)i];
       p.lines = (int32_t)(Mg / p.f);
@@ -435,9 +455,12 @@ std::vector<InvGroup> plan_inverse(int d, const int* n, const int* m, int64_t ch
       p.tj = -1;
       p.tw = tw_off[st[(size_t)i].axis];
       std::vector<uint16_t> steps;
+      // whole columns of one axis: the last pass takes its lines in the order of their lags
+      const bool by_lag = at + 1 == ns && ns > 1 && g.axes == 1 && !P.col_fast;
       for (int64_t line = 0; line < p.lines; ++line) {
         int64_t r = line, off = 0, j = 0;
-        for (int q = ns - 1; q >= 0; --q) {
+        for (int q0 = ns - 1; q0 >= 0; --q0) {
+          const int q = by_lag ? ns - 1 - q0 : q0;
           if (q == i) continue;
           const int64_t digit = r % st[(size_t)q].nin;
           r /= st[(size_t)q].nin;
@@ -452,20 +475,34 @@ std::vector<InvGroup> plan_inverse(int d, const int* n, const int* m, int64_t ch
         g.tab.insert(g.tab.end(), steps.begin(), steps.end());
       }
     }
-    // valid lag o (row-major over the group's axes, Delta_k = o_k - (n_k - 1)) -> offset of the output Delta mod m
+    // value k of each line of the last pass -> its lag (row-major over the group's axes, Delta_k + n_k - 1)
     P.out_tab = (int32_t)g.tab.size();
-    for (int64_t o = 0; o < Ng; ++o) {
-      int64_t r = o, off = 0;
-      for (int a = g.axis0 + g.axes - 1; a >= g.axis0; --a) {
-        const int nout = 2 * n[a] - 1;
-        int delta = (int)(r % nout) - (n[a] - 1);
-        r /= nout;
-        if (delta < 0) delta += m[a];
-        for (int q = 0; q < ns; ++q)
-          if (st[(size_t)q].axis == a) off += (int64_t)((delta / st[(size_t)q].done) % st[(size_t)q].nout) * stride[(size_t)q];
+    const int li = order.back(), lf = st[(size_t)li].nin;
+    std::vector<int> digit((size_t)ns);
+    for (int k = 0; k < lf; ++k)
+      for (int64_t line = 0; line < Mg / lf; ++line) {
+        int64_t r = line;
+        for (int q0 = ns - 1; q0 >= 0; --q0) {
+          const int q = ns > 1 && g.axes == 1 && !P.col_fast ? ns - 1 - q0 : q0;
+          if (q == li) {
+            digit[(size_t)q] = k;
+            continue;
+          }
+          digit[(size_t)q] = (int)(r % st[(size_t)q].nin);
+          r /= st[(size_t)q].nin;
+        }
+        int64_t o = 0;
+        bool valid = true;
+        for (int a = g.axis0; a < g.axis0 + g.axes; ++a) {
+          int delta = 0;
+          for (int q = 0; q < ns; ++q)
+            if (st[(size_t)q].axis == a) delta += digit[(size_t)q] * st[(size_t)q].done;
+          if (delta == n[a]) valid = false;
+          if (delta >= n[a]) delta -= m[a];
+          o = o * (2 * n[a] - 1) + delta + n[a] - 1;
+        }
+        g.tab.push_back(valid ? (uint16_t)o : (uint16_t)kInvNoLag);
       }
-      g.tab.push_back((uint16_t)off);
-    }
     tab_off += g.tab.size();
     outer *= Ng;
     out.push_back(std::move(g));

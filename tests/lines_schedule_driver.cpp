@@ -227,23 +227,20 @@ static int check_inverse(const std::string& name, const std::vector<int>& n, int
       std::vector<cd> out((size_t)(columns * Ng), cd(NAN, NAN));
       for (int64_t col0 = 0; col0 < columns; col0 += P.cols) {
         std::vector<cd> W((size_t)lds_n, cd(NAN, NAN));
-        for (int c = 0; c < P.cols; ++c)
-          for (uint32_t cell = 0; cell < (uint32_t)Mg; ++cell) {
-            const int64_t col = col0 + c, ou = col / inner, in = col % inner;
-            CHECK(fast_div(cell, P.load_magic) == cell / P.load_lines);
-            const int64_t j = cell / P.load_lines, line = cell % P.load_lines;
-            const int64_t a = (int64_t)c * P.col_stride + g.tab[(size_t)(P.pass[0].tab + line)] + j * P.pass[0].stride;
-            CHECK(a < lds_n && std::isnan(W[(size_t)a].real()));
-            W[(size_t)a] = col < columns ? cur[(size_t)((ou * Mg + cell) * inner + in)] : cd(0, 0);
-          }
         for (int pi = 0; pi < P.n_pass; ++pi) {
           const omni::InvPass& p = P.pass[pi];
+          const bool first = pi == 0, last = pi + 1 == P.n_pass;
+          CHECK((int64_t)p.lines * p.f == Mg && p.tab + p.lines <= (int)g.tab.size());
           for (uint32_t q = 0; q < (uint32_t)(p.lines * P.cols); ++q) {
             CHECK(fast_div(q, p.magic) == q / p.lines);
-            const int64_t c = q / p.lines, line = q % p.lines;
+            const int64_t c = q / p.lines, line = q % p.lines, col = col0 + c, ou = col / inner, in = col % inner;
             const int64_t b = c * P.col_stride + g.tab[(size_t)(p.tab + line)];
             std::vector<cd> x;
             for (int j = 0; j < p.f; ++j) {
+              if (first) {
+                x.push_back(col < columns ? cur[(size_t)((ou * Mg + (int64_t)j * p.lines + line) * inner + in)] : cd(0, 0));
+                continue;
+              }
               CHECK(b + (int64_t)j * p.stride < lds_n);
               x.push_back(W[(size_t)(b + (int64_t)j * p.stride)]);
               CHECK(!std::isnan(x.back().real()));
@@ -251,26 +248,26 @@ static int check_inverse(const std::string& name, const std::vector<int>& n, int
             for (int k = 0; k < p.f; ++k) {
               cd z = 0;
               for (int j = 0; j < p.f; ++j) z += x[(size_t)j] * std::conj(w((long long)j * k, p.f));
+              if (last) {
+                CHECK(p.tj < 0);
+                const uint32_t o = g.tab[(size_t)(P.out_tab + k * p.lines + line)];
+                if (o == omni::kInvNoLag || col >= columns) continue;
+                CHECK(o < Ng && std::isnan(out[(size_t)((ou * Ng + o) * inner + in)].real()));
+                out[(size_t)((ou * Ng + o) * inner + in)] = z;
+                continue;
+              }
               if (p.tj >= 0) {
                 const int e = p.tw + k * g.tab[(size_t)(p.tj + line)];
                 CHECK(e < (int)tw.size());
                 z *= tw[(size_t)e];
               }
-              W[(size_t)(b + (int64_t)k * p.stride)] = z;
+              const int64_t a = b + (int64_t)k * p.stride;
+              CHECK(a < lds_n && (!first || std::isnan(W[(size_t)a].real())));
+              W[(size_t)a] = z;
             }
           }
         }
-        for (int c = 0; c < P.cols && col0 + c < columns; ++c)
-          for (uint32_t o = 0; o < (uint32_t)Ng; ++o) {
-            CHECK(fast_div(o, P.g_magic) == o / Ng);
-            const int64_t ou = (col0 + c) / inner, in = (col0 + c) % inner;
-            const int64_t a = (int64_t)c * P.col_stride + g.tab[(size_t)(P.out_tab + o)];
-            CHECK(a < lds_n);
-            out[(size_t)((ou * Ng + o) * inner + in)] = W[(size_t)a];
-          }
       }
-      for (uint32_t q = 0; q < (uint32_t)(P.cols * Mg); ++q) CHECK(fast_div(q, P.m_magic) == q / Mg);
-      for (uint32_t q = 0; q < (uint32_t)(P.cols * Ng); ++q) CHECK(fast_div(q, P.g_magic) == q / Ng);
       CHECK(out.size() == ref.size());
       for (size_t i = 0; i < out.size(); ++i) CHECK(std::abs(out[i] - ref[i]) <= 1e-9 * 256.0 * M);
     }
