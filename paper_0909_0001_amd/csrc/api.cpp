@@ -2237,7 +2237,7 @@ struct omni_fold_s {
   uint32_t* d_off = nullptr;   // per-pixel offsets into d_cell [npix + 1]
   uint32_t* d_pix = nullptr;   // pixels sorted by radial bin [npix]
   uint32_t* d_boff = nullptr;  // per-bin offsets into d_pix [nbins + 1]
-  double* d_dmax = nullptr;    // per-channel largest pixel [F]
+  double* d_dmax = nullptr;    // largest pixel of each part of a channel [F][kMaxParts]
 };
 
 namespace {
@@ -2291,7 +2291,7 @@ int fold_build(omni_fold_s* f) {
   if (e == hipSuccess) e = hipMalloc(&f->d_cell, (size_t)cells * 4);
   if (e == hipSuccess) e = hipMalloc(&f->d_off, (size_t)(f->npix + 1) * 4);
   if (e == hipSuccess) e = hipMalloc(&f->d_pix, (size_t)f->npix * 4);
-  if (e == hipSuccess) e = hipMalloc(&f->d_dmax, (size_t)f->F * sizeof(double));
+  if (e == hipSuccess) e = hipMalloc(&f->d_dmax, (size_t)f->F * omni::kMaxParts * sizeof(double));
   if (e == hipSuccess) e = omni::launch_fold_keys(f->g, k0, v0, nullptr);
   if (e != hipSuccess) {
     release();
@@ -2429,13 +2429,12 @@ int omni_baseline_profile(omni_fold_t fold, const void* image, int32_t nchan, vo
   if (cur != fold->device) return fail(OMNI_E_STATE, "current HIP device is not the fold's device");
   hipStream_t st = static_cast<hipStream_t>(stream);
   const double2* im = static_cast<const double2*>(image);
-  if (map) {
-    HIP_TRY(omni::launch_channel_max(im, fold->npix, nchan, fold->d_dmax, st));
-    HIP_TRY(omni::launch_asinh_map(im, fold->npix, nchan, fold->d_dmax, static_cast<double*>(map), st));
-  }
+  double* d = static_cast<double*>(map);  // holds the real parts until it becomes the map
+  if (map) HIP_TRY(omni::launch_channel_max(im, fold->npix, nchan, d, fold->d_dmax, st));
   if (hist)
-    HIP_TRY(omni::launch_radial_sum(im, fold->npix, nchan, fold->d_pix, fold->d_boff, fold->nbins,
-                                    static_cast<double*>(hist), st));
+    HIP_TRY(omni::launch_radial_sum(map ? d : static_cast<const double*>(image), map ? 1 : 2, fold->npix, nchan,
+                                    fold->d_pix, fold->d_boff, fold->nbins, static_cast<double*>(hist), st));
+  if (map) HIP_TRY(omni::launch_asinh_map(fold->npix, nchan, fold->d_dmax, d, st));
   if (smooth)
     HIP_TRY(omni::launch_boxcar(static_cast<const double*>(hist), fold->nbins, nchan, fold->boxcar,
                                 static_cast<double*>(smooth), st));

@@ -139,42 +139,79 @@ __global__ void fold_gather_kernel(const float2* __restrict__ vis, int64_t cells
     if (j < nf) image[(int64_t)(f0 + j) * npix + p] = make_double2(re[j], im[j]);
 }
 
-__global__ void channel_max_kernel(const double2* __restrict__ image, int64_t npix, double* __restrict__ dmax) {
-  __shared__ double red[kThreads];
-  const int f = blockIdx.x;
-  const double2* im = image + (int64_t)f * npix;
-  double m = -__builtin_inf();
-  for (int64_t p = threadIdx.x; p < npix; p += kThreads) m = fmax(m, im[p].x);
-  red[threadIdx.x] = m;
-  __syncthreads();
-  for (int s = kThreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + s]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) dmax[f] = red[0];
-}
-
-__global__ void asinh_map_kernel(const double2* __restrict__ image, int64_t npix, const double* __restrict__ dmax,
-                                 double* __restrict__ map) {
-#pragma clang fp contract(off)
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Per channel and part (of kMaxParts): the largest Re image among the part's pixels, into part[f][kMaxParts].  One
+// work-group a channel left the GPU idle (64 channels of 255 x 255 pixels: 71 us; 15 parts a channel, copy included:
+// 16 us).
+// The real parts are also copied to `d`, so that the radial sums and the map read 8 bytes a pixel instead of 16.
+__global__ __launch_bounds__(kThreads) void channel_max_kernel(const double2* __restrict__ image, int64_t npix,
+                                                               double* __restrict__ d, double* __restrict__ part) {
+  __shared__ double red[kThreads / 64];
   const int f = blockIdx.y;
-  if (p >= npix) return;
-  const double m = dmax[f] > 0.0 ? dmax[f] : 1.0;
-  const double x = 4.0 * image[(int64_t)f * npix + p].x / m;
-  map[(int64_t)f * npix + p] = asinh(x);
+  const double2* im = image + (int64_t)f * npix;
+  double* out = d + (int64_t)f * npix;
+  double m = -__builtin_inf();
+  const int64_t step = (int64_t)gridDim.x * kThreads;
+  int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  for (; p + 3 * step < npix; p += 4 * step) {
+    const double a = im[p].x, b = im[p + step].x, c = im[p + 2 * step].x, e = im[p + 3 * step].x;
+    out[p] = a;
+    out[p + step] = b;
+    out[p + 2 * step] = c;
+    out[p + 3 * step] = e;
+    m = fmax(m, fmax(fmax(a, b), fmax(c, e)));
+  }
+  for (; p < npix; p += step) {
+    const double a = im[p].x;
+    out[p] = a;
+    m = fmax(m, a);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kThreads / 64; ++w) m = fmax(m, red[w]);
+    part[(int64_t)f * kMaxParts + blockIdx.x] = m;
+  }
 }
 
-// One wave per (bin, channel): lane l adds pixels l, l + 64, ... of the bin, then a fixed butterfly.
-__global__ void radial_sum_kernel(const double2* __restrict__ image, int64_t npix, const uint32_t* __restrict__ pix,
-                                  const uint32_t* __restrict__ boff, int64_t nbins, double* __restrict__ hist) {
+// map <- asinh(4 map / d_max), d_max the largest of the channel's parts (1 if that is not positive).
+__global__ __launch_bounds__(kThreads) void asinh_map_kernel(int64_t npix, const double* __restrict__ part,
+                                                             int n_parts, double* __restrict__ map) {
+#pragma clang fp contract(off)
+  const int f = blockIdx.y;
+  double m = -__builtin_inf();
+  for (int q = 0; q < n_parts; ++q) m = fmax(m, part[(int64_t)f * kMaxParts + q]);
+  if (!(m > 0.0)) m = 1.0;
+  double* d = map + (int64_t)f * npix;
+  for (int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x; p < npix; p += (int64_t)gridDim.x * kThreads) {
+    const double x = 4.0 * d[p] / m;
+    d[p] = asinh(x);
+  }
+}
+
+// One wave per (bin, channel): lane l adds pixels l, l + 64, ... of the bin, then a fixed butterfly.  The real parts
+// are read with `stride` doubles a pixel: 1 (copied out by channel_max_kernel) or 2 (the image itself).
+__global__ void radial_sum_kernel(const double* __restrict__ re, int stride, int64_t npix,
+                                  const uint32_t* __restrict__ pix, const uint32_t* __restrict__ boff, int64_t nbins,
+                                  double* __restrict__ hist) {
   const int64_t k = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
   const int l = threadIdx.x & 63;
   const int f = blockIdx.y;
   if (k >= nbins) return;
-  const double2* im = image + (int64_t)f * npix;
+  const double* im = re + (int64_t)f * npix * stride;
+  const uint32_t end = boff[k + 1];
   double s = 0.0;
-  for (uint32_t i = boff[k] + l; i < boff[k + 1]; i += 64) s += im[pix[i]].x;
+  uint32_t i = boff[k] + l;
+  for (; i + 192 < end; i += 256) {
+    const double a = im[(int64_t)pix[i] * stride], b = im[(int64_t)pix[i + 64] * stride];
+    const double c = im[(int64_t)pix[i + 128] * stride], e = im[(int64_t)pix[i + 192] * stride];
+    s += a;
+    s += b;
+    s += c;
+    s += e;
+  }
+  for (; i < end; i += 64) s += im[(int64_t)pix[i] * stride];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
   if (l == 0) hist[(int64_t)f * nbins + k] = s;
@@ -236,27 +273,31 @@ hipError_t launch_fold_gather(const float2* vis, int64_t cells, const uint32_t* 
   return hipGetLastError();
 }
 
-hipError_t launch_channel_max(const double2* image, int64_t npix, int F, double* dmax, hipStream_t st) {
-  if (F < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(channel_max_kernel, dim3((unsigned)F), dim3(kThreads), 0, st, image, npix, dmax);
+// Parts per channel: about 4096 pixels each, at most kMaxParts.
+static int max_parts(int64_t npix) { return (int)std::max<int64_t>(1, std::min<int64_t>(kMaxParts, npix / 4096)); }
+
+hipError_t launch_channel_max(const double2* image, int64_t npix, int F, double* d, double* part, hipStream_t st) {
+  if (F < 1 || F > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(channel_max_kernel, dim3((unsigned)max_parts(npix), (unsigned)F), dim3(kThreads), 0, st, image,
+                     npix, d, part);
   return hipGetLastError();
 }
 
-hipError_t launch_asinh_map(const double2* image, int64_t npix, int F, const double* dmax, double* map,
-                            hipStream_t st) {
-  const int64_t blocks = (npix + kThreads - 1) / kThreads;
-  if (F < 1 || F > 65535 || blocks > INT32_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(asinh_map_kernel, dim3((unsigned)blocks, (unsigned)F), dim3(kThreads), 0, st, image, npix, dmax,
+hipError_t launch_asinh_map(int64_t npix, int F, const double* part, double* map, hipStream_t st) {
+  if (F < 1 || F > 65535) return hipErrorInvalidValue;
+  // about four pixels a thread, so that reading the parts is a small share
+  const unsigned blocks = grid_for((npix + 3) / 4);
+  hipLaunchKernelGGL(asinh_map_kernel, dim3(blocks, (unsigned)F), dim3(kThreads), 0, st, npix, part, max_parts(npix),
                      map);
   return hipGetLastError();
 }
 
-hipError_t launch_radial_sum(const double2* image, int64_t npix, int F, const uint32_t* pix, const uint32_t* boff,
-                             int64_t nbins, double* hist, hipStream_t st) {
+hipError_t launch_radial_sum(const double* re, int stride, int64_t npix, int F, const uint32_t* pix,
+                             const uint32_t* boff, int64_t nbins, double* hist, hipStream_t st) {
   const int64_t blocks = (nbins + kThreads / 64 - 1) / (kThreads / 64);
-  if (F < 1 || F > 65535 || blocks > INT32_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(radial_sum_kernel, dim3((unsigned)blocks, (unsigned)F), dim3(kThreads), 0, st, image, npix, pix,
-                     boff, nbins, hist);
+  if (F < 1 || F > 65535 || blocks > INT32_MAX || (stride != 1 && stride != 2)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(radial_sum_kernel, dim3((unsigned)blocks, (unsigned)F), dim3(kThreads), 0, st, re, stride, npix,
+                     pix, boff, nbins, hist);
   return hipGetLastError();
 }
 

@@ -39,13 +39,14 @@ hipError_t sort_pairs(void* tmp, size_t* tmp_bytes, const uint32_t* key_in, uint
 // image[f][p] = sum over the cells of pixel p (ascending cell order) of vis[f][cell], float64 complex.
 hipError_t launch_fold_gather(const float2* vis, int64_t cells, const uint32_t* cell, const uint32_t* off,
                               int64_t npix, int F, int64_t origin, double2* image, hipStream_t st);
-// Per channel: dmax[f] = max_p Re image[f][p]; map (may be null) = asinh(4 Re image / dmax);
-// hist (may be null) [F][nbins] = radial sums; smooth (may be null) = centred boxcar of hist over `width` bins.
-hipError_t launch_channel_max(const double2* image, int64_t npix, int F, double* dmax, hipStream_t st);
-hipError_t launch_asinh_map(const double2* image, int64_t npix, int F, const double* dmax, double* map,
-                            hipStream_t st);
-hipError_t launch_radial_sum(const double2* image, int64_t npix, int F, const uint32_t* pix, const uint32_t* boff,
-                             int64_t nbins, double* hist, hipStream_t st);
+// Per channel: part[f][.] = largest Re image among the channel's parts, d[f][p] = Re image[f][p]; then map (holding d)
+// <- asinh(4 d / max); hist [F][nbins] = radial sums of real parts at re[f][p * stride]; smooth (may be null) = centred
+// boxcar of hist over `width` bins.
+constexpr int kMaxParts = 16;
+hipError_t launch_channel_max(const double2* image, int64_t npix, int F, double* d, double* part, hipStream_t st);
+hipError_t launch_asinh_map(int64_t npix, int F, const double* part, double* map, hipStream_t st);
+hipError_t launch_radial_sum(const double* re, int stride, int64_t npix, int F, const uint32_t* pix,
+                             const uint32_t* boff, int64_t nbins, double* hist, hipStream_t st);
 hipError_t launch_boxcar(const double* hist, int64_t nbins, int F, int width, double* smooth, hipStream_t st);
 
 }  // namespace omni
