@@ -602,8 +602,8 @@ void plan_grid_small(ArrayPlan& ap, int kernel) {
 // The general kernel's schedule for the axes after the front passes: the line kernel where it has one (axes whose
 // prime factors are at most 13, cells divisible along the first axis into LDS-sized shares), else the runtime-shape
 // kernel's schedule that is already in ap.fs.  The line kernel is the faster one on every grid measured (kernel
-// times): 16 x 16 floats, one channel, T = 1024: 57 -> 20 us; 5x3 / 3x3 / 3x3 8-bit, 12 channels, T = 333:
-// 5459 -> 649 us; 2x2 / 16x16 8-bit, 16 channels, T = 250: 414 -> 140 us.
+// times): 16 x 16 floats, one channel, T = 1024: 57 -> 12 us; 5x3 / 3x3 / 3x3 8-bit, 12 channels, T = 333:
+// 5459 -> 410 us; 2x2 / 16x16 8-bit, 16 channels, T = 250: 414 -> 70 us.
 void plan_general(ArrayPlan& ap) {
   FusedSetup& fs = ap.fs;
   const int s = ap.n_front, d = (int)ap.n.size() - s;
@@ -977,12 +977,24 @@ int launch_general(ArrayPlan& ap, const FusedSetup& fs, int fmt, const void* src
     L.fmt = fmt;
     L.time_block = time_block;
     L.batch = std::min(L.batch, time_block);
+    const int64_t per = (int64_t)fs.F * L.n_split, slots = 256 * (int64_t)fs.ls.per_cu;
+    // a short call leaves work-groups idle: smaller batches while they all fit the GPU at once
+    while (L.batch > 1 && per * ((T + L.batch / 2 - 1) / (L.batch / 2)) <= slots) L.batch /= 2;
     L.groups = std::min(L.groups, L.batch);
-    // time slices of whole batches
-    const int64_t per = (int64_t)fs.F * L.n_split;
     const int64_t batches = (T + L.batch - 1) / L.batch;
-    int64_t ns = std::max<int64_t>(1, (ap.wg_target + per - 1) / per);
-    ns = std::min<int64_t>(std::min<int64_t>(ns, ap.max_slices), batches);
+    // slices: the fewest rounds of resident work-groups times a work-group's batches, counting its own start and end
+    // (table, power array, partial sums) as 1.5 batches
+    const int64_t most = std::min<int64_t>(std::min<int64_t>(batches, ap.max_slices),
+                                           std::max<int64_t>(1, 4 * (int64_t)ap.wg_target / per));
+    double best = 1e300;
+    int64_t ns = 1;
+    for (int64_t k = 1; k <= most; ++k) {
+      const double cost = (double)((k * per + slots - 1) / slots) * ((double)((batches + k - 1) / k) + 1.5);
+      if (cost < best) {
+        best = cost;
+        ns = k;
+      }
+    }
     const int64_t tps = (batches + ns - 1) / ns * L.batch;
     ns = (T + tps - 1) / tps;
     L.xcd_groups = (ns * fs.F) % 8 == 0 ? 1 : 0;

@@ -10,6 +10,7 @@
 // The LDS working array has one extent per stage (its outputs; the stage of the last pass its inputs), all strides
 // padded to odd numbers of float2, so that lanes on neighbouring lines of any pass fall on different banks.
 // Passes run in place: a line's inputs lie inside its outputs' slots, and one thread transforms a whole line.
+// Two short zero-padded axes (n1 n2 <= 16) are one pass: its "line" is the n1 x n2 block of both, 4 n1 n2 outputs.
 #pragma once
 
 #include <stdint.h>
@@ -19,8 +20,9 @@ namespace omni {
 constexpr int kLineMaxPass = 16;
 
 struct LinePass {
-  int32_t type;    // inputs per line | 32 if zero-padded (twice as many outputs)
-  int32_t stride;  // float2 elements between a line's consecutive values
+  int32_t type;    // inputs per line | 32 if zero-padded (twice as many outputs); two axes: 256 + 16 n1 + n2
+  int32_t stride;  // float2 elements between a line's consecutive values (two axes: along the first)
+  int32_t stride2; // along the second axis
   int32_t lines;   // lines per sample
   uint32_t magic;  // ceil(2^32 / lines): exact division of q < 2^16 by `lines`
   int32_t tab;     // first entry of the lines' offsets in the table
@@ -41,8 +43,11 @@ struct LineP {
   int32_t n_tw;         // twiddles kept in LDS (0: read from global memory)
   int32_t time_block;   // samples summed in float32 before the float64 add
   int32_t xcd_groups;   // 1: XCD-aware block mapping is valid
-  int32_t load_lines;   // N / n_in of pass 0: sample i is value i / load_lines of line i % load_lines
+  int32_t load_lines;   // N / n_in of stage 0: sample i is value i / load_lines of load line i % load_lines
   uint32_t load_magic;  // division by load_lines
+  int32_t load_tab;     // first entry of the load lines' offsets in the table
+  int32_t load_stride;  // float2 elements between a load line's values
+  int32_t load_tj;      // split form: the load lines' twiddle steps (-1: none)
   uint32_t n_magic;     // division by N
   int32_t f1, n1, m0;   // split form: stage 1 of axis 0 has f1 outputs of n1 inputs; length m0 of axis 0
   int32_t k_out;        // split form: outputs kappa_1 of this work-group, f1 / n_split
@@ -51,7 +56,14 @@ struct LineP {
 };
 
 // Lengths with a register transform, as the first stage of a zero-padded axis (n inputs, 2n outputs) or plain.
-constexpr int kLinePadded[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 11, 12, 13, 16};
+constexpr int kLinePadded[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 16};
 constexpr int kLinePlain[] = {2, 3, 4, 5, 6, 7, 8, 11, 13, 16};
+// Pairs of zero-padded axes that are one pass, n1 >= n2.
+constexpr bool line_pair_ok(int n1, int n2) { return n1 >= n2 && n2 >= 2 && n1 <= 8 && n1 * n2 <= 16; }
+
+// Types whose transforms need at most 64 registers: a schedule of these only runs eight waves a SIMD instead of four.
+constexpr bool line_type_small(int type) {
+  return type >= 256 ? (type - 256) / 16 * (type & 15) <= 6 || type == 256 + 51 || type == 256 + 66 : (type & 31) <= 8;
+}
 
 }  // namespace omni

@@ -9,10 +9,13 @@
 //          and adds the sums to the float32 power array in LDS (Sec. II.A: square modulus, time integration).
 // Every time_block samples the power array is added to the float64 partial sums in HBM.
 //
-// What bounds it: the short lines leave few jobs per sample (a 16 x 16 grid has 16 and 32), so samples are batched
-// until a pass fills the work-group; job addresses come from a table in LDS (one 2-byte read) instead of a chain
-// of divisions per job and sample.  Layouts of many short axes (5x3 / 3x3 / 3x3) spend their time on the barriers
-// and LDS round trips of their six passes: 7776 cells of one sample take about 4 us of a CU, half of it vector issue.
+// What bounds it: latency.  The short lines leave few jobs per sample (a 16 x 16 grid has 16 and 32), so samples are
+// batched until a pass fills the work-group; job addresses come from a table in LDS (one 2-byte read) instead of a
+// chain of divisions per job and sample.  A pass costs about 1000 cycles of waiting (table, line, barrier) besides its
+// instructions, which is why short axes are transformed two by two (n1 n2 values a thread): 5x3 / 3x3 / 3x3, 12
+// channels, T = 333: 635 -> 410 us, 2x2 / 16x16, 16 channels, T = 250: 130 -> 70 us, together with one round of
+// work-groups instead of a fixed count.  Vector units issue 30 to 40% of the cycles; more waves a SIMD alone (eight
+// instead of four) did not change the time, so the planner weighs work-groups per CU only through that waiting.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -24,6 +27,10 @@ namespace omni {
 namespace {
 
 using dn::dft;
+
+// Lambdas are called from several unrolled places: always inlined.  A pass' schedule is handed on by value: captured
+// by reference it would make the compiler copy the kernel's whole argument structure into scratch memory.
+#define OMNI_INLINE __attribute__((always_inline))
 
 // q / d for q < 2^16, magic = ceil(2^32 / d) (exact: the excess q (d - 1) / 2^32 stays below 1 / d); d = 1 has
 // magic 0.
@@ -71,7 +78,7 @@ struct Ctx {
 };
 
 template <int N, bool PAD>
-__device__ __forceinline__ void mid_pass(const LinePass& p, const Ctx& c) {
+__device__ __forceinline__ void mid_pass(const LinePass p, const Ctx& c) {
   const uint32_t jobs = (uint32_t)(c.nb * p.lines);
   for (uint32_t q = c.tid; q < jobs; q += c.nt) {
     const uint32_t b = fast_div(q, p.magic), line = q - b * p.lines;
@@ -80,19 +87,19 @@ __device__ __forceinline__ void mid_pass(const LinePass& p, const Ctx& c) {
 #pragma unroll
     for (int j = 0; j < N; ++j) x[j] = w[j * p.stride];
     if (p.tj < 0) {
-      line_dft<N, PAD>(x, [&](int k, float2 v) { w[k * p.stride] = v; });
+      line_dft<N, PAD>(x, [&](int k, float2 v) OMNI_INLINE { w[k * p.stride] = v; });
     } else {
       const int step = c.tab[p.tj + line];
       if (c.lds_tw)
-        line_dft<N, PAD>(x, [&](int k, float2 v) { w[k * p.stride] = k ? dn::mul(v, c.tw_lds[p.tw + k * step]) : v; });
+        line_dft<N, PAD>(x, [&](int k, float2 v) OMNI_INLINE { w[k * p.stride] = k ? dn::mul(v, c.tw_lds[p.tw + k * step]) : v; });
       else
-        line_dft<N, PAD>(x, [&](int k, float2 v) { w[k * p.stride] = k ? dn::mul(v, c.tw_glob[p.tw + k * step]) : v; });
+        line_dft<N, PAD>(x, [&](int k, float2 v) OMNI_INLINE { w[k * p.stride] = k ? dn::mul(v, c.tw_glob[p.tw + k * step]) : v; });
     }
   }
 }
 
 template <int N, bool PAD>
-__device__ __forceinline__ void last_pass(const LinePass& p, const Ctx& c) {
+__device__ __forceinline__ void last_pass(const LinePass p, const Ctx& c) {
   constexpr int OUT = PAD ? 2 * N : N;
   const uint32_t jobs = (uint32_t)(c.groups * p.lines);
   for (uint32_t q = c.tid; q < jobs; q += c.nt) {
@@ -106,7 +113,7 @@ __device__ __forceinline__ void last_pass(const LinePass& p, const Ctx& c) {
       float2 x[N];
 #pragma unroll
       for (int j = 0; j < N; ++j) x[j] = w[b * c.w_size + j * p.stride];
-      line_dft<N, PAD>(x, [&](int k, float2 v) { acc[k] = fmaf(v.x, v.x, fmaf(v.y, v.y, acc[k])); });
+      line_dft<N, PAD>(x, [&](int k, float2 v) OMNI_INLINE { acc[k] = fmaf(v.x, v.x, fmaf(v.y, v.y, acc[k])); });
     }
     float* pw = c.Pw + g * c.cells + line;
 #pragma unroll
@@ -114,52 +121,156 @@ __device__ __forceinline__ void last_pass(const LinePass& p, const Ctx& c) {
   }
 }
 
-#define OMNI_LINE_TYPES(PASS)      \
-  switch (p.type) {                \
-    case 32 + 1: PASS(1, true);    \
-    case 32 + 2: PASS(2, true);    \
-    case 32 + 3: PASS(3, true);    \
-    case 32 + 4: PASS(4, true);    \
-    case 32 + 5: PASS(5, true);    \
-    case 32 + 6: PASS(6, true);    \
-    case 32 + 7: PASS(7, true);    \
-    case 32 + 8: PASS(8, true);    \
-    case 32 + 10: PASS(10, true);  \
-    case 32 + 11: PASS(11, true);  \
-    case 32 + 12: PASS(12, true);  \
-    case 32 + 13: PASS(13, true);  \
-    case 32 + 16: PASS(16, true);  \
-    case 2: PASS(2, false);        \
-    case 3: PASS(3, false);        \
-    case 4: PASS(4, false);        \
-    case 5: PASS(5, false);        \
-    case 6: PASS(6, false);        \
-    case 7: PASS(7, false);        \
-    case 8: PASS(8, false);        \
-    case 11: PASS(11, false);      \
-    case 13: PASS(13, false);      \
-    case 16: PASS(16, false);      \
-    default: break;                \
+// Two zero-padded axes at once: N1 x N2 values in, 2 N1 x 2 N2 out.  The second axis' even outputs and odd outputs are
+// formed one after the other, each followed by the first axis' lines, so that N1 N2 values are live besides the inputs.
+template <int N1, int N2, int HALF, class Get, class Put>
+__device__ __forceinline__ void block_dft(Get get, Put put) {
+  float2 z[N1 * N2];
+#pragma unroll
+  for (int i = 0; i < N1; ++i) {
+    float2 t[N2];
+#pragma unroll
+    for (int j = 0; j < N2; ++j) t[j] = HALF ? dn::rot<2 * N2>(get(i, j), j) : get(i, j);
+    dft<N2>(t);
+#pragma unroll
+    for (int j = 0; j < N2; ++j) z[i * N2 + j] = t[j];
+  }
+#pragma unroll
+  for (int q = 0; q < N2; ++q) {
+    float2 v[N1];
+#pragma unroll
+    for (int i = 0; i < N1; ++i) v[i] = z[i * N2 + q];
+    line_dft<N1, true>(v, [&](int k1, float2 y) OMNI_INLINE { put(k1, 2 * q + HALF, y); });
+  }
+}
+
+template <int N1, int N2>
+__device__ __forceinline__ void mid_pass2(const LinePass p, const Ctx& c) {
+  const uint32_t jobs = (uint32_t)(c.nb * p.lines);
+  for (uint32_t q = c.tid; q < jobs; q += c.nt) {
+    const uint32_t b = fast_div(q, p.magic), line = q - b * p.lines;
+    float2* w = c.W + b * c.w_size + c.tab[p.tab + line];
+    float2 x[N1 * N2];
+#pragma unroll
+    for (int i = 0; i < N1; ++i)
+#pragma unroll
+      for (int j = 0; j < N2; ++j) x[i * N2 + j] = w[i * p.stride + j * p.stride2];
+    const auto get = [&](int i, int j) OMNI_INLINE { return x[i * N2 + j]; };
+    const auto put = [&](int k1, int k2, float2 y) OMNI_INLINE { w[k1 * p.stride + k2 * p.stride2] = y; };
+    block_dft<N1, N2, 0>(get, put);
+    block_dft<N1, N2, 1>(get, put);
+  }
+}
+
+// Output (k1, k2) of a block is cell (k1 2 N2 + k2) lines + line.  The inputs are read again for the odd outputs:
+// the sums of one half are what the registers hold.
+template <int N1, int N2, int HALF>
+__device__ __forceinline__ void last_half(const LinePass p, const Ctx& c, const float2* w, float* pw, int g) {
+  float acc[N2 * 2 * N1];
+#pragma unroll
+  for (int k = 0; k < N2 * 2 * N1; ++k) acc[k] = 0.f;
+#pragma unroll 1
+  for (int b = g; b < c.nb; b += c.groups) {
+    block_dft<N1, N2, HALF>([&](int i, int j) OMNI_INLINE { return w[b * c.w_size + i * p.stride + j * p.stride2]; },
+                            [&](int k1, int k2, float2 y) OMNI_INLINE {
+                              float& a = acc[(k2 / 2) * 2 * N1 + k1];
+                              a = fmaf(y.x, y.x, fmaf(y.y, y.y, a));
+                            });
+  }
+#pragma unroll
+  for (int q = 0; q < N2; ++q)
+#pragma unroll
+    for (int k = 0; k < 2 * N1; ++k) pw[(k * 2 * N2 + 2 * q + HALF) * p.lines] += acc[q * 2 * N1 + k];
+}
+
+template <int N1, int N2>
+__device__ __forceinline__ void last_pass2(const LinePass p, const Ctx& c) {
+  const uint32_t jobs = (uint32_t)(c.groups * p.lines);
+  for (uint32_t q = c.tid; q < jobs; q += c.nt) {
+    const uint32_t g = fast_div(q, p.magic), line = q - g * p.lines;
+    if ((int)g >= c.nb) continue;
+    const float2* w = c.W + c.tab[p.tab + line];
+    float* pw = c.Pw + g * c.cells + line;
+    last_half<N1, N2, 0>(p, c, w, pw, (int)g);
+    last_half<N1, N2, 1>(p, c, w, pw, (int)g);
+  }
+}
+
+// Every type; the ones that need at most 64 registers (`SMALL` kernel: eight waves a SIMD) first.
+#define OMNI_LINE_TYPES(PASS, PASS2)                     \
+  switch (p.type) {                                      \
+    case 32 + 1: PASS(1, true);                          \
+    case 32 + 2: PASS(2, true);                          \
+    case 32 + 3: PASS(3, true);                          \
+    case 32 + 4: PASS(4, true);                          \
+    case 32 + 5: PASS(5, true);                          \
+    case 32 + 6: PASS(6, true);                          \
+    case 32 + 7: PASS(7, true);                          \
+    case 32 + 8: PASS(8, true);                          \
+    case 2: PASS(2, false);                              \
+    case 3: PASS(3, false);                              \
+    case 4: PASS(4, false);                              \
+    case 5: PASS(5, false);                              \
+    case 6: PASS(6, false);                              \
+    case 7: PASS(7, false);                              \
+    case 8: PASS(8, false);                              \
+    case 256 + 34: PASS2(2, 2);                          \
+    case 256 + 50: PASS2(3, 2);                          \
+    case 256 + 66: PASS2(4, 2);                          \
+    case 256 + 51: PASS2(3, 3);                          \
+    default:                                             \
+      if constexpr (!SMALL) {                            \
+        switch (p.type) {                                \
+          case 32 + 9: PASS(9, true);                    \
+          case 32 + 10: PASS(10, true);                  \
+          case 32 + 11: PASS(11, true);                  \
+          case 32 + 12: PASS(12, true);                  \
+          case 32 + 13: PASS(13, true);                  \
+          case 32 + 16: PASS(16, true);                  \
+          case 11: PASS(11, false);                      \
+          case 13: PASS(13, false);                      \
+          case 16: PASS(16, false);                      \
+          case 256 + 82: PASS2(5, 2);                    \
+          case 256 + 98: PASS2(6, 2);                    \
+          case 256 + 114: PASS2(7, 2);                   \
+          case 256 + 130: PASS2(8, 2);                   \
+          case 256 + 67: PASS2(4, 3);                    \
+          case 256 + 83: PASS2(5, 3);                    \
+          case 256 + 68: PASS2(4, 4);                    \
+          default: break;                                \
+        }                                                \
+      }                                                  \
   }
 
-__device__ __forceinline__ void run_mid(const LinePass& p, const Ctx& c) {
+template <bool SMALL>
+__device__ __forceinline__ void run_mid(const LinePass p, const Ctx& c) {
 #define OMNI_MID(N_, PAD_)  \
   mid_pass<N_, PAD_>(p, c); \
   break
-  OMNI_LINE_TYPES(OMNI_MID)
+#define OMNI_MID2(N1_, N2_)   \
+  mid_pass2<N1_, N2_>(p, c); \
+  break
+  OMNI_LINE_TYPES(OMNI_MID, OMNI_MID2)
 #undef OMNI_MID
+#undef OMNI_MID2
 }
 
-__device__ __forceinline__ void run_last(const LinePass& p, const Ctx& c) {
+template <bool SMALL>
+__device__ __forceinline__ void run_last(const LinePass p, const Ctx& c) {
 #define OMNI_LAST(N_, PAD_)  \
   last_pass<N_, PAD_>(p, c); \
   break
-  OMNI_LINE_TYPES(OMNI_LAST)
+#define OMNI_LAST2(N1_, N2_)   \
+  last_pass2<N1_, N2_>(p, c); \
+  break
+  OMNI_LINE_TYPES(OMNI_LAST, OMNI_LAST2)
 #undef OMNI_LAST
+#undef OMNI_LAST2
 }
 
 // Dynamic LDS: W [batch][w_size] float2, twiddles [n_tw] float2, power [groups][cells] float, table [n_tab] uint16.
-__global__ __launch_bounds__(1024) void lines_fp32_kernel(const void* __restrict__ src, int64_t T, int64_t tps,
+template <bool SMALL>
+__global__ __launch_bounds__(1024, SMALL ? 8 : 4) void lines_fp32_kernel(const void* __restrict__ src, int64_t T, int64_t tps,
                                                           const float2* __restrict__ tw_glob,
                                                           const uint16_t* __restrict__ tab_glob,
                                                           double* __restrict__ partial, LineP P) {
@@ -198,20 +309,18 @@ __global__ __launch_bounds__(1024) void lines_fp32_kernel(const void* __restrict
   for (int i = c.tid; i < P.n_tw; i += c.nt) tw[i] = tw_glob[i];
   for (int i = c.tid; i < P.groups * P.cells; i += c.nt) c.Pw[i] = 0.f;
   double* const out = partial + ((int64_t)grp * P.n_split + s) * P.cells;
-  const LinePass& p0 = P.pass[0];
   bool first = true;
   int held = 0;  // samples in the power array
   for (int64_t t = t0; t < t1; t += P.batch) {
     c.nb = (int)min<int64_t>(P.batch, t1 - t);
     __syncthreads();  // W free, tables and power array ready
     const int64_t tile = (t * P.F + f) * (int64_t)P.N, next = (int64_t)P.F * P.N;
-    int pass = 0;
     if (P.n_split == 1) {
       const uint32_t total = (uint32_t)(c.nb * P.N);
       for (uint32_t e = c.tid; e < total; e += c.nt) {
         const uint32_t b = fast_div(e, P.n_magic), i = e - b * P.N;
         const uint32_t j = fast_div(i, P.load_magic), line = i - j * P.load_lines;
-        c.W[b * P.w_size + tab[p0.tab + line] + j * p0.stride] = sample_at(src, tile + b * next + i, P.fmt);
+        c.W[b * P.w_size + tab[P.load_tab + line] + j * P.load_stride] = sample_at(src, tile + b * next + i, P.fmt);
       }
     } else {
       // stage 1 of axis 0 for the outputs kappa_1 = s + n_split k, k < k_out, by direct sums
@@ -226,26 +335,25 @@ __global__ __launch_bounds__(1024) void lines_fp32_kernel(const void* __restrict
         int e = 0;  // kappa_1 j mod f1
         for (int j = 0; j < P.n1; ++j) {
           const float2 v = sample_at(src, base + (int64_t)j * P.load_lines, P.fmt);
-          const float2 w = c.lds_tw ? tw[p0.tw + e * step0] : tw_glob[p0.tw + e * step0];
+          const float2 w = c.lds_tw ? tw[e * step0] : tw_glob[e * step0];
           z.x = fmaf(v.x, w.x, fmaf(-v.y, w.y, z.x));
           z.y = fmaf(v.x, w.y, fmaf(v.y, w.x, z.y));
           e += kap;
           if (e >= P.f1) e -= P.f1;
         }
-        if (p0.tj >= 0) {
-          const int at = p0.tw + kap * (int)tab[p0.tj + line];
+        if (P.load_tj >= 0) {
+          const int at = kap * (int)tab[P.load_tj + line];
           z = dn::mul(z, c.lds_tw ? tw[at] : tw_glob[at]);
         }
-        c.W[b * P.w_size + tab[p0.tab + line] + (int)k * p0.stride] = z;
+        c.W[b * P.w_size + tab[P.load_tab + line] + (int)k * P.load_stride] = z;
       }
-      pass = 1;
     }
     __syncthreads();
-    for (; pass < P.n_pass - 1; ++pass) {
-      run_mid(P.pass[pass], c);
+    for (int pass = 0; pass < P.n_pass - 1; ++pass) {
+      run_mid<SMALL>(P.pass[pass], c);
       __syncthreads();
     }
-    run_last(P.pass[P.n_pass - 1], c);
+    run_last<SMALL>(P.pass[P.n_pass - 1], c);
     held += c.nb;
     if (held + P.batch > P.time_block || t + P.batch >= t1) {
       __syncthreads();
@@ -268,12 +376,16 @@ __global__ __launch_bounds__(1024) void lines_fp32_kernel(const void* __restrict
 hipError_t launch_lines_fp32(const void* src, int64_t T, int64_t tps, const float2* tw, const uint16_t* tab,
                              double* partial, const LineP& P, int grid, int threads, size_t lds, hipStream_t st) {
   if (P.n_pass < 1 || P.n_pass > kLineMaxPass || threads > 1024) return hipErrorInvalidValue;
-  hipError_t e = hipFuncSetAttribute((const void*)lines_fp32_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(lines_fp32_kernel, dim3((unsigned)grid), dim3((unsigned)threads), lds, st, src, T, tps, tw, tab,
-                     partial, P);
-  return hipGetLastError();
+  bool small = true;
+  for (int i = 0; i < P.n_pass; ++i) small = small && line_type_small(P.pass[i].type);
+  const auto go = [&](auto* kernel) {
+    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3((unsigned)threads), lds, st, src, T, tps, tw, tab, partial,
+                       P);
+    return hipGetLastError();
+  };
+  return small ? go(lines_fp32_kernel<true>) : go(lines_fp32_kernel<false>);
 }
 
 }  // namespace omni

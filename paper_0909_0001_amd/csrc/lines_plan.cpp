@@ -99,73 +99,112 @@ bool axis_stages(int axis, int n, int m, int first, std::vector<Stage>& st) {
 
 uint32_t magic_of(int64_t d) { return d <= 1 ? 0u : (uint32_t)(((uint64_t(1) << 32) + (uint64_t)d - 1) / (uint64_t)d); }
 
-struct Layout {
-  std::vector<int> order;    // stage of each pass
-  std::vector<int> stride, ext;
-  std::vector<int64_t> lines;
-  int64_t w_size = 0, cells = 0, tab = 0;
+// One pass: stage a, or the two one-stage zero-padded axes a and b (b >= 0) together.
+struct Unit {
+  int a, b;
 };
 
-// Passes in the order: stage 0, then the other axes' stages (long transforms first: the later passes see more
-// lines), and last the final stage of one axis, a zero-padded one-stage axis where there is one (the working array
-// then holds its inputs, half of its outputs).
-Layout make_layout(const std::vector<Stage>& st, int split) {
+int unit_type(const std::vector<Stage>& st, const Unit& u) {
+  const Stage& a = st[(size_t)u.a];
+  return u.b >= 0 ? 256 + 16 * a.nin + st[(size_t)u.b].nin : a.nin | (a.padded ? 32 : 0);
+}
+
+struct Layout {
+  std::vector<Unit> order;
+  std::vector<int> stride;
+  std::vector<int64_t> lines;
+  int64_t w_size = 0, cells = 0, tab = 0, load_lines = 0;
+};
+
+// Passes: short zero-padded axes two by two where `pairs` allows, everything else stage by stage, long transforms first
+// (the later passes see more lines), an axis' stages in order; last a pair, else a zero-padded one-stage axis, else the
+// final stage of some axis: the working array holds that pass' inputs, a quarter or half of its outputs.  In the split
+// form stage 0 has been summed before the passes.
+Layout make_layout(const std::vector<Stage>& st, int split, bool pairs) {
   Layout L;
   const int n = (int)st.size();
-  auto final_stage = [&](int i) { return i + 1 == n || st[(size_t)i + 1].axis != st[(size_t)i].axis; };
+  auto alone = [&](int i) {  // the only stage of a zero-padded axis
+    return st[(size_t)i].padded && (i + 1 == n || st[(size_t)i + 1].axis != st[(size_t)i].axis);
+  };
+  std::vector<int> left;  // stages without a unit
+  for (int i = split > 1 ? 1 : 0; i < n; ++i) left.push_back(i);
+  std::vector<Unit> units;
+  if (pairs) {
+    std::vector<int> cand;
+    for (int i : left)
+      if (alone(i)) cand.push_back(i);
+    std::stable_sort(cand.begin(), cand.end(), [&](int a, int b) { return st[(size_t)a].nin > st[(size_t)b].nin; });
+    while (!cand.empty()) {
+      const int a = cand.front();
+      cand.erase(cand.begin());
+      for (size_t k = 0; k < cand.size(); ++k)
+        if (line_pair_ok(st[(size_t)a].nin, st[(size_t)cand[k]].nin)) {
+          units.push_back({a, cand[k]});
+          left.erase(std::find(left.begin(), left.end(), a));
+          left.erase(std::find(left.begin(), left.end(), cand[k]));
+          cand.erase(cand.begin() + (std::ptrdiff_t)k);
+          break;
+        }
+    }
+    if (units.empty()) return L;
+  }
+  for (int i : left) units.push_back({i, -1});
+  auto in_of = [&](const Unit& u) { return st[(size_t)u.a].nin * (u.b >= 0 ? st[(size_t)u.b].nin : 1); };
+  auto out_of = [&](const Unit& u) { return st[(size_t)u.a].nout * (u.b >= 0 ? st[(size_t)u.b].nout : 1); };
   int last = -1;
-  for (int i = n - 1; i >= (split > 1 ? 1 : 0); --i) {
-    if (!final_stage(i) || (n > 1 && i == 0)) continue;
+  for (int k = 0; k < (int)units.size(); ++k) {
+    const Unit& u = units[(size_t)k];
+    if (u.b < 0 && u.a + 1 < n && st[(size_t)u.a + 1].axis == st[(size_t)u.a].axis) continue;  // not a final stage
     if (last < 0) {
-      last = i;
+      last = k;
       continue;
     }
-    const Stage &a = st[(size_t)i], &b = st[(size_t)last];
-    if (a.padded != b.padded ? a.padded : a.nin < b.nin) last = i;
+    const Unit& v = units[(size_t)last];
+    const int gu = out_of(u) / in_of(u), gv = out_of(v) / in_of(v);
+    if (gu != gv ? gu > gv : in_of(u) < in_of(v)) last = k;
   }
   if (last < 0) return L;
-  std::vector<int> mid;
-  for (int i = 1; i < n; ++i)
-    if (i != last) mid.push_back(i);
-  if (last != 0) L.order.push_back(0);
-  // whole axes, by decreasing length of their first stage; the stages of an axis stay in order
-  std::vector<int> axes;
-  for (int i : mid)
-    if (axes.empty() || std::find(axes.begin(), axes.end(), st[(size_t)i].axis) == axes.end()) axes.push_back(st[(size_t)i].axis);
-  std::stable_sort(axes.begin(), axes.end(), [&](int a, int b) {
-    int na = 0, nb = 0;
+  const Unit lu = units[(size_t)last];
+  units.erase(units.begin() + last);
+  std::stable_sort(units.begin(), units.end(), [&](const Unit& u, const Unit& v) {
+    const int au = st[(size_t)u.a].axis, av = st[(size_t)v.a].axis;
+    if (au == av) return u.a < v.a;
+    int mu = out_of(u), mv = out_of(v);  // an axis of several stages sorts as one, by its longest stage
     for (const Stage& s : st) {
-      if (s.axis == a) na = std::max(na, s.nout);
-      if (s.axis == b) nb = std::max(nb, s.nout);
+      if (s.axis == au) mu = std::max(mu, s.nout);
+      if (s.axis == av) mv = std::max(mv, s.nout);
     }
-    return na > nb;
+    return mu != mv ? mu > mv : au < av;
   });
-  for (int a : axes)
-    for (int i : mid)
-      if (st[(size_t)i].axis == a) L.order.push_back(i);
-  L.order.push_back(last);
+  L.order = units;
+  L.order.push_back(lu);
   L.stride.assign((size_t)n, 0);
-  L.ext.assign((size_t)n, 0);
   int64_t s = 1;
   L.cells = 1;
   for (int i = n - 1; i >= 0; --i) {
     const int out = i == 0 ? st[0].nout / split : st[(size_t)i].nout;
-    L.ext[(size_t)i] = i == last ? st[(size_t)i].nin : out;
     L.stride[(size_t)i] = (int)std::min<int64_t>(s, 1 << 28);
-    L.w_size = s * L.ext[(size_t)i];
+    L.w_size = s * (i == lu.a || i == lu.b ? st[(size_t)i].nin : out);
     s = L.w_size | 1;
     L.cells *= out;
     if (L.cells > (int64_t(1) << 26) || s > (int64_t(1) << 26)) return Layout();
   }
   std::vector<int> cur((size_t)n);
-  for (int i = 0; i < n; ++i) cur[(size_t)i] = st[(size_t)i].nin;
-  for (int i : L.order) {
+  L.load_lines = 1;
+  for (int i = 0; i < n; ++i) {
+    cur[(size_t)i] = st[(size_t)i].nin;
+    if (i) L.load_lines *= st[(size_t)i].nin;
+  }
+  L.tab = L.load_lines * (split > 1 && st[0].rem > 1 ? 2 : 1);
+  if (split > 1) cur[0] = st[0].nout / split;
+  for (const Unit& u : L.order) {
     int64_t lines = 1;
     for (int k = 0; k < n; ++k)
-      if (k != i) lines *= cur[(size_t)k];
+      if (k != u.a && k != u.b) lines *= cur[(size_t)k];
     L.lines.push_back(lines);
-    L.tab += lines * (st[(size_t)i].rem > 1 ? 2 : 1);
-    cur[(size_t)i] = i == 0 ? st[0].nout / split : st[(size_t)i].nout;
+    L.tab += lines * (st[(size_t)u.a].rem > 1 ? 2 : 1);
+    for (int k : {u.a, u.b})
+      if (k >= 0) cur[(size_t)k] = k == 0 ? st[0].nout / split : st[(size_t)k].nout;
   }
   return L;
 }
@@ -185,10 +224,13 @@ bool plan_lines(int d, const int* n, const int* m, int max_batch, LineSetup& out
     if (!axis_stages(k, n[k], m[k], 0, tail)) return false;
 
   // Candidates: first stage of axis 0 and its split S (a divisor of the stage's outputs; only a zero-padded
-  // stage, which the split form sums directly, so its length is free), threads, batch.  The cost of one sample of
-  // a channel on a CU is the larger of its vector issue and its latency chain over the work-groups that fit a CU.
+  // stage, which the split form sums directly, so its length is free), pairs of axes or not, threads, batch, copies of
+  // the power array.  The cost of one sample of a channel, in cycles of a CU: 1.12 a vector instruction of any wave,
+  // plus 3.7 an instruction of the longest wave and 990 a pass (its barrier and LDS latency), shared by the
+  // work-groups that fit a CU.  Fitted to 88 schedules of seven grids (measured 940 to 98000 cycles; 12% rms);
+  // the last term of the last pass: one wave's LDS latency for each further sample.
   double best = 1e300;
-  int bS = 0, bB = 0, bNT = 0, bG = 0;
+  int bS = 0, bB = 0, bNT = 0, bG = 0, bfit = 1;
   bool bTw = false;
   Layout bL;
   std::vector<Stage> bst, st;
@@ -206,55 +248,70 @@ bool plan_lines(int d, const int* n, const int* m, int max_batch, LineSetup& out
     bool twiddled = false;
     for (const Stage& s : st) twiddled = twiddled || s.rem > 1;
     const Stage s0 = st[0];
-    const Layout L = make_layout(st, S);
+    for (const bool pairs : {false, true}) {
+    const Layout L = make_layout(st, S, pairs);
     if (L.order.empty()) continue;
+    bool small = true;  // eight waves a SIMD instead of four
+    for (const Unit& u : L.order) small = small && line_type_small(unit_type(st, u));
     const int64_t n_tw = (twiddled || S > 1) && tw_all <= 1024 ? tw_all : 0;
     const int64_t load_lines = N / s0.nin, k_out = s0.nout / S;
     for (int NT = 256; NT <= 1024; NT *= 2) {
       for (int B = 1; B <= std::min(kMaxBatch, std::max(1, max_batch)); B *= 2) {
-        const int G = (int)std::max<int64_t>(1, std::min<int64_t>(B, NT / L.lines.back()));
+        const int Gmax = (int)std::max<int64_t>(1, std::min<int64_t>(B, NT / L.lines.back()));
+        for (int G = Gmax; G >= 1; G = G > 1 ? G / 2 : 0) {
         const size_t lds = (size_t)(B * L.w_size * 8 + n_tw * 8 + G * L.cells * 4 + L.tab * 2);
         if (lds > kLds) continue;
         if (B * N >= 65536 && S == 1) continue;
         if (S > 1 && B * load_lines * k_out >= 65536) continue;
         bool ok = L.w_size < 65536;
-        double issue = 0, chain = 0;
+        double issue = 0, chain = 0;  // vector instructions of the work-group's waves; of its longest wave, with waits
         auto add = [&](int64_t jobs, double instr) {
           ok = ok && jobs < 65536;
           issue += std::ceil(jobs / 64.0) * instr;
-          chain += std::ceil((double)jobs / NT) * instr * 5.0 + 400.0;
+          chain += std::ceil((double)jobs / NT) * instr * 3.7 + 990.0;
         };
         if (S == 1)
           add(B * N, 12.0);
         else
-          add(B * load_lines * k_out, 20.0 + 12.0 * s0.nin);
-        for (size_t p = S > 1 ? 1 : 0; p < L.order.size(); ++p) {
-          const Stage& s = st[(size_t)L.order[p]];
-          const bool lastp = p + 1 == L.order.size();
-          const double instr = line_cost(s.nout) + (s.rem > 1 ? 8.0 * s.nout : 0.0);
-          if (lastp) {
+          add(B * load_lines * k_out, 40.0 + 24.0 * s0.nin);  // direct sums with a load from HBM for every input
+        for (size_t p = 0; p < L.order.size(); ++p) {
+          const Unit& u = L.order[p];
+          const Stage& a = st[(size_t)u.a];
+          int nout = a.nout;
+          double instr = line_cost(a.nout) + (a.rem > 1 ? 8.0 * a.nout : 0.0);
+          if (u.b >= 0) {
+            const Stage& b = st[(size_t)u.b];
+            nout *= b.nout;
+            instr = 20.0 + a.nin * (line_cost(b.nout) - 20.0) + b.nout * (line_cost(a.nout) - 20.0);
+          }
+          if (p + 1 == L.order.size()) {
             ok = ok && G * L.lines[p] < 65536;
             const double each = std::ceil((double)B / G);
-            issue += std::ceil(G * L.lines[p] / 64.0) * (instr * each + 4.0 * s.nout);
-            chain += std::ceil((double)G * L.lines[p] / NT) * (instr * each + 4.0 * s.nout) * 5.0 + 400.0;
+            issue += std::ceil(G * L.lines[p] / 64.0) * (instr * each + 4.0 * nout);
+            chain += std::ceil((double)G * L.lines[p] / NT) *
+                         ((instr * each + 4.0 * nout) * 3.7 + (each - 1.0) * (u.b >= 0 ? 500.0 : 250.0)) +
+                     990.0;
           } else {
             add(B * L.lines[p], instr);
           }
         }
         if (!ok) continue;
-        const double fit = std::max(1.0, std::min(std::floor((double)kLds / (double)lds), 1024.0 / NT));
-        const double cost = S * std::max(issue / B, chain / (fit * B));
+        const double fit = std::max(1.0, std::min(std::floor((double)kLds / (double)lds), (small ? 2048.0 : 1024.0) / NT));
+        const double cost = (double)S / B * (1.12 * issue + chain / fit);
         if (cost < best * 0.98) {
           best = cost;
           bS = S;
           bB = B;
           bNT = NT;
           bG = G;
+          bfit = (int)fit;
           bL = L;
           bst = st;
           bTw = twiddled || S > 1;
         }
+        }
       }
+    }
     }
   }
   if (!bS) return false;
@@ -271,8 +328,10 @@ bool plan_lines(int d, const int* n, const int* m, int max_batch, LineSetup& out
   P.cells = (int32_t)bL.cells;
   P.n_split = bS;
   P.n_tw = bTw && tw_all <= 1024 ? tw_all : 0;
-  P.load_lines = (int32_t)(N / s0.nin);
+  P.load_lines = (int32_t)bL.load_lines;
   P.load_magic = magic_of(P.load_lines);
+  P.load_stride = bL.stride[0];
+  P.load_tj = -1;
   P.n_magic = magic_of(N);
   P.f1 = s0.nout;
   P.n1 = s0.nin;
@@ -285,41 +344,57 @@ bool plan_lines(int d, const int* n, const int* m, int max_batch, LineSetup& out
   out.order.clear();
   std::vector<int> cur((size_t)ns);
   for (int i = 0; i < ns; ++i) cur[(size_t)i] = st[(size_t)i].nin;
-  for (size_t p = 0; p < bL.order.size(); ++p) {
-    const int i = bL.order[p];
-    const Stage& s = st[(size_t)i];
-    LinePass& q = P.pass[p];
-    q.type = s.nin | (s.padded ? 32 : 0);
-    q.stride = bL.stride[(size_t)i];
-    q.lines = (int32_t)bL.lines[p];
-    q.magic = magic_of(q.lines);
-    q.tab = (int32_t)out.tab.size();
-    q.tw = tw_off[(size_t)s.axis];
-    q.tj = -1;
+  // the offsets of the lines along the stages a and b (b = -1: a alone), at the extents `cur`, and their twiddle steps
+  // where `twiddle`; returns the first entry of each (-1: no steps)
+  auto put_lines = [&](int a, int b, int64_t lines, bool twiddle) {
+    const int at = (int)out.tab.size();
     std::vector<uint16_t> steps;
-    for (int64_t line = 0; line < bL.lines[p]; ++line) {
+    for (int64_t line = 0; line < lines; ++line) {
       int64_t r = line, off = 0, j = 0;
       for (int k = ns - 1; k >= 0; --k) {
-        if (k == i) continue;
+        if (k == a || k == b) continue;
         const int64_t digit = r % cur[(size_t)k];
         r /= cur[(size_t)k];
         off += digit * bL.stride[(size_t)k];
-        if (st[(size_t)k].axis == s.axis && k > i) j += digit * st[(size_t)k].rem;
+        if (st[(size_t)k].axis == st[(size_t)a].axis && k > a) j += digit * st[(size_t)k].rem;
       }
       out.tab.push_back((uint16_t)off);
-      steps.push_back((uint16_t)(j * s.done));
+      steps.push_back((uint16_t)(j * st[(size_t)a].done));
     }
-    if (s.rem > 1) {
-      q.tj = (int32_t)out.tab.size();
+    int tj = -1;
+    if (twiddle) {
+      tj = (int)out.tab.size();
       out.tab.insert(out.tab.end(), steps.begin(), steps.end());
     }
-    cur[(size_t)i] = i == 0 ? st[0].nout / bS : s.nout;
-    out.order.push_back(s.axis);
+    return std::pair<int, int>(at, tj);
+  };
+  const auto load = put_lines(0, -1, bL.load_lines, bS > 1 && s0.rem > 1);
+  P.load_tab = load.first;
+  P.load_tj = load.second;
+  if (bS > 1) cur[0] = P.k_out;
+  for (size_t p = 0; p < bL.order.size(); ++p) {
+    const Unit& u = bL.order[p];
+    const Stage& s = st[(size_t)u.a];
+    LinePass& q = P.pass[p];
+    q.type = unit_type(st, u);
+    q.stride = bL.stride[(size_t)u.a];
+    if (u.b >= 0) q.stride2 = bL.stride[(size_t)u.b];
+    q.lines = (int32_t)bL.lines[p];
+    q.magic = magic_of(q.lines);
+    q.tw = tw_off[(size_t)s.axis];
+    const auto t = put_lines(u.a, u.b, bL.lines[p], s.rem > 1);
+    q.tab = t.first;
+    q.tj = t.second;
+    for (int k : {u.a, u.b})
+      if (k >= 0) {
+        cur[(size_t)k] = k == 0 ? P.k_out : st[(size_t)k].nout;
+        out.order.push_back(st[(size_t)k].axis);
+      }
   }
   P.n_tab = (int32_t)out.tab.size();
 
   // cell (split residue c, output q of the last pass, line) -> natural frequency index
-  const int last = bL.order.back();
+  const Unit lu = bL.order.back();
   std::vector<int64_t> nat((size_t)d, 1);
   for (int k = d - 2; k >= 0; --k) nat[(size_t)k] = nat[(size_t)k + 1] * m[k + 1];
   out.kmap.assign((size_t)(bS * bL.cells), 0);
@@ -327,20 +402,27 @@ bool plan_lines(int d, const int* n, const int* m, int max_batch, LineSetup& out
   for (int c = 0; c < bS; ++c)
     for (int64_t cell = 0; cell < bL.cells; ++cell) {
       int64_t r = cell % lines, at = 0;
+      const int64_t o = cell / lines;
       auto put = [&](int k, int64_t digit) {
         const Stage& s = st[(size_t)k];
         if (k == 0) digit = c + digit * bS;
         at += digit * s.done * nat[(size_t)s.axis];
       };
-      put(last, cell / lines);
+      if (lu.b >= 0) {
+        put(lu.a, o / st[(size_t)lu.b].nout);
+        put(lu.b, o % st[(size_t)lu.b].nout);
+      } else {
+        put(lu.a, o);
+      }
       for (int k = ns - 1; k >= 0; --k) {
-        if (k == last) continue;
+        if (k == lu.a || k == lu.b) continue;
         put(k, r % cur[(size_t)k]);
         r /= cur[(size_t)k];
       }
       out.kmap[(size_t)(c * bL.cells + cell)] = (int32_t)at;
     }
   out.threads = bNT;
+  out.per_cu = bfit;
   out.lds = (size_t)(bB * bL.w_size * 8 + (int64_t)P.n_tw * 8 + bG * bL.cells * 4 + (int64_t)P.n_tab * 2);
   return true;
 }

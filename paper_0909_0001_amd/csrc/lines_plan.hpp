@@ -15,6 +15,7 @@ struct LineSetup {
   std::vector<int32_t> kmap;  // [n_split][cells] -> natural frequency index
   std::vector<int> order;     // axis of each pass
   int threads = 0;
+  int per_cu = 1;             // work-groups that fit a CU
   size_t lds = 0;
 };
 

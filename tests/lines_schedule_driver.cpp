@@ -90,7 +90,7 @@ static int check(const std::string& name, const std::vector<int>& n, const std::
     }
     for (const cd& v : cur) ref[(size_t)b].push_back(std::norm(v));
   }
-  const LinePass& p0 = P.pass[0];
+  CHECK(P.load_tab + P.load_lines <= P.n_tab && P.load_tj + P.load_lines <= P.n_tab);
   for (int c = 0; c < P.n_split; ++c) {
     std::vector<cd> W((size_t)(P.batch * P.w_size), cd(NAN, NAN));
     std::vector<double> pw((size_t)(P.batch * P.cells), 0.0);
@@ -98,7 +98,7 @@ static int check(const std::string& name, const std::vector<int>& n, const std::
       if (P.n_split == 1) {
         for (int64_t i = 0; i < N; ++i) {
           const int64_t j = i / P.load_lines, line = i % P.load_lines;
-          const int64_t at = s.tab[(size_t)(p0.tab + line)] + j * p0.stride;
+          const int64_t at = s.tab[(size_t)(P.load_tab + line)] + j * P.load_stride;
           CHECK(at < P.w_size);
           W[(size_t)(b * P.w_size + at)] = x[(size_t)b][(size_t)i];
         }
@@ -111,21 +111,23 @@ static int check(const std::string& name, const std::vector<int>& n, const std::
               CHECK(j * P.load_lines + line < N);
               z += x[(size_t)b][(size_t)(j * P.load_lines + line)] * w((long long)kap * j, P.f1);
             }
-            if (p0.tj >= 0) {
-              const int e = kap * s.tab[(size_t)(p0.tj + line)];
+            if (P.load_tj >= 0) {
+              const int e = kap * s.tab[(size_t)(P.load_tj + line)];
               CHECK(e < m[0]);
-              z *= tw[(size_t)(p0.tw + e)];
+              z *= tw[(size_t)e];
             }
-            const int64_t at = s.tab[(size_t)(p0.tab + line)] + (int64_t)k * p0.stride;
+            const int64_t at = s.tab[(size_t)(P.load_tab + line)] + (int64_t)k * P.load_stride;
             CHECK(at < P.w_size);
             W[(size_t)(b * P.w_size + at)] = z;
           }
       }
     }
-    for (int pi = P.n_split == 1 ? 0 : 1; pi < P.n_pass; ++pi) {
+    for (int pi = 0; pi < P.n_pass; ++pi) {
       const LinePass& p = P.pass[pi];
-      const int nin = p.type & 31, nout = (p.type & 32) ? 2 * nin : nin;
-      const bool last = pi + 1 == P.n_pass;
+      const bool two = (p.type & 256) != 0, last = pi + 1 == P.n_pass;
+      const int n1 = two ? (p.type - 256) / 16 : p.type & 31, n2 = two ? p.type & 15 : 1;
+      const int o1 = two || (p.type & 32) ? 2 * n1 : n1, o2 = two ? 2 * n2 : 1;
+      CHECK(!two || (omni::line_pair_ok(n1, n2) && p.tj < 0));
       CHECK((int64_t)P.batch * p.lines < 65536 && p.tab + p.lines <= P.n_tab);
       for (uint32_t q = 0; q < (uint32_t)(P.batch * p.lines); ++q) CHECK(fast_div(q, p.magic) == q / p.lines);
       std::vector<char> owner(W.size(), 0);
@@ -133,36 +135,43 @@ static int check(const std::string& name, const std::vector<int>& n, const std::
         for (int line = 0; line < p.lines; ++line) {
           const int64_t base = (int64_t)b * P.w_size + s.tab[(size_t)(p.tab + line)];
           std::vector<cd> in, outv;
-          for (int j = 0; j < nin; ++j) {
-            const int64_t at = base + (int64_t)j * p.stride;
-            CHECK(at < (int64_t)(b + 1) * P.w_size);
-            CHECK(!owner[(size_t)at]);  // not yet written by another line of this pass
-            CHECK(!std::isnan(W[(size_t)at].real()));
-            in.push_back(W[(size_t)at]);
-          }
-          for (int k = 0; k < nout; ++k) {
-            cd z = 0;
-            for (int j = 0; j < nin; ++j) z += in[(size_t)j] * w((long long)j * k, nout);
-            if (!last && p.tj >= 0) {
-              const int e = k * s.tab[(size_t)(p.tj + line)];
-              CHECK(p.tw + e < (int)tw.size());
-              z *= tw[(size_t)(p.tw + e)];
-            }
-            outv.push_back(z);
-          }
-          CHECK(!last || p.tj < 0);
-          for (int k = 0; k < nout; ++k) {
-            if (last) {
-              CHECK((int64_t)k * p.lines + line < P.cells);
-              pw[(size_t)((int64_t)b * P.cells + (int64_t)k * p.lines + line)] += std::norm(outv[(size_t)k]);
-            } else {
-              const int64_t at = base + (int64_t)k * p.stride;
+          for (int i = 0; i < n1; ++i)
+            for (int j = 0; j < n2; ++j) {
+              const int64_t at = base + (int64_t)i * p.stride + (int64_t)j * p.stride2;
               CHECK(at < (int64_t)(b + 1) * P.w_size);
-              CHECK(!owner[(size_t)at]);
-              owner[(size_t)at] = 1;
-              W[(size_t)at] = outv[(size_t)k];
+              CHECK(!owner[(size_t)at]);  // not yet written by another line of this pass
+              CHECK(!std::isnan(W[(size_t)at].real()));
+              in.push_back(W[(size_t)at]);
             }
-          }
+          for (int k = 0; k < o1; ++k)
+            for (int k2 = 0; k2 < o2; ++k2) {
+              cd z = 0;
+              for (int i = 0; i < n1; ++i)
+                for (int j = 0; j < n2; ++j)
+                  z += in[(size_t)(i * n2 + j)] * w((long long)i * k, o1) * w((long long)j * k2, o2);
+              if (!last && p.tj >= 0) {
+                const int e = k * s.tab[(size_t)(p.tj + line)];
+                CHECK(p.tw + e < (int)tw.size());
+                z *= tw[(size_t)(p.tw + e)];
+              }
+              outv.push_back(z);
+            }
+          CHECK(!last || p.tj < 0);
+          for (int k = 0; k < o1; ++k)
+            for (int k2 = 0; k2 < o2; ++k2) {
+              const cd z = outv[(size_t)(k * o2 + k2)];
+              if (last) {
+                const int64_t cell = (int64_t)(k * o2 + k2) * p.lines + line;
+                CHECK(cell < P.cells);
+                pw[(size_t)((int64_t)b * P.cells + cell)] += std::norm(z);
+              } else {
+                const int64_t at = base + (int64_t)k * p.stride + (int64_t)k2 * p.stride2;
+                CHECK(at < (int64_t)(b + 1) * P.w_size);
+                CHECK(!owner[(size_t)at]);
+                owner[(size_t)at] = 1;
+                W[(size_t)at] = z;
+              }
+            }
         }
     }
     for (int b = 0; b < P.batch; ++b)

@@ -24,10 +24,12 @@ def smooth(v):
 GRIDS = [f"{n}" for n in range(1, 65) if smooth(n)] + ["128", "240", "512"]
 GRIDS += [f"{n} {k}" for n, k in [(2, 3), (3, 5), (16, 16), (6, 10), (8, 8), (9, 15), (20, 24), (7, 13), (32, 16), (40, 39)]]
 GRIDS += ["64 48", "96 32", "128 24", "26 64", "19 4", "34 2"]  # split along axis 0
-GRIDS += ["5 3 3 3 3 3", "2 2 16 16", "3 3 3 3 5 3", "4 4 4 4", "4 4 4 4 4", "8 8 4 4", "6 5 4 3 2", "2 2 2 2 2 2", "12 3 12"]
+GRIDS += ["5 3 3 3 3 3", "2 2 16 16", "3 3 3 3 5 3", "4 4 4 4", "4 4 4 4 4", "8 8 4 4", "6 5 4 3 2", "2 2 2 2 2 2", "2 2 2 2 2 2 2 2", "12 3 12"]
+# short axes two by two: every pair of lengths that is one pass, alone and behind another axis
+GRIDS += [f"{a} {b}" for a in range(2, 9) for b in range(2, a + 1) if a * b <= 16] + ["2 8 2 8", "3 4 7 2", "5 3 16", "11 3 3"]
 GRIDS += ["4 4 8 8 b2", "2 3 3 3 4 4 b2", "3 3 5 5 b2", "4 8 b1", "6 5 9 10 b2", "4 4 16 12 b2", "7 7 b1"]
 # prime factors without a register transform; a grid that axis 0 cannot divide far enough
-NOT_PLANNED = ["17", "4 19", "3 34", "5 5 23 b1", "2 2 2 2 2 2 2 2"]
+NOT_PLANNED = ["17", "4 19", "3 34", "5 5 23 b1", "2 2 16 16 16"]
 
 
 def test_line_schedules_against_plain_dfts(tmp_path):
