@@ -82,8 +82,8 @@ typedef enum { OMNI_FORM_FP32 = 0, OMNI_FORM_MIXED = 1 } omni_form;
 /* omni_opts.flags */
 #define OMNI_PLAN_HOST_ONLY 0x1u /* geometry only: no device resources; correlate -> OMNI_E_STATE */
 #define OMNI_PLAN_TIMING 0x2u    /* record HIP events around each stage of every correlate call  */
-#define OMNI_PLAN_GRAPH 0x8u     /* run every correlate call as one HIP graph whose arrays are     \
-                                    parallel branches (first call captured, later calls replay)  */
+#define OMNI_PLAN_GRAPH 0x8u     /* run every correlate call as one HIP graph with a branch per    \
+                                    array (first call captured, later calls replay)              */
 /* Beam-space ("digital pointing") variant of Appendix A, steps 4-5: the lowest
  * level (the last level, axes d-2 and d-1) consists of fully sampled n_x x n_y
  * blocks; every block is Fourier transformed over those two axes without zero
@@ -195,9 +195,10 @@ int omni_correlate(omni_plan_t plan, const void* volt, int64_t T, void* vis, voi
  * n_arrays device pointers, read during the call only.
  * Without OMNI_PLAN_GRAPH the arrays run one after another on `stream`.  With
  * it, the plan captures its first call (all arrays, all stages) into one HIP
- * graph in which each array is an independent branch on a stream of its own,
- * so that the arrays' kernels overlap and fill each other's tails; the graph
- * is launched on `stream` and every later call replays it.  Later calls must
+ * graph in which each array is a branch on a stream of its own; the forward
+ * stages follow one another (each fills the GPU by itself), the largest array
+ * first, and an array's reduction and inverse overlap the next one's forward
+ * stage; the graph is launched on `stream` and every later call replays it.  Later calls must
  * repeat the first call's T, flags and volt / vis pointers (the buffers'
  * contents may change): any other call returns OMNI_E_STATE (make another
  * plan for another call shape).  Results are identical to the sequential

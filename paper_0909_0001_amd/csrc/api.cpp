@@ -158,6 +158,7 @@ struct ArrayPlan {
   int ct_index = -1;         // entry of the compile-time shape table (kernel 3)
   int lcap = 32;             // longest short DFT the general kernel may use (autotuned)
   int wg_target = 1024;      // work-groups the time slicing aims for (general and sliced kernels; autotuned)
+  int wg_most = 0, wg_samples = 0;  // sliced kernels: larger target while a slice keeps wg_samples samples (0: none)
   int tb = 0;                // float32 block of the sliced kernels (0: the plan's time_block; autotuned)
   double tuned_ms = 0.0;     // best candidate's time in the autotuner (0: not tuned)
   // front mode: the first n_front axes are transformed by front passes over HBM
@@ -222,6 +223,7 @@ struct omni_plan_s {
   bool graph = false;
   std::vector<hipStream_t> branch;
   std::vector<hipEvent_t> join;
+  std::vector<hipEvent_t> fwd;  // an array's forward stage has been enqueued up to here
   hipStream_t capture = nullptr;
   hipEvent_t fork = nullptr;
   hipEvent_t g_done = nullptr;  // recorded after every launch of the graph
@@ -250,19 +252,25 @@ bool is_pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
 // float32), 2 (8x8x8x8 mixed) and 6-8 (single-level 128 x 128, 64 x 64, 32 x 32 mixed).
 bool sliced_kernel(int k) { return k == 1 || k == 2 || (k >= 6 && k <= 8); }
 
-// Default work-group target of the time slicing, per kernel: 8x8x8x8 float32: three 48 KiB work-groups a CU,
-// two rounds over 256 CUs; 8x8x8x8 mixed: one 112 KiB work-group a CU, one round; 128 x 128: one 128 KiB
-// work-group a CU, about four rounds; 64 x 64: one 96 KiB work-group a CU, four rounds; 32 x 32: 256 threads
-// and 12 KiB, about five work-groups a CU, two rounds.
-int default_wg_target(int k) {
+// Default work-group target of the time slicing, per kernel, and a larger one for long calls: slices beyond the first
+// target are taken while each keeps `samples` samples (every slice costs a set of float64 partial sums, written and
+// read once).  8x8x8x8 float32: three 48 KiB work-groups a CU; two rounds are the least, eight run 7% faster because
+// the work-groups of a CU drift apart and fill each other's waits (F = 64, T = 4096: 9.27 -> 8.71 ms a call; 32
+// channels of 1000 float samples lose below 64 samples a slice).  8x8x8x8 mixed: one 112 KiB work-group a CU, one
+// round.  128 x 128 and 64 x 64: one work-group a CU, two rounds (four rounds: 1.68 -> 1.62 and 0.46 -> 0.41 ms at
+// F = 64, T = 512; 64 x 64 at T = 2048 1.26 -> 1.24).  32 x 32: 256 threads and 12 KiB, five work-groups a CU, one
+// round, two while slices keep 24 samples (T = 512: 157 -> 153 us; T = 2048: 390 us, 400 with one).
+struct WgTarget {
+  int least, most, samples;
+};
+WgTarget default_wg_target(int k) {
   switch (k) {
-    case 1: return 1536;
-    case 2: return 256;
-    case 8: return 2560;
-    default: return 1024;
+    case 1: return {1536, 6144, 64};
+    case 2: return {256, 256, 0};
+    case 8: return {1280, 2560, 24};
+    default: return {512, 512, 0};
   }
 }
-
 
 int64_t prod(const std::vector<int>& v) {
   int64_t p = 1;
@@ -770,7 +778,12 @@ int build_array_core(ArrayPlan& ap, int levels, const int32_t* dims, const doubl
   if (form == OMNI_FORM_MIXED && dtype == OMNI_CI4 && ap.n_front == 0 && ap.n == std::vector<int>{32, 32})
     plan_grid_small(ap, 8);
   if (ap.kernel == 0) plan_general(ap);
-  if (sliced_kernel(ap.kernel)) ap.wg_target = default_wg_target(ap.kernel);
+  if (sliced_kernel(ap.kernel)) {
+    const WgTarget t = default_wg_target(ap.kernel);
+    ap.wg_target = t.least;
+    ap.wg_most = t.most;
+    ap.wg_samples = t.samples;
+  }
   const size_t per_slice = (size_t)ap.F * (size_t)ap.M * sizeof(double);
   ap.max_slices = (int)std::max<size_t>(1, std::min<size_t>(1024, kPartialBudget / per_slice));
   // inverse in groups of channels whose complex float32 workspace fits 1 GiB per buffer
@@ -1046,6 +1059,8 @@ int launch_sliced(omni_plan_s* p, ArrayPlan& ap, const void* volt, int64_t T, in
                   hipStream_t st, int* slices) {
   const int64_t per_slice_groups = (int64_t)ap.F * (ap.kernel == 1 ? 8 : (ap.kernel == 2 || ap.kernel == 6) ? 2 : 1);
   int64_t ns = std::max<int64_t>(1, (target + per_slice_groups / 2) / per_slice_groups);
+  if (target == ap.wg_target && ap.wg_most > target)
+    ns = std::max<int64_t>(ns, std::min<int64_t>(ap.wg_most / per_slice_groups, T / ap.wg_samples));
   ns = std::min<int64_t>(ns, ap.max_slices);
   ns = std::min<int64_t>(ns, std::max<int64_t>(1, T / 8));
   const int64_t tps = (T + ns - 1) / ns;
@@ -1260,6 +1275,7 @@ int tune_sliced(omni_plan_s* p, ArrayPlan& ap) {
   if (p->tune == OMNI_TUNE_CACHE && tune_cache_lookup(p->tune_cache, key, &c_tb, &c_wg) && c_tb > 0 && c_wg > 0) {
     ap.tb = c_tb;
     ap.wg_target = c_wg;
+    ap.wg_most = 0;  // the stored target as it is
     log_msg(2, "autotuner: %s -> block %d, work-group target %d (from the cache)", key.c_str(), c_tb, c_wg);
     return OMNI_OK;
   }
@@ -1272,6 +1288,7 @@ int tune_sliced(omni_plan_s* p, ArrayPlan& ap) {
     tbs = {p->time_block};
   std::vector<int> wgs = {256, 512, 1024, 2048, 4096};
   if (std::find(wgs.begin(), wgs.end(), ap.wg_target) == wgs.end()) wgs.push_back(ap.wg_target);
+  ap.wg_most = 0;  // the search tries targets as they are
   void* zero = nullptr;
   HIP_TRY(hipMalloc(&zero, bytes_t * (size_t)Tt));
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1395,12 +1412,14 @@ int make_graph_resources(omni_plan_s* p) {
   p->graph = true;
   p->branch.assign(p->arrays.size(), nullptr);
   p->join.assign(p->arrays.size(), nullptr);
+  p->fwd.assign(p->arrays.size(), nullptr);
   HIP_TRY(hipStreamCreateWithFlags(&p->capture, hipStreamNonBlocking));
   HIP_TRY(hipEventCreateWithFlags(&p->fork, hipEventDisableTiming));
   HIP_TRY(hipEventCreateWithFlags(&p->g_done, hipEventDisableTiming));
   for (size_t i = 0; i < p->arrays.size(); ++i) {
     HIP_TRY(hipStreamCreateWithFlags(&p->branch[i], hipStreamNonBlocking));
     HIP_TRY(hipEventCreateWithFlags(&p->join[i], hipEventDisableTiming));
+    HIP_TRY(hipEventCreateWithFlags(&p->fwd[i], hipEventDisableTiming));
   }
   return OMNI_OK;
 }
@@ -1427,6 +1446,9 @@ void destroy_plan_resources(omni_plan_s* p) {
   p->kev.clear();
   for (auto& e : p->join)
     if (e) hipEventDestroy(e);
+  for (auto& e : p->fwd)
+    if (e) hipEventDestroy(e);
+  p->fwd.clear();
   for (auto& s : p->branch)
     if (s) hipStreamDestroy(s);
   p->join.clear();
@@ -1440,18 +1462,29 @@ void destroy_plan_resources(omni_plan_s* p) {
   for (auto& ap : p->arrays) free_array(ap);
 }
 
-// Capture one correlate call of a graph plan: the fork event on the capture
-// stream, each array's three stages on its branch stream, the joins back.
+// Capture one correlate call of a graph plan: the fork event on the capture stream, each array's three stages on its
+// branch stream, the joins back.  The forward stages follow one another, the largest array first: each fills the GPU
+// by itself (one work-group a CU for the larger matrix-core kernels), and two of them at once take turns on the CUs
+// and leave uneven ends (32 x 32, 64 x 64 and 128 x 128, 64 channels, T = 2048: 8.93 ms with free branches,
+// 7.19 ms in order).  An array's reduction and inverse overlap the next one's forward stage.
 int capture_call(omni_plan_s* p, const void* const* volt, int64_t T, void* const* vis, uint32_t flags) {
   drop_graph(p);
+  std::vector<size_t> order(p->arrays.size());
+  for (size_t i = 0; i < order.size(); ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) {
+    return (int64_t)p->arrays[a].F * p->arrays[a].M > (int64_t)p->arrays[b].F * p->arrays[b].M;
+  });
   HIP_TRY(hipStreamBeginCapture(p->capture, hipStreamCaptureModeThreadLocal));
   int rc = OMNI_OK;
   hipError_t e = hipEventRecord(p->fork, p->capture);
-  for (size_t i = 0; i < p->arrays.size() && rc == OMNI_OK && e == hipSuccess; ++i) {
-    e = hipStreamWaitEvent(p->branch[i], p->fork, 0);
-    for (int stage = 0; stage < 3 && rc == OMNI_OK && e == hipSuccess; ++stage)
+  for (size_t k = 0; k < order.size() && rc == OMNI_OK && e == hipSuccess; ++k) {
+    const size_t i = order[k];
+    e = hipStreamWaitEvent(p->branch[i], k == 0 ? p->fork : p->fwd[order[k - 1]], 0);
+    for (int stage = 0; stage < 3 && rc == OMNI_OK && e == hipSuccess; ++stage) {
       rc = correlate_array(p, p->arrays[i], T > 0 ? volt[i] : nullptr, T,
                            (flags & OMNI_NO_FINALIZE) ? nullptr : vis[i], p->branch[i], flags, stage);
+      if (stage == 0 && rc == OMNI_OK) e = hipEventRecord(p->fwd[i], p->branch[i]);
+    }
     if (rc == OMNI_OK && e == hipSuccess) e = hipEventRecord(p->join[i], p->branch[i]);
     if (rc == OMNI_OK && e == hipSuccess) e = hipStreamWaitEvent(p->capture, p->join[i], 0);
   }
