@@ -33,8 +33,8 @@ hipError_t launch_fill_f64(double* p, int64_t n, double v, hipStream_t st);
 hipError_t launch_inverse_axis(bool real_in, bool last, const void* src, void* dst, const double2* twi,
                                int64_t outer, int m, int n, int64_t inner, double scale, hipStream_t st);
 hipError_t launch_inverse_group(int src_kind, const void* src, void* dst, const double2* twi, const uint16_t* tab,
-                                int64_t outer, int64_t inner, double scale, const InvP& P, size_t lds,
-                                hipStream_t st);
+                                int64_t outer, int64_t inner, double scale, const InvP& P, size_t lds, hipStream_t st,
+                                const uint16_t* pair_tab = nullptr, int n_tiles = 0);
 hipError_t launch_twiddles(const int32_t* desc_dev, int n_tables, float2* tw32, double2* tw64, hipStream_t st);
 hipError_t launch_fused8x4_fp32(int fmt, const void* src, int64_t T, int64_t tps, const float2* tw16, double* partial,
                                 int F, int n_slices, int time_block, hipStream_t st);
@@ -73,6 +73,9 @@ hipError_t launch_xengine(const float2* Y, int64_t Tc, int F, int P, int64_t Mp,
 bool xengine_fused_ok(int P, int ny);
 hipError_t launch_xengine_fused(const float2* Y1, int64_t Tc, int F, int P, int mx, int ny, const float2* twy,
                                 double2* S, int accumulate, hipStream_t st);
+bool xengine_mfma_ok(int P, int nx, int ny);
+hipError_t launch_xengine_mfma(const float2* Y1, int64_t Tc, int F, int P, int mx, int ny, float scale, double2* S,
+                               int accumulate, hipStream_t st);
 hipError_t launch_even_cells(const double* A, double* E, int64_t rows, int na, int nb, int axes, hipStream_t st);
 }  // namespace omni
 
@@ -2099,6 +2102,8 @@ struct omni_hybrid_s {
   omni_dtype dtype = OMNI_CF32;
   int64_t N = 0, mx = 0, my = 0, Mp = 0, chunk_T = 1;
   bool fused = false;              // the y-axis transform runs inside the pair stage (P m_y <= 512)
+  bool mfma = false;               // pair stage on the matrix cores (integer samples): d_S is [F][mx][my][P][P], p <= q
+  float in_scale = 1.f;            // its power-of-two input scale
   std::vector<double> offsets, A;  // metadata for omni_hybrid_baselines (may be empty)
   float2* d_tw32 = nullptr;        // forward tables: w_mx^q then w_my^q (float32)
   double2* d_tw64 = nullptr;       // inverse tables (float64)
@@ -2106,6 +2111,7 @@ struct omni_hybrid_s {
   double2* d_S = nullptr;          // [F][P][P][mx][my] cross-power sums
   std::vector<omni::InvGroup> inv;  // the inverse's one group of axes
   uint16_t* d_inv_tab = nullptr;    // its offset table
+  uint16_t* d_pairs = nullptr;      // matrix-core pair stage: p P + q of the pairs p <= q
 };
 
 namespace {
@@ -2119,6 +2125,7 @@ void hybrid_free(omni_hybrid_s* h) {
   hipFree(h->d_y[1]);
   hipFree(h->d_S);
   hipFree(h->d_inv_tab);
+  hipFree(h->d_pairs);
 }
 
 int hybrid_alloc(omni_hybrid_s* h) {
@@ -2131,8 +2138,17 @@ int hybrid_alloc(omni_hybrid_s* h) {
   HIP_TRY(hipMalloc(&h->d_S, (size_t)(pairs * h->Mp) * sizeof(double2)));
   // both axes are powers of two of at most 64: one inverse group, no intermediate
   const int n2[2] = {h->nx, h->ny}, m2[2] = {(int)h->mx, (int)h->my}, off2[2] = {0, (int)h->mx};
-  const int rc = alloc_inverse(2, n2, m2, pairs, 1, off2, h->inv, &h->d_inv_tab);
+  const int n_pairs = h->P * (h->P + 1) / 2;
+  const int rc = h->mfma ? alloc_inverse(2, n2, m2, h->F, n_pairs, off2, h->inv, &h->d_inv_tab)
+                         : alloc_inverse(2, n2, m2, pairs, 1, off2, h->inv, &h->d_inv_tab);
   if (rc) return rc;
+  if (h->mfma) {
+    std::vector<uint16_t> pq;
+    for (int p = 0; p < h->P; ++p)
+      for (int q = p; q < h->P; ++q) pq.push_back((uint16_t)(p * h->P + q));
+    HIP_TRY(hipMalloc(&h->d_pairs, pq.size() * sizeof(uint16_t)));
+    HIP_TRY(hipMemcpy(h->d_pairs, pq.data(), pq.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
+  }
   if (h->inv.size() != 1 || h->inv[0].direct) return fail(OMNI_E_SHAPE, "hybrid tiles: no inverse schedule");
   const int32_t desc[12] = {(int32_t)h->mx, -1, 0, (int32_t)h->my, -1, (int32_t)h->mx,
                             (int32_t)h->mx, +1, 0, (int32_t)h->my, +1, (int32_t)h->mx};
@@ -2183,6 +2199,13 @@ int omni_hybrid_plan(omni_hybrid_t* out, int32_t P, int32_t nx, int32_t ny, int3
     const int64_t rows = 512 / (P * h->my);
     h->fused = rows >= 1 && h->mx % rows == 0;
   }
+  // the matrix-core pair stage: integer samples (their size bounds the transforms: |Y| <= n_x n_y sqrt(2) max, scaled
+  // below 2^15), and the shapes its kernel takes
+  if (h->dtype != OMNI_CF32 && omni::xengine_mfma_ok(P, nx, ny)) {
+    h->mfma = true;
+    const double top = 1.4143 * (h->dtype == OMNI_CI8 ? 128.0 : 8.0) * nx * ny;
+    while (top * h->in_scale > 32768.0) h->in_scale *= 0.5f;
+  }
   int rc = check_device(&h->device);
   if (rc) return rc;
   try {
@@ -2224,6 +2247,10 @@ int omni_hybrid_correlate(omni_hybrid_t h, const void* volt, int64_t T, void* vi
                                     std::max<int>(1, (int)h->mx / 16), h->ny, h->N, h->P * h->mx * h->ny, st, false,
                                     1.f));
     const int acc = (accumulate || c0 > 0) ? 1 : 0;
+    if (h->mfma) {
+      HIP_TRY(omni::launch_xengine_mfma(h->d_y[0], tc, h->F, h->P, (int)h->mx, h->ny, h->in_scale, h->d_S, acc, st));
+      continue;
+    }
     if (h->fused) {
       // y-axis transform inside the pair stage
       HIP_TRY(omni::launch_xengine_fused(h->d_y[0], tc, h->F, h->P, (int)h->mx, h->ny, h->d_tw32 + h->mx, h->d_S, acc,
@@ -2237,8 +2264,12 @@ int omni_hybrid_correlate(omni_hybrid_t h, const void* volt, int64_t T, void* vi
   }
   if (!(flags & OMNI_NO_FINALIZE)) {
     const omni::InvGroup& g = h->inv[0];
-    HIP_TRY(omni::launch_inverse_group(2, h->d_S, vis, h->d_tw64, h->d_inv_tab, pairs, 1, 1.0 / (double)h->Mp, g.P,
-                                       g.lds, st));
+    if (h->mfma)
+      HIP_TRY(omni::launch_inverse_group(3, h->d_S, vis, h->d_tw64, h->d_inv_tab, h->F, h->P * (h->P + 1) / 2,
+                                         1.0 / (double)h->Mp, g.P, g.lds, st, h->d_pairs, h->P));
+    else
+      HIP_TRY(omni::launch_inverse_group(2, h->d_S, vis, h->d_tw64, h->d_inv_tab, pairs, 1, 1.0 / (double)h->Mp, g.P,
+                                         g.lds, st));
   }
   return OMNI_OK;
 }

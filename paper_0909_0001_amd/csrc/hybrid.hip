@@ -30,6 +30,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "dftn.hpp"
+
 namespace omni {
 namespace {
 
@@ -235,6 +237,249 @@ hipError_t launch_xf_ny(const float2* Y1, int64_t Tc, int F, int mx, int ny, con
   }
 }
 
+// ---------------------------------------------------------------------------
+// Pair stage on the matrix cores, for integer samples.
+//
+// Every Fourier cell's matrix S_pq = sum_t Y_p conj(Y_q) is a product with the time axis as the contraction.  The
+// float32 values are split into two float16 parts, Y = hi + lo (lo = rn16(Y - hi): the pair holds 22 bits, an error
+// of 2^-24 of the value), and hi hi + hi lo + lo hi is summed in float32 by v_mfma_f32_16x16x32_f16, K = 16 samples
+// x (re, im):
+//   Re S_pq = sum (re_p, im_p) . (re_q, im_q),   Im S_pq = sum (re_p, im_p) . (-im_q, re_q).
+// Integer samples bound |Y| (a power-of-two input scale keeps it below 2^15), so float16's range is never left; float
+// samples run the vector-unit kernels above.
+//
+// A work-group of 4 waves owns R = 256 / (P n_y) rows kappa_x of one channel: R m_y P = 512 matrix rows in 32 tiles of
+// 16 (a cell's P tiles are consecutive rows: a 16-row tile holds 16 / P cells, or half a cell for P = 32), 8 tiles a
+// wave.  Per 16 samples:
+//   stage  the rows' lines Y1[t][p][kappa_x][i_y] arrive coalesced (prefetched into registers one batch ahead) in LDS;
+//   lines  a thread transforms a line (n_y -> 2 n_y, register transform) and writes hi and lo as float16 (re, im)
+//          pairs, [tile][row][sample], 16-byte chunks XOR-permuted so that these 4-byte writes and the operand reads
+//          (16 bytes: 4 samples) meet every bank once;
+//   pairs  6 products a tile.
+// The staged lines and the operands share one 64 KiB LDS buffer: two work-groups a CU, whose phases overlap.  Float32
+// sums over the call's samples (at most 256), then float64 read-modify-writes of S[f][kappa][p][q], p <= q only.
+//
+// What bounds it: the vector units' line transforms and splits (busy 51% of the time) and HBM (the lines are read
+// once, S read and written once a call: 1.4 GB), in phases that two work-groups a CU overlap only in part.  16 tiles
+// of 16x16, 64 channels, 256 samples (4-bit): 402 us a launch (335 us the first, which reads no S) against 640 us for
+// the vector-unit kernel above.  Reading the lines straight into the transforming thread's registers, without the
+// stage in LDS, takes 499 us (a thread's 16-byte reads are then 256 KiB apart).
+// ---------------------------------------------------------------------------
+typedef _Float16 xe_half8 __attribute__((ext_vector_type(8)));
+typedef _Float16 xe_half2 __attribute__((ext_vector_type(2)));
+typedef float xe_float4 __attribute__((ext_vector_type(4)));
+
+constexpr int kXmSamples = 16;  // samples per matrix product
+
+// (re, im) pairs -> (-im, re)
+__device__ __forceinline__ xe_half8 xe_rotate(xe_half8 v) {
+  uint4 u = __builtin_bit_cast(uint4, v);
+  u.x = __builtin_amdgcn_alignbit(u.x, u.x, 16) ^ 0x8000u;
+  u.y = __builtin_amdgcn_alignbit(u.y, u.y, 16) ^ 0x8000u;
+  u.z = __builtin_amdgcn_alignbit(u.z, u.z, 16) ^ 0x8000u;
+  u.w = __builtin_amdgcn_alignbit(u.w, u.w, 16) ^ 0x8000u;
+  return __builtin_bit_cast(xe_half8, u);
+}
+
+template <int P, int NY>
+__global__ __launch_bounds__(kXeThreads, 2) void xengine_mfma_kernel(const float2* __restrict__ Y1, int Tc, int F,
+                                                                     int mx, float in_scale, float out_scale,
+                                                                     double2* __restrict__ S, int accumulate) {
+  constexpr int MY = 2 * NY;
+  constexpr int R = kXeThreads / (P * NY);        // rows kappa_x
+  constexpr int SLOTS = R * P;                    // lines per sample
+  constexpr int LINES = kXmSamples * SLOTS;       // per batch: 4096 / NY
+  constexpr int PER = LINES / kXeThreads;         // lines a thread transforms
+  constexpr int CH = NY / 2;                      // 16-byte pieces per line
+  constexpr int TILES = 32, WT = TILES / 4;       // tiles, tiles per wave
+  constexpr int GR = P > 16 ? 2 : 1;              // row groups of 16 per cell
+  constexpr int PAIRS = GR == 2 ? 3 : 1;          // tile products per cell (of GR tiles)
+  constexpr int ACC = WT / GR * PAIRS;
+  static_assert(R * P * NY == kXeThreads && PER >= 1 && NY >= 4 && R * MY * P == 16 * TILES, "geometry");
+  __shared__ uint4 buf[2 * TILES * 16 * 4];  // operands: [hi, lo][tile][row][4 chunks]; staged lines alias the start
+  uint4* const stage = buf;                  // [line][CH], 2048 pieces
+  uint32_t* const words = reinterpret_cast<uint32_t*>(buf);
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int f = blockIdx.y, kx0 = blockIdx.x * R;
+
+  // Pieces in memory order (R CH consecutive threads read consecutive memory): 128 a sample, so piece u of a thread
+  // belongs to sample 2 u + tid / 128 and differs from piece 0 by a multiple of the sample stride only.  Lines are
+  // numbered p fastest, then t, then r: a wave's lines then differ in matrix row and sample, which its operand writes
+  // need to meet different banks.
+  constexpr int LOADS = 2048 / kXeThreads, SH = CH == 8 ? 0 : CH == 4 ? 2 : 3;
+  static_assert(LINES * CH == 2048 && CH * SLOTS == 128, "pieces of a batch");
+  const int pc = tid % CH, pr = tid / CH % R, pp = tid / (CH * R) % P, pt = tid >> 7;
+  const int64_t slab = (int64_t)P * mx * NY, sample = (int64_t)F * slab;
+  const float2* const src = Y1 + pt * sample + (int64_t)f * slab + ((int64_t)pp * mx + kx0 + pr) * NY + 2 * pc;
+  float4 pf[LOADS];
+  auto fetch = [&](int t0) __attribute__((always_inline)) {
+    if (t0 + kXmSamples <= Tc) {
+#pragma unroll
+      for (int u = 0; u < LOADS; ++u) pf[u] = *reinterpret_cast<const float4*>(src + (t0 + 2 * u) * sample);
+    } else {
+#pragma unroll
+      for (int u = 0; u < LOADS; ++u) {
+        pf[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (t0 + 2 * u + pt < Tc) pf[u] = *reinterpret_cast<const float4*>(src + (t0 + 2 * u) * sample);
+      }
+    }
+  };
+
+  xe_float4 re[ACC], im[ACC];
+#pragma unroll
+  for (int k = 0; k < ACC; ++k) re[k] = im[k] = xe_float4{0.f, 0.f, 0.f, 0.f};
+
+  fetch(0);
+#pragma unroll 1
+  for (int t0 = 0; t0 < Tc; t0 += kXmSamples) {
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) {
+      const int line = (pr * kXmSamples + pt + 2 * u) * P + pp;
+      stage[line * CH + (pc ^ ((line >> SH) & (CH - 1)))] = __builtin_bit_cast(uint4, pf[u]);
+    }
+    __syncthreads();
+    float2 x[PER][NY];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int line = k * kXeThreads + tid;
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        const float4 v = __builtin_bit_cast(float4, stage[line * CH + (c ^ ((line >> SH) & (CH - 1)))]);
+        x[k][2 * c] = make_float2(v.x, v.y);
+        x[k][2 * c + 1] = make_float2(v.z, v.w);
+      }
+    }
+    if (in_scale != 1.f) {
+#pragma unroll
+      for (int k = 0; k < PER; ++k)
+#pragma unroll
+        for (int j = 0; j < NY; ++j) x[k][j] = make_float2(x[k][j].x * in_scale, x[k][j].y * in_scale);
+    }
+    if (t0 + kXmSamples < Tc) fetch(t0 + kXmSamples);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int line = k * kXeThreads + tid;
+      const int p = line % P, t = line / P % kXmSamples, r = line / (P * kXmSamples);
+      auto put = [&](int ky, float2 v) __attribute__((always_inline)) {
+        const int g = (r * MY + ky) * P + p, tile = g >> 4, row = g & 15;
+        const int at = (tile * 16 + row) * 16 + ((t >> 2) ^ (row >> 2)) * 4 + (t & 3);
+        const xe_half2 h = {(_Float16)v.x, (_Float16)v.y};
+        const uint32_t hb = __builtin_bit_cast(uint32_t, h);
+        float lx, ly;  // v - hi, exact (one mixed-precision FMA each instead of a conversion and a subtraction)
+        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(lx) : "v"(hb), "v"(v.x));
+        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(ly) : "v"(hb), "v"(v.y));
+        const xe_half2 l = {(_Float16)lx, (_Float16)ly};
+        words[at] = hb;
+        words[TILES * 256 + at] = __builtin_bit_cast(uint32_t, l);
+      };
+      float2 z[NY];
+#pragma unroll
+      for (int j = 0; j < NY; ++j) z[j] = x[k][j];
+      dn::dft<NY>(z);
+#pragma unroll
+      for (int q = 0; q < NY; ++q) put(2 * q, z[q]);
+#pragma unroll
+      for (int j = 0; j < NY; ++j) z[j] = dn::rot<MY>(x[k][j], j);
+      dn::dft<NY>(z);
+#pragma unroll
+      for (int q = 0; q < NY; ++q) put(2 * q + 1, z[q]);
+    }
+    __syncthreads();
+    {
+      const int row = lane & 15, kb = lane >> 4;
+      const int at = row * 4 + (kb ^ (row >> 2));
+#pragma unroll
+      for (int k = 0; k < WT / GR; ++k) {
+        xe_half8 h[GR], l[GR];
+#pragma unroll
+        for (int g = 0; g < GR; ++g) {
+          const int tile = (wave * WT + k * GR + g) * 64;
+          h[g] = __builtin_bit_cast(xe_half8, buf[tile + at]);
+          l[g] = __builtin_bit_cast(xe_half8, buf[TILES * 64 + tile + at]);
+        }
+#pragma unroll
+        for (int q = 0; q < PAIRS; ++q) {
+          const int a = q == 2 ? 1 : 0, b = q == 0 ? 0 : GR - 1;  // (0,0), (0,1), (1,1)
+          xe_float4& cr = re[k * PAIRS + q];
+          xe_float4& ci = im[k * PAIRS + q];
+          cr = __builtin_amdgcn_mfma_f32_16x16x32_f16(h[a], h[b], cr, 0, 0, 0);
+          cr = __builtin_amdgcn_mfma_f32_16x16x32_f16(h[a], l[b], cr, 0, 0, 0);
+          cr = __builtin_amdgcn_mfma_f32_16x16x32_f16(l[a], h[b], cr, 0, 0, 0);
+          const xe_half8 hb = xe_rotate(h[b]), lb = xe_rotate(l[b]);
+          ci = __builtin_amdgcn_mfma_f32_16x16x32_f16(h[a], hb, ci, 0, 0, 0);
+          ci = __builtin_amdgcn_mfma_f32_16x16x32_f16(h[a], lb, ci, 0, 0, 0);
+          ci = __builtin_amdgcn_mfma_f32_16x16x32_f16(l[a], hb, ci, 0, 0, 0);
+        }
+      }
+    }
+    __syncthreads();
+  }
+
+  // lane: column q = lane % 16, rows 4 (lane / 16) + i of each tile product
+  const int64_t Mp = (int64_t)mx * MY;
+#pragma unroll
+  for (int k = 0; k < WT / GR; ++k) {
+#pragma unroll
+    for (int q2 = 0; q2 < PAIRS; ++q2) {
+      const int a = q2 == 2 ? 1 : 0, b = q2 == 0 ? 0 : GR - 1;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = 4 * (lane >> 4) + i, col = lane & 15;
+        const int g0 = (wave * WT + k * GR) * 16;  // first matrix row of the cell's (or tile's) rows
+        int cell, p, q;
+        if constexpr (P >= 16) {
+          cell = g0 / P;
+          p = 16 * a + row;
+          q = 16 * b + col;
+        } else {
+          if (row / P != col / P) continue;
+          cell = (g0 + row) / P;
+          p = row % P;
+          q = col % P;
+        }
+        if (p > q) continue;
+        const int64_t kappa = (int64_t)(kx0 + cell / MY) * MY + cell % MY;
+        double2* sp = S + (((int64_t)f * Mp + kappa) * P + p) * P + q;
+        double2 o = make_double2((double)(re[k * PAIRS + q2][i] * out_scale), (double)(im[k * PAIRS + q2][i] * out_scale));
+        if (accumulate) {
+          const double2 old = *sp;
+          o.x += old.x;
+          o.y += old.y;
+        }
+        *sp = o;
+      }
+    }
+  }
+}
+
+template <int P, int NY>
+hipError_t launch_xm(const float2* Y1, int64_t Tc, int F, int mx, float scale, double2* S, int accumulate,
+                     hipStream_t st) {
+  if constexpr (P * NY > kXeThreads) {
+    return hipErrorInvalidValue;
+  } else {
+    constexpr int R = kXeThreads / (P * NY);
+    if (mx % R != 0 || F < 1 || F > 65535 || Tc < 1 || Tc > 1 << 20 ||
+        (reinterpret_cast<uintptr_t>(Y1) & 15) != 0)
+      return hipErrorInvalidValue;
+    hipLaunchKernelGGL((xengine_mfma_kernel<P, NY>), dim3((unsigned)(mx / R), (unsigned)F), dim3(kXeThreads), 0, st, Y1,
+                       (int)Tc, F, mx, scale, 1.f / (scale * scale), S, accumulate);
+    return hipGetLastError();
+  }
+}
+
+template <int P>
+hipError_t launch_xm_ny(const float2* Y1, int64_t Tc, int F, int mx, int ny, float scale, double2* S, int accumulate,
+                        hipStream_t st) {
+  switch (ny) {
+    case 4: return launch_xm<P, 4>(Y1, Tc, F, mx, scale, S, accumulate, st);
+    case 8: return launch_xm<P, 8>(Y1, Tc, F, mx, scale, S, accumulate, st);
+    case 16: return launch_xm<P, 16>(Y1, Tc, F, mx, scale, S, accumulate, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 }  // namespace
 
 // The fused form applies when P n_y <= 256 (n_y a power of two up to 32).
@@ -260,6 +505,24 @@ hipError_t launch_xengine(const float2* Y, int64_t Tc, int F, int P, int64_t Mp,
     case 8: return launch_xe<8>(Y, Tc, F, Mp, S, accumulate, st);
     case 16: return launch_xe<16>(Y, Tc, F, Mp, S, accumulate, st);
     case 32: return launch_xe<32>(Y, Tc, F, Mp, S, accumulate, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// The matrix-core pair stage takes P of 4 to 32 tiles of n_y of 4 to 16 with P n_y <= 256, its rows dividing m_x, and
+// at most 1024 cells (one inverse group).
+bool xengine_mfma_ok(int P, int nx, int ny) {
+  if (P < 4 || P > 32 || (ny != 4 && ny != 8 && ny != 16) || P * ny > kXeThreads) return false;
+  return 2 * nx % (kXeThreads / (P * ny)) == 0 && 4 * nx * ny <= 1024;
+}
+
+hipError_t launch_xengine_mfma(const float2* Y1, int64_t Tc, int F, int P, int mx, int ny, float scale, double2* S,
+                               int accumulate, hipStream_t st) {
+  switch (P) {
+    case 4: return launch_xm_ny<4>(Y1, Tc, F, mx, ny, scale, S, accumulate, st);
+    case 8: return launch_xm_ny<8>(Y1, Tc, F, mx, ny, scale, S, accumulate, st);
+    case 16: return launch_xm_ny<16>(Y1, Tc, F, mx, ny, scale, S, accumulate, st);
+    case 32: return launch_xm_ny<32>(Y1, Tc, F, mx, ny, scale, S, accumulate, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -29,24 +29,37 @@ struct Ctx {
   double scale;
   int n_cols;                 // columns of this tile
   bool mine;                  // this thread's column exists (interleaved columns)
+  const uint16_t* __restrict__ pair_tab;  // SRC 3: p P + q of every tile pair p <= q
+  uint32_t col0, n_pairs, n_tiles;        // SRC 3: first column, pairs per channel, tiles
 };
 
 // One pass' lines: FIRST reads them from HBM, otherwise from LDS; LAST writes the valid lags to HBM.
-// SRC: 0 = real float64, 1 = complex float32, 2 = complex float64.
+// SRC: 0 = real float64, 1 = complex float32, 2 = complex float64, 3 = complex float64 of the tile pairs p <= q,
+// [channel][cell][p][q]: a column is one pair, written as C_pq[Delta] and as C_qp[-Delta] = conj C_pq[Delta].
 template <int N, int SRC, bool FIRST, bool LAST>
 __device__ __forceinline__ void inv_pass(const InvPass& p, const InvP& P, const Ctx& x) {
   const uint32_t jobs = (uint32_t)(p.lines * (P.col_fast ? P.cols : x.n_cols));
   for (uint32_t q = threadIdx.x; q < jobs; q += blockDim.x) {
     uint32_t c, line;
-    if (P.col_fast) {
+    if (P.col_fast && !(SRC == 3 && LAST)) {
       c = q & (uint32_t)(P.cols - 1);
       line = q >> P.lg_cols;
-    } else {
+    } else {  // (a pair's lags are one run: neighbouring threads write neighbouring lags)
       c = fast_div(q, p.magic);
       line = q - c * p.lines;
     }
     double2 v[N];
-    if constexpr (FIRST) {
+    if constexpr (FIRST && SRC == 3) {
+      const int64_t step = (int64_t)x.n_tiles * x.n_tiles;
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        v[j] = make_double2(0.0, 0.0);
+        if (x.mine) {
+          const double2 t = static_cast<const double2*>(x.src)[x.src0 + (int64_t)(j * p.lines + line) * step];
+          v[j] = make_double2(t.y, t.x);
+        }
+      }
+    } else if constexpr (FIRST) {
       const int64_t at = x.src0 + (P.col_fast ? (int64_t)line * x.inner : (int64_t)(c * P.Mg + line));
       const int64_t step = P.col_fast ? (int64_t)p.lines * x.inner : (int64_t)p.lines;
 #pragma unroll
@@ -81,6 +94,20 @@ __device__ __forceinline__ void inv_pass(const InvPass& p, const InvP& P, const 
       }
 #pragma unroll
       for (int k = 0; k < N; ++k) w[k * p.stride] = v[k];
+    } else if constexpr (SRC == 3) {
+      if ((int)c >= x.n_cols) continue;
+      const uint32_t col = x.col0 + c, f = col / x.n_pairs, pq = x.pair_tab[col - f * x.n_pairs];
+      const uint32_t tp = pq / x.n_tiles, tq = pq - tp * x.n_tiles;
+      float2* d = x.dst + ((int64_t)f * x.n_tiles * x.n_tiles + pq) * P.Ng;
+      float2* m = x.dst + ((int64_t)f * x.n_tiles * x.n_tiles + tq * x.n_tiles + tp) * P.Ng + (P.Ng - 1);
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        const uint32_t o = x.tab[P.out_tab + k * p.lines + line];
+        if (o == kInvNoLag) continue;
+        const float a = (float)(v[k].y * x.scale), b = (float)(v[k].x * x.scale);
+        d[o] = make_float2(a, b);
+        if (tp != tq) m[-(int64_t)o] = make_float2(a, -b);
+      }
     } else if (x.mine) {
 #pragma unroll
       for (int k = 0; k < N; ++k) {
@@ -114,7 +141,8 @@ template <int SRC>
 __global__ __launch_bounds__(512, 4) void inverse_group_kernel(const void* __restrict__ src, float2* __restrict__ dst,
                                                             const double2* __restrict__ twi,
                                                             const uint16_t* __restrict__ tab, int64_t columns,
-                                                            int64_t inner, double scale, InvP P) {
+                                                            int64_t inner, double scale, InvP P,
+                                                            const uint16_t* __restrict__ pair_tab, int n_tiles) {
   extern __shared__ double2 W[];
   // consecutive column tiles on one XCD: where the columns are interleaved, tiles share cache lines
   int64_t blk = blockIdx.x;
@@ -123,19 +151,26 @@ __global__ __launch_bounds__(512, 4) void inverse_group_kernel(const void* __res
   // interleaved columns: this thread's column is fixed (the thread count is a multiple of cols); whole columns: the
   // tile is one contiguous run
   const int64_t col = col0 + (threadIdx.x & (uint32_t)(P.cols - 1)), ou = P.col_fast ? col / inner : 0;
+  int64_t src0 = P.col_fast ? ou * P.Mg * inner + (col - ou * inner) : col0 * P.Mg;
+  if constexpr (SRC == 3)
+    src0 = col < columns ? ou * P.Mg * n_tiles * n_tiles + pair_tab[col - ou * inner] : 0;
   const Ctx x{W,
               twi,
               tab,
               src,
               dst,
-              P.col_fast ? ou * P.Mg * inner + (col - ou * inner) : col0 * P.Mg,
+              src0,
               P.col_fast ? ou * P.Ng * inner + (col - ou * inner) : col0 * P.Ng,
               inner,
               scale,
               (int)min<int64_t>(P.cols, columns - col0),
-              !P.col_fast || col < columns};
-  if (P.n_pass == 1) {
-    inv_any<SRC, true, true>(P.pass[0], P, x);
+              !P.col_fast || col < columns,
+              pair_tab,
+              (uint32_t)col0,
+              (uint32_t)inner,
+              (uint32_t)n_tiles};
+  if (SRC != 3 && P.n_pass == 1) {
+    inv_any<SRC == 3 ? 1 : SRC, true, true>(P.pass[0], P, x);
     return;
   }
   inv_any<SRC, true, false>(P.pass[0], P, x);
@@ -144,31 +179,36 @@ __global__ __launch_bounds__(512, 4) void inverse_group_kernel(const void* __res
     inv_any<1, false, false>(P.pass[i], P, x);
   }
   __syncthreads();
-  inv_any<1, false, true>(P.pass[P.n_pass - 1], P, x);
+  inv_any<SRC == 3 ? 3 : 1, false, true>(P.pass[P.n_pass - 1], P, x);
 }
 
 }  // namespace
 
-// src_kind: 0 = real float64, 1 = complex float32, 2 = complex float64; outer x inner columns.
+// src_kind: 0 = real float64, 1 = complex float32, 2 = complex float64; outer x inner columns.  3 = the tile pairs
+// p <= q of n_tiles tiles (inner = their number, pair_tab = p n_tiles + q of each), both orders written.
 hipError_t launch_inverse_group(int src_kind, const void* src, void* dst, const double2* twi, const uint16_t* tab,
-                                int64_t outer, int64_t inner, double scale, const InvP& P, size_t lds,
-                                hipStream_t st) {
+                                int64_t outer, int64_t inner, double scale, const InvP& P, size_t lds, hipStream_t st,
+                                const uint16_t* pair_tab, int n_tiles) {
   const int64_t columns = outer * inner, blocks = (columns + P.cols - 1) / P.cols;
   const int threads = P.cols * P.Mg > 2048 ? 512 : 256;
   if (threads % P.cols) return hipErrorInvalidValue;
   if (blocks < 1 || blocks > INT32_MAX || P.n_pass < 1 || P.n_pass > kInvMaxPass || (inner > 1) != (P.col_fast != 0))
     return hipErrorInvalidValue;
+  if (src_kind == 3 && (!pair_tab || P.n_pass < 2 || !P.col_fast || n_tiles < 2 || columns >= INT32_MAX ||
+                        inner != (int64_t)n_tiles * (n_tiles + 1) / 2))
+    return hipErrorInvalidValue;
   const auto go = [&](auto* kernel) {
     hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3((unsigned)threads), lds, st, src, static_cast<float2*>(dst), twi,
-                       tab, columns, inner, scale, P);
+                       tab, columns, inner, scale, P, pair_tab, n_tiles);
     return hipGetLastError();
   };
   switch (src_kind) {
     case 0: return go(inverse_group_kernel<0>);
     case 1: return go(inverse_group_kernel<1>);
     case 2: return go(inverse_group_kernel<2>);
+    case 3: return go(inverse_group_kernel<3>);
     default: return hipErrorInvalidValue;
   }
 }

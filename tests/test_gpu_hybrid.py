@@ -142,3 +142,35 @@ def test_hybrid_bench_size_sampled():
             say(f"[hybrid] bench size f={f} tiles ({p},{q}): err {err:.3g}")
             assert err <= 1e-5
     h.close()
+
+
+MATRIX_CASES = [
+    (4, 8, 4, "ci4", 1, 3),  # one sample of a 16-sample product
+    (4, 4, 8, "ci8", 15, 2),
+    (4, 16, 16, "ci8", 16, 2),  # one whole product
+    (8, 8, 4, "ci4", 17, 2),  # a whole product and one sample
+    (8, 2, 8, "ci8", 33, 1),
+    (8, 16, 16, "ci8", 40, 1),  # input scale below one
+    (16, 2, 4, "ci4", 300, 1),  # two chunks, the second ragged
+    (16, 1, 8, "ci8", 31, 2),  # one row kappa_x per antenna row
+    (32, 4, 4, "ci4", 20, 2),  # two 16-row tiles per cell
+    (32, 16, 8, "ci8", 258, 1),
+]
+
+
+@pytest.mark.parametrize("P,nx,ny,dtype,T,F", MATRIX_CASES)
+def test_hybrid_matrix_core_pair_stage(P, nx, ny, dtype, T, F):
+    """Every tile count and line length of the matrix-core pair stage, sample counts around its 16-sample products and
+    256-sample chunks.  The split keeps 2^-22 of a value (three dropped or rounded parts a product) and a float32 sum
+    of at most 17 partial sums a chunk adds 17 x 2^-24: 2e-6 of the pair's power."""
+    N = P * nx * ny
+    gen = torch.Generator().manual_seed(N + 3 * T)
+    raw = random_raw(dtype, T, F, N, gen)
+    say(f"[hybrid matrix] case P={P} {nx}x{ny} {dtype} T={T} F={F}")
+    h = omni.Hybrid(P, nx, ny, F, dtype)
+    vis = h.correlate(raw.cuda())
+    torch.cuda.synchronize()
+    x = oracle.decode(raw.numpy(), dtype, T, F, N)
+    err = pair_err(vis.cpu().numpy(), hybrid.tile_cross_correlations(x, P, nx, ny), nx, ny)
+    say(f"[hybrid matrix] P={P} {nx}x{ny}: err {err:.3g}")
+    assert err <= 2e-6
