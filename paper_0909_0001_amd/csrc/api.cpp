@@ -35,6 +35,8 @@ hipError_t launch_inverse_axis(bool real_in, bool last, const void* src, void* d
 hipError_t launch_inverse_group(int src_kind, const void* src, void* dst, const double2* twi, const uint16_t* tab,
                                 int64_t outer, int64_t inner, double scale, const InvP& P, size_t lds, hipStream_t st,
                                 const uint16_t* pair_tab = nullptr, int n_tiles = 0);
+hipError_t launch_inverse_line(int src_kind, const void* src, void* dst, int64_t outer, int m, int64_t inner,
+                               hipStream_t st);
 hipError_t launch_twiddles(const int32_t* desc_dev, int n_tables, float2* tw32, double2* tw64, hipStream_t st);
 hipError_t launch_fused8x4_fp32(int fmt, const void* src, int64_t T, int64_t tps, const float2* tw16, double* partial,
                                 int F, int n_slices, int time_block, hipStream_t st);
@@ -894,6 +896,8 @@ int run_inverse(const std::vector<omni::InvGroup>& groups, const uint16_t* d_tab
     if (g.direct)
       HIP_TRY(omni::launch_inverse_axis(src_kind == 0, last, src, dst, twi + tw_off[g.axis0], outer, m[g.axis0],
                                         n[g.axis0], inner, scale, st));
+    else if (g.line)
+      HIP_TRY(omni::launch_inverse_line(src_kind, src, dst, outer, m[g.axis0], inner, st));
     else
       HIP_TRY(omni::launch_inverse_group(src_kind, src, dst, twi, d_tab + g.tab_off, outer, inner, last ? scale : 1.0,
                                          g.P, g.lds, st));

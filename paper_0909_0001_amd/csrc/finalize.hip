@@ -35,7 +35,10 @@ __global__ __launch_bounds__(256) void reduce_scatter_kernel(const double* __res
   for (int64_t i0 = (int64_t)blockIdx.x * CELLS; i0 < total; i0 += (int64_t)gridDim.x * CELLS) {
     const int64_t i = i0 + lane;
     double s = 0.0;
+    double* dst = nullptr;
     if (i < total) {
+      const int64_t f = i / per_f;
+      dst = A + f * M + kmap[i - f * per_f];  // (read beside the slices, not behind them)
       const double* p = partial + i;
       int sl = sg;
       for (; sl + 3 * SG < n_slices; sl += 4 * SG) {
@@ -56,8 +59,6 @@ __global__ __launch_bounds__(256) void reduce_scatter_kernel(const double* __res
         for (int g = 1; g < SG; ++g) s += part[g * CELLS + lane];
     }
     if (sg == 0 && i < total) {
-      const int64_t f = i / per_f;
-      double* dst = A + f * M + kmap[i - f * per_f];
       *dst = accumulate ? *dst + s : s;
     }
   }

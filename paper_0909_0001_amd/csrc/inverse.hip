@@ -3,8 +3,11 @@
 //   V[Delta] = (1/M) sum_kappa A[kappa] exp(+2 pi i sum_k kappa_k Delta_k / m_k)    (Sec. II.A "inverse FFT")
 //
 // The stages are the forward register transforms (dftn.hpp) on values with real and imaginary parts exchanged,
-// which turns a forward transform into an inverse one.  Bound by HBM where the array is large (each group reads and
-// writes it once), by its barriers where it is small.
+// which turns a forward transform into an inverse one.  Bound by the barriers between its passes: a group moves about
+// 2 TB/s, so that arrays beyond the caches take their axes of 8, 16 and 32 one by one (inverse_line_kernel).  Passes
+// of 2 to 8 values leave three work-groups a CU their registers; with passes of 16 (fewer passes, four waves a SIMD and
+// spills) 64 channels of 64x64 took 23 us instead of 19, of 12x12/5x5 (32) 45 instead of 35.  Loading a tile's lines
+// while the tile before is transformed (one persistent work-group a slot) was slower: 1269 for 745 us at 6 x 2^24 cells.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -120,7 +123,7 @@ __device__ __forceinline__ void inv_pass(const InvPass& p, const InvP& P, const 
   }
 }
 
-template <int SRC, bool FIRST, bool LAST>
+template <int SRC, bool WIDE, bool FIRST, bool LAST>
 __device__ __forceinline__ void inv_any(const InvPass& p, const InvP& P, const Ctx& x) {
   switch (p.f) {
     case 2: inv_pass<2, SRC, FIRST, LAST>(p, P, x); break;
@@ -130,15 +133,19 @@ __device__ __forceinline__ void inv_any(const InvPass& p, const InvP& P, const C
     case 6: inv_pass<6, SRC, FIRST, LAST>(p, P, x); break;
     case 7: inv_pass<7, SRC, FIRST, LAST>(p, P, x); break;
     case 8: inv_pass<8, SRC, FIRST, LAST>(p, P, x); break;
-    case 11: inv_pass<11, SRC, FIRST, LAST>(p, P, x); break;
-    case 13: inv_pass<13, SRC, FIRST, LAST>(p, P, x); break;
-    case 16: inv_pass<16, SRC, FIRST, LAST>(p, P, x); break;
+    case 11:
+      if constexpr (WIDE) inv_pass<11, SRC, FIRST, LAST>(p, P, x);
+      break;
+    case 13:
+      if constexpr (WIDE) inv_pass<13, SRC, FIRST, LAST>(p, P, x);
+      break;
     default: break;
   }
 }
 
-template <int SRC>
-__global__ __launch_bounds__(512, 4) void inverse_group_kernel(const void* __restrict__ src, float2* __restrict__ dst,
+// WIDE: a pass of 11 or 13 values, which need the registers of four waves a SIMD.
+template <int SRC, bool WIDE>
+__global__ __launch_bounds__(512, WIDE ? 4 : 6) void inverse_group_kernel(const void* __restrict__ src, float2* __restrict__ dst,
                                                             const double2* __restrict__ twi,
                                                             const uint16_t* __restrict__ tab, int64_t columns,
                                                             int64_t inner, double scale, InvP P,
@@ -170,19 +177,64 @@ __global__ __launch_bounds__(512, 4) void inverse_group_kernel(const void* __res
               (uint32_t)inner,
               (uint32_t)n_tiles};
   if (SRC != 3 && P.n_pass == 1) {
-    inv_any<SRC == 3 ? 1 : SRC, true, true>(P.pass[0], P, x);
+    inv_any<SRC == 3 ? 1 : SRC, WIDE, true, true>(P.pass[0], P, x);
     return;
   }
-  inv_any<SRC, true, false>(P.pass[0], P, x);
+  inv_any<SRC, WIDE, true, false>(P.pass[0], P, x);
   for (int i = 1; i + 1 < P.n_pass; ++i) {
     __syncthreads();
-    inv_any<1, false, false>(P.pass[i], P, x);
+    inv_any<1, WIDE, false, false>(P.pass[i], P, x);
   }
   __syncthreads();
-  inv_any<SRC == 3 ? 3 : 1, false, true>(P.pass[P.n_pass - 1], P, x);
+  inv_any<SRC == 3 ? 3 : 1, WIDE, false, true>(P.pass[P.n_pass - 1], P, x);
+}
+
+// One axis of an array beyond the caches, a thread a line, transformed in registers: neighbouring threads take
+// neighbouring columns.  One read and one write of the array at HBM's rate: axes
+// of 32, 32, 16, 16 of 6 x 2^24 cells 411, 284, 266 and 244 us (3.7 to 5.5 TB/s), the same axes in two groups 745 and 689 us.
+template <int M, int SRC>
+__global__ __launch_bounds__(256) void inverse_line_kernel(const void* __restrict__ src, float2* __restrict__ dst,
+                                                           int64_t columns, int64_t inner) {
+  const int64_t col = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (col >= columns) return;
+  const int64_t ou = col / inner, in = col - ou * inner;
+  double2 v[M];
+#pragma unroll
+  for (int j = 0; j < M; ++j) {
+    const int64_t at = (ou * M + j) * inner + in;
+    if constexpr (SRC == 0) {
+      v[j] = make_double2(0.0, static_cast<const double*>(src)[at]);
+    } else {
+      const float2 t = static_cast<const float2*>(src)[at];
+      v[j] = make_double2(t.y, t.x);
+    }
+  }
+  dn::dft<M>(v);
+#pragma unroll
+  for (int o = 0; o < M - 1; ++o) {
+    const int k = (o + M / 2 + 1) % M;  // lag o - (M / 2 - 1)
+    dst[(ou * (M - 1) + o) * inner + in] = make_float2((float)v[k].y, (float)v[k].x);
+  }
 }
 
 }  // namespace
+
+// One axis of length 8, 16 or 32 that is not the last one: [outer][m][inner] -> [outer][m - 1][inner].
+hipError_t launch_inverse_line(int src_kind, const void* src, void* dst, int64_t outer, int m, int64_t inner,
+                               hipStream_t st) {
+  const int64_t columns = outer * inner, blocks = (columns + 255) / 256;
+  if (blocks < 1 || blocks > INT32_MAX || src_kind < 0 || src_kind > 1) return hipErrorInvalidValue;
+  const auto go = [&](auto* kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st, src, static_cast<float2*>(dst), columns, inner);
+    return hipGetLastError();
+  };
+  switch (m) {
+    case 8: return src_kind ? go(inverse_line_kernel<8, 1>) : go(inverse_line_kernel<8, 0>);
+    case 16: return src_kind ? go(inverse_line_kernel<16, 1>) : go(inverse_line_kernel<16, 0>);
+    case 32: return src_kind ? go(inverse_line_kernel<32, 1>) : go(inverse_line_kernel<32, 0>);
+    default: return hipErrorInvalidValue;
+  }
+}
 
 // src_kind: 0 = real float64, 1 = complex float32, 2 = complex float64; outer x inner columns.  3 = the tile pairs
 // p <= q of n_tiles tiles (inner = their number, pair_tab = p n_tiles + q of each), both orders written.
@@ -204,11 +256,13 @@ hipError_t launch_inverse_group(int src_kind, const void* src, void* dst, const 
                        tab, columns, inner, scale, P, pair_tab, n_tiles);
     return hipGetLastError();
   };
+  bool wide = false;
+  for (int i = 0; i < P.n_pass; ++i) wide = wide || P.pass[i].f > 8;
   switch (src_kind) {
-    case 0: return go(inverse_group_kernel<0>);
-    case 1: return go(inverse_group_kernel<1>);
-    case 2: return go(inverse_group_kernel<2>);
-    case 3: return go(inverse_group_kernel<3>);
+    case 0: return wide ? go(inverse_group_kernel<0, true>) : go(inverse_group_kernel<0, false>);
+    case 1: return wide ? go(inverse_group_kernel<1, true>) : go(inverse_group_kernel<1, false>);
+    case 2: return wide ? go(inverse_group_kernel<2, true>) : go(inverse_group_kernel<2, false>);
+    case 3: return wide ? go(inverse_group_kernel<3, true>) : go(inverse_group_kernel<3, false>);
     default: return hipErrorInvalidValue;
   }
 }

@@ -17,6 +17,7 @@
 namespace omni {
 
 constexpr int kInvMaxPass = 16;
+constexpr int kInvPlain[] = {2, 3, 4, 5, 6, 7, 8, 11, 13};  // register transforms of the passes
 constexpr uint32_t kInvNoLag = 0xffff;
 
 struct InvPass {
@@ -43,6 +44,7 @@ struct InvP {
 struct InvGroup {
   int axis0 = 0, axes = 0;    // the axes it covers
   bool direct = false;        // one axis without a register transform: plain sums (finalize.hip)
+  bool line = false;          // one axis, a thread a line (arrays beyond the caches)
   InvP P{};
   std::vector<uint16_t> tab;
   size_t tab_off = 0;         // first entry in the plan's device table

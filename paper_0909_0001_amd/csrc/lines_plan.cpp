@@ -432,14 +432,14 @@ bool plan_lines(int d, const int* n, const int* m, int max_batch, LineSetup& out
 // kTileCells cells, fewer where there would be under two work-groups a CU.
 std::vector<InvGroup> plan_inverse(int d, const int* n, const int* m, int64_t channels, int64_t inner,
                                    const int* tw_off) {
-  constexpr int64_t kGroupCells = 1024, kChannelCells = 4096, kTileCells = 4096;
+  constexpr int64_t kGroupCells = 1024, kChannelCells = 4096, kTileCells = 4096, kLineCells = int64_t(1) << 25;
   std::vector<InvGroup> out;
   std::vector<int> chain;
   int64_t all = inner;
   bool whole = inner == 1;
   for (int k = 0; k < d; ++k) {
     all *= m[k];
-    whole = whole && plain_chain(m[k], chain, kLinePlain);
+    whole = whole && plain_chain(m[k], chain, kInvPlain);
   }
   whole = whole && all <= kChannelCells;
   int64_t outer = channels, rest = all;
@@ -448,7 +448,7 @@ std::vector<InvGroup> plan_inverse(int d, const int* n, const int* m, int64_t ch
     InvGroup g;
     g.axis0 = k;
     g.tab_off = tab_off;
-    if (!plain_chain(m[k], chain, kLinePlain) || m[k] > kTileCells) {
+    if (!plain_chain(m[k], chain, kInvPlain) || m[k] > kTileCells) {
       g.axes = 1;
       g.direct = true;
       rest /= m[k];
@@ -457,9 +457,20 @@ std::vector<InvGroup> plan_inverse(int d, const int* n, const int* m, int64_t ch
       out.push_back(g);
       continue;
     }
+    // An array beyond the last-level cache (256 MB) goes through HBM with every pass: threads that transform a line
+    // each in registers run at its rate, a group at half of it, so they win where their reads are whole cache lines.
+    if (inner == 1 && channels * all >= kLineCells && rest / m[k] >= 64 && (m[k] == 8 || m[k] == 16 || m[k] == 32)) {
+      g.axes = 1;
+      g.line = true;
+      rest /= m[k];
+      outer *= 2 * n[k] - 1;
+      ++k;
+      out.push_back(g);
+      continue;
+    }
     int64_t Mg = 1, Ng = 1;
     std::vector<Stage> st;
-    while (k < d && plain_chain(m[k], chain, kLinePlain) && (g.axes == 0 || whole || Mg * m[k] <= kGroupCells)) {
+    while (k < d && plain_chain(m[k], chain, kInvPlain) && (g.axes == 0 || whole || Mg * m[k] <= kGroupCells)) {
       int done = 1, rem = m[k];
       std::vector<Stage> one;
       for (int f : chain) {
@@ -493,8 +504,8 @@ std::vector<InvGroup> plan_inverse(int d, const int* n, const int* m, int64_t ch
       // stages, one to read with and one to write with
       const int mm = m[g.axis0];
       int f = 2;
-      for (int v : kLinePlain)
-        if (mm % v == 0 && v * v <= mm && has(kLinePlain, mm / v)) f = v;
+      for (int v : kInvPlain)
+        if (mm % v == 0 && v * v <= mm && has(kInvPlain, mm / v)) f = v;
       st.insert(st.begin(), st[0]);
       st[0] = {g.axis0, f, f, false, 1, mm / f};
       st[1] = {g.axis0, mm / f, mm / f, false, f, 1};
@@ -511,8 +522,10 @@ std::vector<InvGroup> plan_inverse(int d, const int* n, const int* m, int64_t ch
       s *= st[(size_t)i].nout;
       if (i == ns - 1 && slot < 16) s |= 1;
     }
-    P.col_stride = P.col_fast ? 1 : (int32_t)(s | 1);
-    g.lds = (size_t)(P.col_fast ? s * slot : (s | 1) * cols) * 16;
+    // (16 neighbouring lanes are in different columns only where a pass has fewer than 16 lines a column)
+    if (!P.col_fast && Mg < 16 * 8) s |= 1;
+    P.col_stride = P.col_fast ? 1 : (int32_t)s;
+    g.lds = (size_t)(P.col_fast ? s * slot : s * cols) * 16;
     P.n_pass = ns;
     // pass order: stage 0 first, the first axis' last stage last
     int own = 1;
