@@ -20,6 +20,8 @@
 // q = 2 rb + e mod P, e = 0 .. P/2 + 1, so every register index is a
 // compile-time constant.
 //
+// xengine_mfma_kernel (integer samples): the sums on the matrix cores, p <= q only, the y-axis transform fused in.
+//
 // xengine_kernel: a thread owns one cell kappa and a row block, its P + 2
 // complex float32 sums over the chunk's samples, then float64
 // read-modify-writes of S (the pair and, off the diagonal, its conjugate).

@@ -145,11 +145,10 @@ __device__ __forceinline__ void inv_any(const InvPass& p, const InvP& P, const C
 
 // WIDE: a pass of 11 or 13 values, which need the registers of four waves a SIMD.
 template <int SRC, bool WIDE>
-__global__ __launch_bounds__(512, WIDE ? 4 : 6) void inverse_group_kernel(const void* __restrict__ src, float2* __restrict__ dst,
-                                                            const double2* __restrict__ twi,
-                                                            const uint16_t* __restrict__ tab, int64_t columns,
-                                                            int64_t inner, double scale, InvP P,
-                                                            const uint16_t* __restrict__ pair_tab, int n_tiles) {
+__global__ __launch_bounds__(512, WIDE ? 4 : 6) void inverse_group_kernel(
+    const void* __restrict__ src, float2* __restrict__ dst, const double2* __restrict__ twi,
+    const uint16_t* __restrict__ tab, int64_t columns, int64_t inner, double scale, InvP P,
+    const uint16_t* __restrict__ pair_tab, int n_tiles) {
   extern __shared__ double2 W[];
   // consecutive column tiles on one XCD: where the columns are interleaved, tiles share cache lines
   int64_t blk = blockIdx.x;

@@ -5,8 +5,9 @@
 // work-group transforms a few (outer, inner) columns in LDS as complex float64 (stages as in lines.hpp, all plain: in
 // place, one thread a line); the first pass takes its lines straight from HBM, the last one writes the valid lags
 // straight to it.  The first axis' last stage comes last, so that neighbouring lines of that pass are neighbouring
-// lags of the inner axes.  The axes of a group need no round trip through HBM between them, and all their sums and intermediates are float64; only the values between
-// two groups are stored as complex float32.
+// lags of the inner axes.  The axes of a group need no round trip through HBM between them, and all their sums and
+// intermediates are float64; only the values between two groups are stored as complex float32.  Arrays beyond the
+// last-level cache take their axes of 8, 16 and 32 one by one instead, a thread a line (InvGroup::line).
 #pragma once
 
 #include <stddef.h>

@@ -459,7 +459,7 @@ std::vector<InvGroup> plan_inverse(int d, const int* n, const int* m, int64_t ch
     }
     // An array beyond the last-level cache (256 MB) goes through HBM with every pass: threads that transform a line
     // each in registers run at its rate, a group at half of it, so they win where their reads are whole cache lines.
-    if (inner == 1 && channels * all >= kLineCells && rest / m[k] >= 64 && (m[k] == 8 || m[k] == 16 || m[k] == 32)) {
+    if (inner == 1 && !whole && channels * all >= kLineCells && rest / m[k] >= 64 && (m[k] == 8 || m[k] == 16 || m[k] == 32)) {
       g.axes = 1;
       g.line = true;
       rest /= m[k];

@@ -287,7 +287,38 @@ static int check_inverse(const std::string& name, const std::vector<int>& n, int
   return 0;
 }
 
+// Arrays beyond the caches: one axis of 8, 16 or 32 at a time while whole cache lines lie behind it, every axis once;
+// a channel that fits one work-group stays one group however many there are (tile pairs are inverted in one launch).
+static int check_large_inverse() {
+  const std::string name = "large arrays";
+  const int off[8] = {};
+  for (const auto& n : std::vector<std::vector<int>>{{16, 16, 8, 8, 4, 4}, {4, 4, 8, 8, 4, 4}, {16, 16, 6, 5, 8, 8}, {128, 128}}) {
+    std::vector<int> m;
+    int64_t rest = 1;
+    for (int v : n) {
+      m.push_back(2 * v);
+      rest *= 2 * v;
+    }
+    int axis = 0;
+    for (const auto& g : omni::plan_inverse((int)n.size(), n.data(), m.data(), 4096, 1, off)) {
+      CHECK(g.axis0 == axis && !g.direct && (!g.line || g.axes == 1));
+      const int before = m[(size_t)axis];
+      for (int k = 0; k < g.axes; ++k) rest /= m[(size_t)axis++];
+      CHECK(g.line == (rest >= 64 && (before == 8 || before == 16 || before == 32)));
+    }
+    CHECK(axis == (int)n.size());
+  }
+  for (int x = 1; x <= 32; x *= 2)
+    for (int y = 1; y <= 32; y *= 2) {
+      const int n[2] = {x, y}, m[2] = {2 * x, 2 * y};
+      const auto g = omni::plan_inverse(2, n, m, int64_t(1) << 20, 1, off);
+      CHECK(g.size() == 1 && !g[0].line && !g[0].direct && g[0].axes == 2);
+    }
+  return 0;
+}
+
 int main() {
+  if (check_large_inverse()) return 1;
   std::string line;
   int done = 0, none = 0;
   while (std::getline(std::cin, line)) {
