@@ -163,7 +163,8 @@ struct ArrayPlan {
   int ct_index = -1;         // entry of the compile-time shape table (kernel 3)
   int lcap = 32;             // longest short DFT the general kernel may use (autotuned)
   int wg_target = 1024;      // work-groups the time slicing aims for (general and sliced kernels; autotuned)
-  int wg_most = 0, wg_samples = 0;  // sliced kernels: larger target while a slice keeps wg_samples samples (0: none)
+  int wg_most = 0, wg_samples = 0;  // sliced kernels: larger target while a slice keeps wg_samples samples (0: none),
+  int wg_round = 1;                 // in whole rounds of wg_round work-groups
   int tb = 0;                // float32 block of the sliced kernels (0: the plan's time_block; autotuned)
   double tuned_ms = 0.0;     // best candidate's time in the autotuner (0: not tuned)
   // front mode: the first n_front axes are transformed by front passes over HBM
@@ -265,15 +266,18 @@ bool sliced_kernel(int k) { return k == 1 || k == 2 || (k >= 6 && k <= 8); }
 // round.  128 x 128 and 64 x 64: one work-group a CU, two rounds (four rounds: 1.68 -> 1.62 and 0.46 -> 0.41 ms at
 // F = 64, T = 512; 64 x 64 at T = 2048 1.26 -> 1.24).  32 x 32: 256 threads and 12 KiB, five work-groups a CU, one
 // round, two while slices keep 24 samples (T = 512: 157 -> 153 us; T = 2048: 390 us, 400 with one).
+// The larger counts come in whole rounds of the work-groups that are resident at once (`round`), a last partial round
+// leaves CUs idle: 8x8x8x8 float32, 16 channels, T = 919: 1792 work-groups 624 us, two rounds of 768 604 us (the least
+// target alone 630); 32 x 32, 16 channels, T = 2048: 1312 work-groups 136 us, one round of 1280 128 us.
 struct WgTarget {
-  int least, most, samples;
+  int least, most, samples, round;
 };
 WgTarget default_wg_target(int k) {
   switch (k) {
-    case 1: return {1536, 6144, 64};
-    case 2: return {256, 256, 0};
-    case 8: return {1280, 2560, 24};
-    default: return {512, 512, 0};
+    case 1: return {1536, 6144, 64, 768};
+    case 2: return {256, 256, 0, 256};
+    case 8: return {1280, 2560, 24, 1280};
+    default: return {512, 512, 0, 256};
   }
 }
 
@@ -788,6 +792,7 @@ int build_array_core(ArrayPlan& ap, int levels, const int32_t* dims, const doubl
     ap.wg_target = t.least;
     ap.wg_most = t.most;
     ap.wg_samples = t.samples;
+    ap.wg_round = t.round;
   }
   const size_t per_slice = (size_t)ap.F * (size_t)ap.M * sizeof(double);
   ap.max_slices = (int)std::max<size_t>(1, std::min<size_t>(1024, kPartialBudget / per_slice));
@@ -1067,7 +1072,9 @@ int launch_sliced(omni_plan_s* p, ArrayPlan& ap, const void* volt, int64_t T, in
   const int64_t per_slice_groups = (int64_t)ap.F * (ap.kernel == 1 ? 8 : (ap.kernel == 2 || ap.kernel == 6) ? 2 : 1);
   int64_t ns = std::max<int64_t>(1, (target + per_slice_groups / 2) / per_slice_groups);
   if (target == ap.wg_target && ap.wg_most > target)
-    ns = std::max<int64_t>(ns, std::min<int64_t>(ap.wg_most / per_slice_groups, T / ap.wg_samples));
+    ns = std::max<int64_t>(
+        ns, std::min<int64_t>(ap.wg_most, T / ap.wg_samples * per_slice_groups) / ap.wg_round * ap.wg_round /
+                per_slice_groups);
   ns = std::min<int64_t>(ns, ap.max_slices);
   ns = std::min<int64_t>(ns, std::max<int64_t>(1, T / 8));
   const int64_t tps = (T + ns - 1) / ns;
