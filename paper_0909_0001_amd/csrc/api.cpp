@@ -2113,13 +2113,14 @@ struct omni_hybrid_s {
   omni_dtype dtype = OMNI_CF32;
   int64_t N = 0, mx = 0, my = 0, Mp = 0, chunk_T = 1;
   bool fused = false;              // the y-axis transform runs inside the pair stage (P m_y <= 512)
-  bool mfma = false;               // pair stage on the matrix cores (integer samples): d_S is [F][mx][my][P][P], p <= q
+  bool mfma = false;               // pair stage on the matrix cores (integer samples): d_S is [F][mx][my][pairs p <= q]
   float in_scale = 1.f;            // its power-of-two input scale
   std::vector<double> offsets, A;  // metadata for omni_hybrid_baselines (may be empty)
   float2* d_tw32 = nullptr;        // forward tables: w_mx^q then w_my^q (float32)
   double2* d_tw64 = nullptr;       // inverse tables (float64)
   float2* d_y[2] = {nullptr, nullptr};  // the two front passes' outputs for one chunk
   double2* d_S = nullptr;          // [F][P][P][mx][my] cross-power sums
+  int64_t s_values = 0;            // their number
   std::vector<omni::InvGroup> inv;  // the inverse's one group of axes
   uint16_t* d_inv_tab = nullptr;    // its offset table
   uint16_t* d_pairs = nullptr;      // matrix-core pair stage: p P + q of the pairs p <= q
@@ -2146,7 +2147,8 @@ int hybrid_alloc(omni_hybrid_s* h) {
   HIP_TRY(hipMalloc(&h->d_tw64, (size_t)(h->mx + h->my) * sizeof(double2)));
   HIP_TRY(hipMalloc(&h->d_y[0], (size_t)(tiles * h->P * h->mx * h->ny) * sizeof(float2)));
   if (!h->fused) HIP_TRY(hipMalloc(&h->d_y[1], (size_t)(tiles * h->P * h->Mp) * sizeof(float2)));
-  HIP_TRY(hipMalloc(&h->d_S, (size_t)(pairs * h->Mp) * sizeof(double2)));
+  h->s_values = (h->mfma ? (int64_t)h->F * h->P * (h->P + 1) / 2 : pairs) * h->Mp;
+  HIP_TRY(hipMalloc(&h->d_S, (size_t)h->s_values * sizeof(double2)));
   // both axes are powers of two of at most 64: one inverse group, no intermediate
   const int n2[2] = {h->nx, h->ny}, m2[2] = {(int)h->mx, (int)h->my}, off2[2] = {0, (int)h->mx};
   const int n_pairs = h->P * (h->P + 1) / 2;
@@ -2168,7 +2170,7 @@ int hybrid_alloc(omni_hybrid_s* h) {
   hipError_t e = hipMemcpy(d_desc, desc, sizeof(desc), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = omni::launch_twiddles(d_desc, 2, h->d_tw32, nullptr, 0);
   if (e == hipSuccess) e = omni::launch_twiddles(d_desc + 6, 2, nullptr, h->d_tw64, 0);
-  if (e == hipSuccess) e = omni::launch_fill_f64(reinterpret_cast<double*>(h->d_S), 2 * pairs * h->Mp, 0.0, 0);
+  if (e == hipSuccess) e = omni::launch_fill_f64(reinterpret_cast<double*>(h->d_S), 2 * h->s_values, 0.0, 0);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   hipFree(d_desc);
   if (e != hipSuccess) return fail(OMNI_E_HIP, std::string("hybrid plan setup: ") + hipGetErrorString(e));
@@ -2249,7 +2251,7 @@ int omni_hybrid_correlate(omni_hybrid_t h, const void* volt, int64_t T, void* vi
   const bool accumulate = (flags & OMNI_NO_RESET) != 0;
   const int64_t pairs = (int64_t)h->F * h->P * h->P;
   if (T == 0 && !accumulate)
-    HIP_TRY(omni::launch_fill_f64(reinterpret_cast<double*>(h->d_S), 2 * pairs * h->Mp, 0.0, st));
+    HIP_TRY(omni::launch_fill_f64(reinterpret_cast<double*>(h->d_S), 2 * h->s_values, 0.0, st));
   for (int64_t c0 = 0; c0 < T; c0 += h->chunk_T) {
     const int64_t tc = std::min<int64_t>(h->chunk_T, T - c0);
     const void* src = static_cast<const char*>(volt) + (size_t)(c0 * h->F * h->N) * sb;

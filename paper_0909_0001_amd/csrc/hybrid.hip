@@ -259,12 +259,13 @@ hipError_t launch_xf_ny(const float2* Y1, int64_t Tc, int F, int mx, int ny, con
 //          (16 bytes: 4 samples) meet every bank once;
 //   pairs  6 products a tile.
 // The staged lines and the operands share one 64 KiB LDS buffer: two work-groups a CU, whose phases overlap.  Float32
-// sums over the call's samples (at most 256), then float64 read-modify-writes of S[f][kappa][p][q], p <= q only.
+// sums over the call's samples (at most 256), then float64 read-modify-writes of S[f][kappa][pair], the pairs
+// p <= q row by row.
 //
 // What bounds it: the vector units' line transforms and splits (busy 51% of the time) and HBM (the lines are read
-// once, S read and written once a call: 1.4 GB), in phases that two work-groups a CU overlap only in part.  16 tiles
-// of 16x16, 64 channels, 256 samples (4-bit): 402 us a launch (335 us the first, which reads no S) against 640 us for
-// the vector-unit kernel above.  Reading the lines straight into the transforming thread's registers, without the
+// once, S read and written once a call: 1.35 GB), in phases that two work-groups a CU overlap only in part.  16 tiles
+// of 16x16, 64 channels, 256 samples (4-bit): 387 us a launch (325 us the first, which reads no S) against 640 us for
+// the vector-unit kernel above; with S as whole P x P matrices (half of each unused) 402 and 335 us.  Reading the lines straight into the transforming thread's registers, without the
 // stage in LDS, takes 499 us (a thread's 16-byte reads are then 256 KiB apart).
 // ---------------------------------------------------------------------------
 typedef _Float16 xe_half8 __attribute__((ext_vector_type(8)));
@@ -442,7 +443,7 @@ __global__ __launch_bounds__(kXeThreads, 2) void xengine_mfma_kernel(const float
         }
         if (p > q) continue;
         const int64_t kappa = (int64_t)(kx0 + cell / MY) * MY + cell % MY;
-        double2* sp = S + (((int64_t)f * Mp + kappa) * P + p) * P + q;
+        double2* sp = S + ((int64_t)f * Mp + kappa) * (P * (P + 1) / 2) + p * P - p * (p - 1) / 2 + (q - p);
         double2 o = make_double2((double)(re[k * PAIRS + q2][i] * out_scale), (double)(im[k * PAIRS + q2][i] * out_scale));
         if (accumulate) {
           const double2 old = *sp;

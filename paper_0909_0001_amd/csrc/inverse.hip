@@ -38,7 +38,7 @@ struct Ctx {
 
 // One pass' lines: FIRST reads them from HBM, otherwise from LDS; LAST writes the valid lags to HBM.
 // SRC: 0 = real float64, 1 = complex float32, 2 = complex float64, 3 = complex float64 of the tile pairs p <= q,
-// [channel][cell][p][q]: a column is one pair, written as C_pq[Delta] and as C_qp[-Delta] = conj C_pq[Delta].
+// [channel][cell][pair]: a column is one pair, written as C_pq[Delta] and as C_qp[-Delta] = conj C_pq[Delta].
 template <int N, int SRC, bool FIRST, bool LAST>
 __device__ __forceinline__ void inv_pass(const InvPass& p, const InvP& P, const Ctx& x) {
   const uint32_t jobs = (uint32_t)(p.lines * (P.col_fast ? P.cols : x.n_cols));
@@ -52,17 +52,7 @@ __device__ __forceinline__ void inv_pass(const InvPass& p, const InvP& P, const 
       line = q - c * p.lines;
     }
     double2 v[N];
-    if constexpr (FIRST && SRC == 3) {
-      const int64_t step = (int64_t)x.n_tiles * x.n_tiles;
-#pragma unroll
-      for (int j = 0; j < N; ++j) {
-        v[j] = make_double2(0.0, 0.0);
-        if (x.mine) {
-          const double2 t = static_cast<const double2*>(x.src)[x.src0 + (int64_t)(j * p.lines + line) * step];
-          v[j] = make_double2(t.y, t.x);
-        }
-      }
-    } else if constexpr (FIRST) {
+    if constexpr (FIRST) {
       const int64_t at = x.src0 + (P.col_fast ? (int64_t)line * x.inner : (int64_t)(c * P.Mg + line));
       const int64_t step = P.col_fast ? (int64_t)p.lines * x.inner : (int64_t)p.lines;
 #pragma unroll
@@ -157,15 +147,12 @@ __global__ __launch_bounds__(512, WIDE ? 4 : 6) void inverse_group_kernel(
   // interleaved columns: this thread's column is fixed (the thread count is a multiple of cols); whole columns: the
   // tile is one contiguous run
   const int64_t col = col0 + (threadIdx.x & (uint32_t)(P.cols - 1)), ou = P.col_fast ? col / inner : 0;
-  int64_t src0 = P.col_fast ? ou * P.Mg * inner + (col - ou * inner) : col0 * P.Mg;
-  if constexpr (SRC == 3)
-    src0 = col < columns ? ou * P.Mg * n_tiles * n_tiles + pair_tab[col - ou * inner] : 0;
   const Ctx x{W,
               twi,
               tab,
               src,
               dst,
-              src0,
+              P.col_fast ? ou * P.Mg * inner + (col - ou * inner) : col0 * P.Mg,
               P.col_fast ? ou * P.Ng * inner + (col - ou * inner) : col0 * P.Ng,
               inner,
               scale,
