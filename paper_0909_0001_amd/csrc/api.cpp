@@ -367,11 +367,24 @@ int plan_fused_axes(const std::vector<int>& n, int F, int tw_base, bool single_s
     split[0] = s0_force;
     n_split = s0_force;
   }
-  for (int p = 0; p < (single_split ? 1 : d) && fs.M / n_split > kCellsMax && s0_force == 0; ++p) {
-    const int k = order[p];
+  const auto divide = [&](int k) {  // axis k's residues among as many work-groups as the cells need
     while (fs.M / n_split > kCellsMax && m[k] % (2 * split[k]) == 0) {
       split[k] *= 2;
       n_split *= 2;
+    }
+  };
+  if (s0_force == 0) {
+    divide(0);
+    if (!single_split) {
+      // An axis between the first and the last keeps its n inputs in the LDS working array however few outputs are
+      // left of it: divided by two (m = 2 n outputs to n) it costs no more than those, a further division only repeats
+      // work.  So the middle axes once, then the last axis, then what is still needed.
+      for (int p = 1; p + 1 < d && fs.M / n_split > kCellsMax; ++p)
+        if (m[order[p]] == 2 * n[order[p]]) {
+          split[order[p]] *= 2;
+          n_split *= 2;
+        }
+      for (int p = d - 1; p >= 1; --p) divide(order[p]);
     }
   }
   if (fs.M / n_split > kCellsMax) {
@@ -393,12 +406,13 @@ int plan_fused_axes(const std::vector<int>& n, int F, int tw_base, bool single_s
     E[k] = R[k] * L[k];
   }
   const int last = order[d - 1];
-  // LDS layouts: W holds every axis but the last at its transformed extent; Pw holds all cells.
+  // LDS layouts: W holds every axis but the last at its transformed extent, or at its inputs' where the split leaves
+  // fewer outputs than those (an axis after the first is in W before its own pass); Pw holds all cells.
   std::vector<int64_t> w_str(d), p_str(d);
   int64_t ws = 1, pst = 1;
   for (int k = d - 1; k >= 0; --k) {
     w_str[k] = ws;
-    ws *= (k == last && d > 1) ? n[k] : E[k];
+    ws *= (k == last && d > 1) ? n[k] : k == order[0] ? E[k] : std::max(E[k], n[k]);
     p_str[k] = pst;
     pst *= E[k];
   }

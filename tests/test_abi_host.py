@@ -342,3 +342,12 @@ def test_log_level_controls_stderr():
     verbose = _run_with_log_level(2, _LOG_PROBE)
     plans = [ln for ln in verbose.stderr.splitlines() if ln.startswith("omniscope: plan {")]
     assert len(plans) == 1 and '"arrays"' in plans[0]
+
+
+def test_grid_beyond_every_working_set_is_refused():
+    """A grid whose first axis can neither be divided further nor be transformed by a front pass, and whose other axes'
+    inputs exceed the LDS working array, has no schedule: planning says so."""
+    with pytest.raises(omni.OmniError):
+        omni.Plan([[17, 17], [16, 16]], None, 1, "ci8", "fp32", host_only=True)
+    # the same tiles on a grid that leaves room for them
+    omni.Plan([[3, 16], [16, 16]], None, 1, "ci8", "fp32", host_only=True)

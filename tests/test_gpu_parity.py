@@ -996,3 +996,28 @@ def test_single_level_mixed_unaligned_and_sky():
     assert torch.equal(got, ref)
     x = oracle.decode(raw.cpu().numpy(), "ci4", 24, 64, w.N)
     check_cells(ref.cpu().numpy()[:4], x[:, :4], w.dims, "mixed", 256, 3, "grid128 sky")
+
+
+@pytest.mark.parametrize(
+    "level_dims,dtype,T,F",
+    [
+        ([[3, 19], [8, 8]], "ci8", 9, 2),  # a quarter of the innermost axis' outputs would be fewer than its inputs
+        ([[1, 3], [17, 2], [3, 8]], "cf32", 5, 1),  # every axis with an even length divided
+        ([[3, 17], [8, 5]], "ci4", 40, 1),  # the innermost axis divided into as many outputs as inputs
+    ],
+)
+def test_general_kernel_divided_inner_axes(level_dims, dtype, T, F):
+    """Grids of the runtime-shape kernel whose cells are divided among work-groups along several axes: an axis keeps
+    all its inputs in LDS however few of its outputs a work-group owns."""
+    import json
+
+    plan = omni.Plan(level_dims, None, F, dtype, "fp32")
+    a = json.loads(plan.describe())["arrays"][0]
+    assert a["kernel"] == "fused_fp32" and sum(x["split"] > 1 for x in a["axes"]) > 1
+    N = math.prod(dims_of(level_dims))
+    gen = torch.Generator().manual_seed(N)
+    raw = random_raw(dtype, T, F, N, gen)
+    say("divided inner axes", level_dims, [x["split"] for x in a["axes"]])
+    vis = plan.correlate(raw.cuda())
+    torch.cuda.synchronize()
+    assert rel_err(vis.cpu().numpy(), oracle_vis(raw, dtype, level_dims)) <= TOL["fp32"]
