@@ -76,8 +76,8 @@ bool xengine_fused_ok(int P, int ny);
 hipError_t launch_xengine_fused(const float2* Y1, int64_t Tc, int F, int P, int mx, int ny, const float2* twy,
                                 double2* S, int accumulate, hipStream_t st);
 bool xengine_mfma_ok(int P, int nx, int ny);
-hipError_t launch_xengine_mfma(const float2* Y1, int64_t Tc, int F, int P, int mx, int ny, float scale, double2* S,
-                               int accumulate, hipStream_t st);
+hipError_t launch_xengine_mfma(const float2* Y1, int64_t Tc, int F, int P, int mx, int ny, double2* S, int accumulate,
+                               hipStream_t st);
 hipError_t launch_even_cells(const double* A, double* E, int64_t rows, int na, int nb, int axes, hipStream_t st);
 }  // namespace omni
 
@@ -2128,7 +2128,6 @@ struct omni_hybrid_s {
   int64_t N = 0, mx = 0, my = 0, Mp = 0, chunk_T = 1;
   bool fused = false;              // the y-axis transform runs inside the pair stage (P m_y <= 512)
   bool mfma = false;               // pair stage on the matrix cores (integer samples): d_S is [F][mx][my][pairs p <= q]
-  float in_scale = 1.f;            // its power-of-two input scale
   std::vector<double> offsets, A;  // metadata for omni_hybrid_baselines (may be empty)
   float2* d_tw32 = nullptr;        // forward tables: w_mx^q then w_my^q (float32)
   double2* d_tw64 = nullptr;       // inverse tables (float64)
@@ -2226,13 +2225,9 @@ int omni_hybrid_plan(omni_hybrid_t* out, int32_t P, int32_t nx, int32_t ny, int3
     const int64_t rows = 512 / (P * h->my);
     h->fused = rows >= 1 && h->mx % rows == 0;
   }
-  // the matrix-core pair stage: integer samples (their size bounds the transforms: |Y| <= n_x n_y sqrt(2) max, scaled
-  // below 2^15), and the shapes its kernel takes
-  if (h->dtype != OMNI_CF32 && omni::xengine_mfma_ok(P, nx, ny)) {
-    h->mfma = true;
-    const double top = 1.4143 * (h->dtype == OMNI_CI8 ? 128.0 : 8.0) * nx * ny;
-    while (top * h->in_scale > 32768.0) h->in_scale *= 0.5f;
-  }
+  // the matrix-core pair stage, for integer samples and the shapes its kernel takes (float samples run the vector-unit
+  // kernels)
+  h->mfma = h->dtype != OMNI_CF32 && omni::xengine_mfma_ok(P, nx, ny);
   int rc = check_device(&h->device);
   if (rc) return rc;
   try {
@@ -2275,7 +2270,7 @@ int omni_hybrid_correlate(omni_hybrid_t h, const void* volt, int64_t T, void* vi
                                     1.f));
     const int acc = (accumulate || c0 > 0) ? 1 : 0;
     if (h->mfma) {
-      HIP_TRY(omni::launch_xengine_mfma(h->d_y[0], tc, h->F, h->P, (int)h->mx, h->ny, h->in_scale, h->d_S, acc, st));
+      HIP_TRY(omni::launch_xengine_mfma(h->d_y[0], tc, h->F, h->P, (int)h->mx, h->ny, h->d_S, acc, st));
       continue;
     }
     if (h->fused) {

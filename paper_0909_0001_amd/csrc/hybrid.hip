@@ -242,52 +242,36 @@ hipError_t launch_xf_ny(const float2* Y1, int64_t Tc, int F, int mx, int ny, con
 // ---------------------------------------------------------------------------
 // Pair stage on the matrix cores, for integer samples.
 //
-// Every Fourier cell's matrix S_pq = sum_t Y_p conj(Y_q) is a product with the time axis as the contraction.  The
-// float32 values are split into two float16 parts, Y = hi + lo (lo = rn16(Y - hi): the pair holds 22 bits, an error
-// of 2^-24 of the value), and hi hi + hi lo + lo hi is summed in float32 by v_mfma_f32_16x16x32_f16, K = 16 samples
-// x (re, im):
+// Every Fourier cell's matrix S_pq = sum_t Y_p conj(Y_q) is a product with the time axis as the contraction, in float32
+// throughout (v_mfma_f32_16x16x4_f32; K = samples x (re, im)):
 //   Re S_pq = sum (re_p, im_p) . (re_q, im_q),   Im S_pq = sum (re_p, im_p) . (-im_q, re_q).
-// Integer samples bound |Y| (a power-of-two input scale keeps it below 2^15), so float16's range is never left; float
-// samples run the vector-unit kernels above.
 //
 // A work-group of 4 waves owns R = 256 / (P n_y) rows kappa_x of one channel: R m_y P = 512 matrix rows in 32 tiles of
 // 16 (a cell's P tiles are consecutive rows: a 16-row tile holds 16 / P cells, or half a cell for P = 32), 8 tiles a
 // wave.  Per 16 samples:
 //   stage  the rows' lines Y1[t][p][kappa_x][i_y] arrive coalesced (prefetched into registers one batch ahead) in LDS;
-//   lines  a thread transforms a line (n_y -> 2 n_y, register transform) and writes hi and lo as float16 (re, im)
-//          pairs, [tile][row][sample], 16-byte chunks XOR-permuted so that these 4-byte writes and the operand reads
-//          (16 bytes: 4 samples) meet every bank once;
-//   pairs  6 products a tile.
+//   lines  a thread transforms a line (n_y -> 2 n_y, register transform) and writes its values [tile][row][sample],
+//          16-byte chunks (two samples) XOR-permuted by the row, so that the operand reads meet every bank once;
+//   pairs  16 products a tile.
 // The staged lines and the operands share one 64 KiB LDS buffer: two work-groups a CU, whose phases overlap.  Float32
 // sums over the call's samples (at most 256), then float64 read-modify-writes of S[f][kappa][pair], the pairs
 // p <= q row by row.
 //
-// What bounds it: the vector units' line transforms and splits (busy 51% of the time) and HBM (the lines are read
-// once, S read and written once a call: 1.35 GB), in phases that two work-groups a CU overlap only in part.  16 tiles
-// of 16x16, 64 channels, 256 samples (4-bit): 387 us a launch (325 us the first, which reads no S) against 640 us for
-// the vector-unit kernel above; with S as whole P x P matrices (half of each unused) 402 and 335 us.  Reading the lines straight into the transforming thread's registers, without the
-// stage in LDS, takes 499 us (a thread's 16-byte reads are then 256 KiB apart).
+// What bounds it: the float32 products (a 16x16x4 step takes 32 cycles: 220 us of matrix-core time at 2.4 GHz, 6 / 16 of
+// it for pairs p > q) beside the vector units' line transforms and HBM (the lines are read once, S read and written once
+// a call: 1.35 GB), in phases that two work-groups a CU overlap only in part.  16 tiles of 16x16, 64 channels, 256
+// samples (4-bit): 483 us a launch (440 us the first, which reads no S) against 640 us for the vector-unit kernel
+// above.  Float16 operands in two parts of 11 bits (hi hi + hi lo + lo hi) took 387 us a launch and lost 3.7e-8 of
+// every zero lag (the product of the low parts) and up to 2^-23 of every value: the largest error of a pair grew from
+// 0.7e-7 - 1.4e-7 to 1.4e-7 - 2.1e-7 of its power, which is why the operands are float32.
 // ---------------------------------------------------------------------------
-typedef _Float16 xe_half8 __attribute__((ext_vector_type(8)));
-typedef _Float16 xe_half2 __attribute__((ext_vector_type(2)));
 typedef float xe_float4 __attribute__((ext_vector_type(4)));
 
 constexpr int kXmSamples = 16;  // samples per matrix product
 
-// (re, im) pairs -> (-im, re)
-__device__ __forceinline__ xe_half8 xe_rotate(xe_half8 v) {
-  uint4 u = __builtin_bit_cast(uint4, v);
-  u.x = __builtin_amdgcn_alignbit(u.x, u.x, 16) ^ 0x8000u;
-  u.y = __builtin_amdgcn_alignbit(u.y, u.y, 16) ^ 0x8000u;
-  u.z = __builtin_amdgcn_alignbit(u.z, u.z, 16) ^ 0x8000u;
-  u.w = __builtin_amdgcn_alignbit(u.w, u.w, 16) ^ 0x8000u;
-  return __builtin_bit_cast(xe_half8, u);
-}
-
 template <int P, int NY>
 __global__ __launch_bounds__(kXeThreads, 2) void xengine_mfma_kernel(const float2* __restrict__ Y1, int Tc, int F,
-                                                                     int mx, float in_scale, float out_scale,
-                                                                     double2* __restrict__ S, int accumulate) {
+                                                                     int mx, double2* __restrict__ S, int accumulate) {
   constexpr int MY = 2 * NY;
   constexpr int R = kXeThreads / (P * NY);        // rows kappa_x
   constexpr int SLOTS = R * P;                    // lines per sample
@@ -299,9 +283,9 @@ __global__ __launch_bounds__(kXeThreads, 2) void xengine_mfma_kernel(const float
   constexpr int PAIRS = GR == 2 ? 3 : 1;          // tile products per cell (of GR tiles)
   constexpr int ACC = WT / GR * PAIRS;
   static_assert(R * P * NY == kXeThreads && PER >= 1 && NY >= 4 && R * MY * P == 16 * TILES, "geometry");
-  __shared__ uint4 buf[2 * TILES * 16 * 4];  // operands: [hi, lo][tile][row][4 chunks]; staged lines alias the start
-  uint4* const stage = buf;                  // [line][CH], 2048 pieces
-  uint32_t* const words = reinterpret_cast<uint32_t*>(buf);
+  __shared__ float4 buf[TILES * 16 * 8];  // operands: [tile][row][8 chunks of 2 samples]; staged lines alias the start
+  float4* const stage = buf;              // [line][CH], 2048 pieces
+  float2* const words = reinterpret_cast<float2*>(buf);
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int f = blockIdx.y, kx0 = blockIdx.x * R;
 
@@ -338,7 +322,7 @@ __global__ __launch_bounds__(kXeThreads, 2) void xengine_mfma_kernel(const float
 #pragma unroll
     for (int u = 0; u < LOADS; ++u) {
       const int line = (pr * kXmSamples + pt + 2 * u) * P + pp;
-      stage[line * CH + (pc ^ ((line >> SH) & (CH - 1)))] = __builtin_bit_cast(uint4, pf[u]);
+      stage[line * CH + (pc ^ ((line >> SH) & (CH - 1)))] = pf[u];
     }
     __syncthreads();
     float2 x[PER][NY];
@@ -347,16 +331,10 @@ __global__ __launch_bounds__(kXeThreads, 2) void xengine_mfma_kernel(const float
       const int line = k * kXeThreads + tid;
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
-        const float4 v = __builtin_bit_cast(float4, stage[line * CH + (c ^ ((line >> SH) & (CH - 1)))]);
+        const float4 v = stage[line * CH + (c ^ ((line >> SH) & (CH - 1)))];
         x[k][2 * c] = make_float2(v.x, v.y);
         x[k][2 * c + 1] = make_float2(v.z, v.w);
       }
-    }
-    if (in_scale != 1.f) {
-#pragma unroll
-      for (int k = 0; k < PER; ++k)
-#pragma unroll
-        for (int j = 0; j < NY; ++j) x[k][j] = make_float2(x[k][j].x * in_scale, x[k][j].y * in_scale);
     }
     if (t0 + kXmSamples < Tc) fetch(t0 + kXmSamples);
     __syncthreads();
@@ -366,15 +344,7 @@ __global__ __launch_bounds__(kXeThreads, 2) void xengine_mfma_kernel(const float
       const int p = line % P, t = line / P % kXmSamples, r = line / (P * kXmSamples);
       auto put = [&](int ky, float2 v) __attribute__((always_inline)) {
         const int g = (r * MY + ky) * P + p, tile = g >> 4, row = g & 15;
-        const int at = (tile * 16 + row) * 16 + ((t >> 2) ^ (row >> 2)) * 4 + (t & 3);
-        const xe_half2 h = {(_Float16)v.x, (_Float16)v.y};
-        const uint32_t hb = __builtin_bit_cast(uint32_t, h);
-        float lx, ly;  // v - hi, exact (one mixed-precision FMA each instead of a conversion and a subtraction)
-        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(lx) : "v"(hb), "v"(v.x));
-        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(ly) : "v"(hb), "v"(v.y));
-        const xe_half2 l = {(_Float16)lx, (_Float16)ly};
-        words[at] = hb;
-        words[TILES * 256 + at] = __builtin_bit_cast(uint32_t, l);
+        words[((tile * 16 + row) * 8 + ((t >> 1) ^ (row & 7))) * 2 + (t & 1)] = v;
       };
       float2 z[NY];
 #pragma unroll
@@ -391,28 +361,26 @@ __global__ __launch_bounds__(kXeThreads, 2) void xengine_mfma_kernel(const float
     __syncthreads();
     {
       const int row = lane & 15, kb = lane >> 4;
-      const int at = row * 4 + (kb ^ (row >> 2));
 #pragma unroll
       for (int k = 0; k < WT / GR; ++k) {
-        xe_half8 h[GR], l[GR];
 #pragma unroll
-        for (int g = 0; g < GR; ++g) {
-          const int tile = (wave * WT + k * GR + g) * 64;
-          h[g] = __builtin_bit_cast(xe_half8, buf[tile + at]);
-          l[g] = __builtin_bit_cast(xe_half8, buf[TILES * 64 + tile + at]);
-        }
+        for (int half = 0; half < 2; ++half) {
+          // lane (row, kb): samples 8 half + 2 kb and the next one, a product step for each of the four values
+          xe_float4 v[GR];
 #pragma unroll
-        for (int q = 0; q < PAIRS; ++q) {
-          const int a = q == 2 ? 1 : 0, b = q == 0 ? 0 : GR - 1;  // (0,0), (0,1), (1,1)
-          xe_float4& cr = re[k * PAIRS + q];
-          xe_float4& ci = im[k * PAIRS + q];
-          cr = __builtin_amdgcn_mfma_f32_16x16x32_f16(h[a], h[b], cr, 0, 0, 0);
-          cr = __builtin_amdgcn_mfma_f32_16x16x32_f16(h[a], l[b], cr, 0, 0, 0);
-          cr = __builtin_amdgcn_mfma_f32_16x16x32_f16(l[a], h[b], cr, 0, 0, 0);
-          const xe_half8 hb = xe_rotate(h[b]), lb = xe_rotate(l[b]);
-          ci = __builtin_amdgcn_mfma_f32_16x16x32_f16(h[a], hb, ci, 0, 0, 0);
-          ci = __builtin_amdgcn_mfma_f32_16x16x32_f16(h[a], lb, ci, 0, 0, 0);
-          ci = __builtin_amdgcn_mfma_f32_16x16x32_f16(l[a], hb, ci, 0, 0, 0);
+          for (int g = 0; g < GR; ++g)
+            v[g] = __builtin_bit_cast(xe_float4, buf[((wave * WT + k * GR + g) * 16 + row) * 8 + ((4 * half + kb) ^ (row & 7))]);
+#pragma unroll
+          for (int q = 0; q < PAIRS; ++q) {
+            const int a = q == 2 ? 1 : 0, b = q == 0 ? 0 : GR - 1;  // (0,0), (0,1), (1,1)
+            xe_float4& cr = re[k * PAIRS + q];
+            xe_float4& ci = im[k * PAIRS + q];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              cr = __builtin_amdgcn_mfma_f32_16x16x4f32(v[a][j], v[b][j], cr, 0, 0, 0);
+              ci = __builtin_amdgcn_mfma_f32_16x16x4f32(v[a][j], j & 1 ? v[b][j - 1] : -v[b][j + 1], ci, 0, 0, 0);
+            }
+          }
         }
       }
     }
@@ -444,7 +412,7 @@ __global__ __launch_bounds__(kXeThreads, 2) void xengine_mfma_kernel(const float
         if (p > q) continue;
         const int64_t kappa = (int64_t)(kx0 + cell / MY) * MY + cell % MY;
         double2* sp = S + ((int64_t)f * Mp + kappa) * (P * (P + 1) / 2) + p * P - p * (p - 1) / 2 + (q - p);
-        double2 o = make_double2((double)(re[k * PAIRS + q2][i] * out_scale), (double)(im[k * PAIRS + q2][i] * out_scale));
+        double2 o = make_double2((double)re[k * PAIRS + q2][i], (double)im[k * PAIRS + q2][i]);
         if (accumulate) {
           const double2 old = *sp;
           o.x += old.x;
@@ -457,8 +425,7 @@ __global__ __launch_bounds__(kXeThreads, 2) void xengine_mfma_kernel(const float
 }
 
 template <int P, int NY>
-hipError_t launch_xm(const float2* Y1, int64_t Tc, int F, int mx, float scale, double2* S, int accumulate,
-                     hipStream_t st) {
+hipError_t launch_xm(const float2* Y1, int64_t Tc, int F, int mx, double2* S, int accumulate, hipStream_t st) {
   if constexpr (P * NY > kXeThreads) {
     return hipErrorInvalidValue;
   } else {
@@ -467,18 +434,18 @@ hipError_t launch_xm(const float2* Y1, int64_t Tc, int F, int mx, float scale, d
         (reinterpret_cast<uintptr_t>(Y1) & 15) != 0)
       return hipErrorInvalidValue;
     hipLaunchKernelGGL((xengine_mfma_kernel<P, NY>), dim3((unsigned)(mx / R), (unsigned)F), dim3(kXeThreads), 0, st, Y1,
-                       (int)Tc, F, mx, scale, 1.f / (scale * scale), S, accumulate);
+                       (int)Tc, F, mx, S, accumulate);
     return hipGetLastError();
   }
 }
 
 template <int P>
-hipError_t launch_xm_ny(const float2* Y1, int64_t Tc, int F, int mx, int ny, float scale, double2* S, int accumulate,
+hipError_t launch_xm_ny(const float2* Y1, int64_t Tc, int F, int mx, int ny, double2* S, int accumulate,
                         hipStream_t st) {
   switch (ny) {
-    case 4: return launch_xm<P, 4>(Y1, Tc, F, mx, scale, S, accumulate, st);
-    case 8: return launch_xm<P, 8>(Y1, Tc, F, mx, scale, S, accumulate, st);
-    case 16: return launch_xm<P, 16>(Y1, Tc, F, mx, scale, S, accumulate, st);
+    case 4: return launch_xm<P, 4>(Y1, Tc, F, mx, S, accumulate, st);
+    case 8: return launch_xm<P, 8>(Y1, Tc, F, mx, S, accumulate, st);
+    case 16: return launch_xm<P, 16>(Y1, Tc, F, mx, S, accumulate, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -519,13 +486,13 @@ bool xengine_mfma_ok(int P, int nx, int ny) {
   return 2 * nx % (kXeThreads / (P * ny)) == 0 && 4 * nx * ny <= 1024;
 }
 
-hipError_t launch_xengine_mfma(const float2* Y1, int64_t Tc, int F, int P, int mx, int ny, float scale, double2* S,
-                               int accumulate, hipStream_t st) {
+hipError_t launch_xengine_mfma(const float2* Y1, int64_t Tc, int F, int P, int mx, int ny, double2* S, int accumulate,
+                               hipStream_t st) {
   switch (P) {
-    case 4: return launch_xm_ny<4>(Y1, Tc, F, mx, ny, scale, S, accumulate, st);
-    case 8: return launch_xm_ny<8>(Y1, Tc, F, mx, ny, scale, S, accumulate, st);
-    case 16: return launch_xm_ny<16>(Y1, Tc, F, mx, ny, scale, S, accumulate, st);
-    case 32: return launch_xm_ny<32>(Y1, Tc, F, mx, ny, scale, S, accumulate, st);
+    case 4: return launch_xm_ny<4>(Y1, Tc, F, mx, ny, S, accumulate, st);
+    case 8: return launch_xm_ny<8>(Y1, Tc, F, mx, ny, S, accumulate, st);
+    case 16: return launch_xm_ny<16>(Y1, Tc, F, mx, ny, S, accumulate, st);
+    case 32: return launch_xm_ny<32>(Y1, Tc, F, mx, ny, S, accumulate, st);
     default: return hipErrorInvalidValue;
   }
 }
