@@ -195,10 +195,12 @@ int omni_correlate(omni_plan_t plan, const void* volt, int64_t T, void* vis, voi
  * n_arrays device pointers, read during the call only.
  * Without OMNI_PLAN_GRAPH the arrays run one after another on `stream`.  With
  * it, the plan captures its first call (all arrays, all stages) into one HIP
- * graph in which each array is a branch on a stream of its own; the forward
- * stages follow one another (each fills the GPU by itself), the largest array
- * first, and an array's reduction and inverse overlap the next one's forward
- * stage; the graph is launched on `stream` and every later call replays it.  Later calls must
+ * graph in which each array is a branch on a stream of its own, the largest
+ * array first: an array's forward stage follows that of an earlier array that
+ * fills the GPU by itself or is over sooner than a parallel branch pays, and
+ * starts beside the others'; an array's reduction and inverse overlap the next
+ * one's forward stage.  The graph is launched on `stream` and every later call
+ * replays it.  Later calls must
  * repeat the first call's T, flags and volt / vis pointers (the buffers'
  * contents may change): any other call returns OMNI_E_STATE (make another
  * plan for another call shape).  Results are identical to the sequential

@@ -180,6 +180,9 @@ struct ArrayPlan {
   int n_tw = 0;
   int max_slices = 1;
   int last_slices = 1;
+  // the last forward launch: its work-groups, how many run at once, and the cells x samples of one of them
+  int64_t fwd_groups = 0, fwd_slots = 256, fwd_span = 0;
+  int waits_for = -1;        // graph plans: the array whose forward stage this one's follows (-1: none)
   int inv_group = 1;         // channels per inverse-transform group
   std::vector<omni::InvGroup> inv;  // groups of axes of the inverse (made with the device resources)
   // device resources
@@ -1039,6 +1042,9 @@ int launch_general(ArrayPlan& ap, const FusedSetup& fs, int fmt, const void* src
     L.xcd_groups = (ns * fs.F) % 8 == 0 ? 1 : 0;
     if (ns * per > INT32_MAX) return fail(OMNI_E_SHAPE, "grid too large");
     *slices = (int)ns;
+    ap.fwd_groups = ns * per;
+    ap.fwd_slots = slots;
+    ap.fwd_span = tps * L.cells;
     HIP_TRY(omni::launch_lines_fp32(src, T, tps, tw, ap.d_ltab, ap.d_partial, L, (int)(ns * per), fs.ls.threads,
                                     fs.ls.lds, st));
     return OMNI_OK;
@@ -1057,6 +1063,8 @@ int launch_general(ArrayPlan& ap, const FusedSetup& fs, int fmt, const void* src
   const int64_t grid = groups * P.n_split;
   if (grid > INT32_MAX) return fail(OMNI_E_SHAPE, "grid too large");
   *slices = (int)ns;
+  ap.fwd_groups = grid;
+  ap.fwd_span = tps * P.cells_wg;
   HIP_TRY(omni::launch_fused_fp32(fmt, fs.cpt, src, T, tps, tw, ap.d_partial, P, (int)grid, fs.lds, st));
   return OMNI_OK;
 }
@@ -1074,6 +1082,8 @@ int launch_ct(ArrayPlan& ap, int fmt, const void* src, int64_t T, int time_block
   ns = (T + tps - 1) / tps;
   if (ns * per_slice_groups > INT32_MAX) return fail(OMNI_E_SHAPE, "grid too large");
   *slices = (int)ns;
+  ap.fwd_groups = ns * per_slice_groups;
+  ap.fwd_span = tps * ap.fs.fp.cells_wg;
   HIP_TRY(omni::launch_fused_ct(ap.ct_index, fmt, src, T, tps, tw, ap.d_partial, ap.fs.F, (int)ns, time_block,
                                 accumulate, st));
   return OMNI_OK;
@@ -1094,6 +1104,9 @@ int launch_sliced(omni_plan_s* p, ArrayPlan& ap, const void* volt, int64_t T, in
   const int64_t tps = (T + ns - 1) / ns;
   ns = (T + tps - 1) / tps;
   *slices = (int)ns;
+  ap.fwd_groups = ns * per_slice_groups;
+  ap.fwd_slots = ap.wg_round;
+  ap.fwd_span = tps * ap.fs.fp.cells_wg;
   const int fmt = fmt_of(p->dtype);
   switch (ap.kernel) {
     case 1:
@@ -1167,6 +1180,8 @@ int correlate_array(omni_plan_s* p, ArrayPlan& ap, const void* volt, int64_t T, 
                                              p->time_block, c0 > 0 ? 1 : 0, unscale * unscale, st));
         kmark(p, 1, st);
         first_slices = 1;
+        ap.fwd_groups = ap.fs.F;
+        ap.fwd_span = tc * ap.fs.fp.cells_wg;
         continue;
       }
       if (ap.kernel == 5) {
@@ -1178,6 +1193,8 @@ int correlate_array(omni_plan_s* p, ArrayPlan& ap, const void* volt, int64_t T, 
                                              c0 > 0 ? 1 : 0, unscale * unscale, st));
         kmark(p, 1, st);
         first_slices = 1;
+        ap.fwd_groups = ap.fs.F;
+        ap.fwd_span = tc * ap.fs.fp.cells_wg;
         continue;
       }
       if (ap.kernel == 3) {
@@ -1491,10 +1508,17 @@ void destroy_plan_resources(omni_plan_s* p) {
 }
 
 // Capture one correlate call of a graph plan: the fork event on the capture stream, each array's three stages on its
-// branch stream, the joins back.  The forward stages follow one another, the largest array first: each fills the GPU
-// by itself (one work-group a CU for the larger matrix-core kernels), and two of them at once take turns on the CUs
-// and leave uneven ends (32 x 32, 64 x 64 and 128 x 128, 64 channels, T = 2048: 8.93 ms with free branches,
-// 7.19 ms in order).  An array's reduction and inverse overlap the next one's forward stage.
+// branch stream, the joins back, the largest array first.  An array's forward stage follows the last one before it that
+//   - fills the GPU by itself: two of those at once take turns on the CUs and leave uneven ends (32 x 32, 64 x 64 and
+//     128 x 128, 64 channels, T = 2048: 8.4 ms with free branches, 6.95 ms in order); or
+//   - is over sooner than a branch pays: parallel branches cost a graph about 20 us, a work-group of less than 2^16
+//     cells x samples on the matrix cores, of less than 2^15 in float32, runs for less (four arrays: 16 x 16, 4
+//     channels, T = 1024: 120 us in order, 128 free; 32 x 32 mixed, 1 channel, T = 256: 116 and 137; 32 x 32 float32,
+//     2 channels, T = 256: 125 and 140).
+// Behind the others the next array starts at once (four arrays: 64 x 64, 2 channels, T = 512: 192 us in order, 142
+// free; 128 x 128, 1 channel, T = 128: 296 and 146; 64 x 64 float32, 2 channels, T = 128: 179 and 150; three of
+// 8x8x8x8 float32, 4 channels, T = 128: 149 and 127).  An array's reduction and inverse always overlap the next one's
+// forward stage.
 int capture_call(omni_plan_s* p, const void* const* volt, int64_t T, void* const* vis, uint32_t flags) {
   drop_graph(p);
   std::vector<size_t> order(p->arrays.size());
@@ -1505,14 +1529,19 @@ int capture_call(omni_plan_s* p, const void* const* volt, int64_t T, void* const
   HIP_TRY(hipStreamBeginCapture(p->capture, hipStreamCaptureModeThreadLocal));
   int rc = OMNI_OK;
   hipError_t e = hipEventRecord(p->fork, p->capture);
+  int after = -1;
   for (size_t k = 0; k < order.size() && rc == OMNI_OK && e == hipSuccess; ++k) {
     const size_t i = order[k];
-    e = hipStreamWaitEvent(p->branch[i], k == 0 ? p->fork : p->fwd[order[k - 1]], 0);
+    ArrayPlan& ap = p->arrays[i];
+    ap.waits_for = after;
+    e = hipStreamWaitEvent(p->branch[i], after < 0 ? p->fork : p->fwd[(size_t)after], 0);
     for (int stage = 0; stage < 3 && rc == OMNI_OK && e == hipSuccess; ++stage) {
-      rc = correlate_array(p, p->arrays[i], T > 0 ? volt[i] : nullptr, T,
+      rc = correlate_array(p, ap, T > 0 ? volt[i] : nullptr, T,
                            (flags & OMNI_NO_FINALIZE) ? nullptr : vis[i], p->branch[i], flags, stage);
       if (stage == 0 && rc == OMNI_OK) e = hipEventRecord(p->fwd[i], p->branch[i]);
     }
+    const bool matrix = ap.kernel == 2 || ap.kernel >= 4;
+    if (ap.fwd_groups >= ap.fwd_slots || ap.fwd_span < (matrix ? 1 << 16 : 1 << 15)) after = (int)i;
     if (rc == OMNI_OK && e == hipSuccess) e = hipEventRecord(p->join[i], p->branch[i]);
     if (rc == OMNI_OK && e == hipSuccess) e = hipStreamWaitEvent(p->capture, p->join[i], 0);
   }
@@ -2004,7 +2033,7 @@ int omni_plan_describe(omni_plan_t plan, char* buf, size_t len, size_t* needed) 
          ",\"inverse_group\":" + std::to_string(ap.inv_group) + ",\"lcap\":" + std::to_string(ap.lcap) +
          ",\"wg_target\":" + std::to_string(ap.wg_target) +
          ",\"block\":" + std::to_string(ap.tb > 0 ? ap.tb : plan->time_block) +
-         ",\"tuned_ms\":" + std::to_string(ap.tuned_ms) +
+         ",\"tuned_ms\":" + std::to_string(ap.tuned_ms) + ",\"waits_for\":" + std::to_string(ap.waits_for) +
          ",\"axes\":[";
     for (int k = 0; k < P.d; ++k) {
       const AxisP& a = P.ax[k];

@@ -1021,3 +1021,34 @@ def test_general_kernel_divided_inner_axes(level_dims, dtype, T, F):
     vis = plan.correlate(raw.cuda())
     torch.cuda.synchronize()
     assert rel_err(vis.cpu().numpy(), oracle_vis(raw, dtype, level_dims)) <= TOL["fp32"]
+
+
+@pytest.mark.parametrize(
+    "batch,form,T,waits",
+    [
+        # 64 work-groups each, long ones: side by side
+        ([([[64, 64]], 1), ([[64, 64]], 1), ([[64, 64]], 1)], "mixed", 512, [-1, -1, -1]),
+        ([([[8, 8], [8, 8]], 4), ([[8, 8], [8, 8]], 4)], "fp32", 128, [-1, -1]),
+        # 512 work-groups each fill the GPU: in order
+        ([([[64, 64]], 16), ([[64, 64]], 16)], "mixed", 256, [-1, 0]),
+        # few and short work-groups: in order
+        ([([[16, 16]], 1), ([[32, 32]], 1)], "mixed", 64, [1, -1]),
+        # behind an array that fills the GPU, two that do not run side by side
+        ([([[64, 64]], 1), ([[128, 128]], 32), ([[64, 64]], 1)], "mixed", 128, [1, -1, 1]),
+    ],
+)
+def test_graph_orders_only_forward_stages_that_gain(batch, form, T, waits):
+    """Which forward stages of a graph plan follow another one, and that every order gives the sequential bytes."""
+    import json
+
+    batch = [(ld, None, F) for ld, F in batch]
+    gen = torch.Generator().manual_seed(11)
+    raws = [random_raw("ci4", T, F, math.prod(dims_of(ld)), gen).cuda() for ld, _, F in batch]
+    say("graph order", [b[0] for b in batch])
+    gp = omni.Plan(batch=batch, dtype="ci4", form=form, graph=True)
+    want = [o.clone() for o in omni.Plan(batch=batch, dtype="ci4", form=form).correlate_batch(raws)]
+    for _ in range(3):
+        got = gp.correlate_batch(raws)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+    assert [a["waits_for"] for a in json.loads(gp.describe())["arrays"]] == waits
