@@ -1319,8 +1319,8 @@ int tune_sliced(omni_plan_s* p, ArrayPlan& ap) {
   int c_tb = 0, c_wg = 0;
   if (p->tune == OMNI_TUNE_CACHE && tune_cache_lookup(p->tune_cache, key, &c_tb, &c_wg) && c_tb > 0 && c_wg > 0) {
     ap.tb = c_tb;
+    if (c_wg != ap.wg_target) ap.wg_most = 0;  // the stored target as it is; the default one stands for its policy
     ap.wg_target = c_wg;
-    ap.wg_most = 0;  // the stored target as it is
     log_msg(2, "autotuner: %s -> block %d, work-group target %d (from the cache)", key.c_str(), c_tb, c_wg);
     return OMNI_OK;
   }
@@ -1331,9 +1331,10 @@ int tune_sliced(omni_plan_s* p, ArrayPlan& ap) {
     tbs = {256, 1024};
   else
     tbs = {p->time_block};
+  // the default target stands for the default policy (launch_sliced), the others are tried as they are
   std::vector<int> wgs = {256, 512, 1024, 2048, 4096};
-  if (std::find(wgs.begin(), wgs.end(), ap.wg_target) == wgs.end()) wgs.push_back(ap.wg_target);
-  ap.wg_most = 0;  // the search tries targets as they are
+  for (int wg : {ap.wg_target, ap.wg_most})
+    if (wg > 0 && std::find(wgs.begin(), wgs.end(), wg) == wgs.end()) wgs.push_back(wg);
   void* zero = nullptr;
   HIP_TRY(hipMalloc(&zero, bytes_t * (size_t)Tt));
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1368,6 +1369,7 @@ int tune_sliced(omni_plan_s* p, ArrayPlan& ap) {
   if (rc) return rc;
   if (he != hipSuccess) return fail(OMNI_E_HIP, std::string("autotuner: ") + hipGetErrorString(he));
   ap.tb = best_tb;
+  if (best_wg != ap.wg_target) ap.wg_most = 0;
   ap.wg_target = best_wg;
   ap.tuned_ms = best;
   tune_cache_store(p->tune_cache, key, best_tb, best_wg, best);
@@ -2031,7 +2033,7 @@ int omni_plan_describe(omni_plan_t plan, char* buf, size_t len, size_t* needed) 
          ",\"cells_wg\":" + std::to_string(P.cells_wg) + ",\"cells_per_thread\":" + std::to_string(ap.fs.cpt) +
          ",\"lds_bytes\":" + std::to_string(ap.fs.lds) + ",\"max_slices\":" + std::to_string(ap.max_slices) +
          ",\"inverse_group\":" + std::to_string(ap.inv_group) + ",\"lcap\":" + std::to_string(ap.lcap) +
-         ",\"wg_target\":" + std::to_string(ap.wg_target) +
+         ",\"wg_target\":" + std::to_string(ap.wg_target) + ",\"slices\":" + std::to_string(ap.last_slices) +
          ",\"block\":" + std::to_string(ap.tb > 0 ? ap.tb : plan->time_block) +
          ",\"tuned_ms\":" + std::to_string(ap.tuned_ms) + ",\"waits_for\":" + std::to_string(ap.waits_for) +
          ",\"axes\":[";

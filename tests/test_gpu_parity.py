@@ -1052,3 +1052,30 @@ def test_graph_orders_only_forward_stages_that_gain(batch, form, T, waits):
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(got, want))
     assert [a["waits_for"] for a in json.loads(gp.describe())["arrays"]] == waits
+
+
+def test_tuned_schedule_may_be_the_default_policy(tmp_path):
+    """The default time slicing of a fixed-shape kernel (a least target, a larger one for long calls) is among the
+    autotuner's candidates: its target in the cache file stands for the whole policy, other targets for themselves."""
+    import json
+
+    level_dims, F, T = [[8, 8], [8, 8]], 16, 2000
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    raw = torch.randint(-100, 101, (T, F, 4096, 2), generator=gen, device="cuda", dtype=torch.int16).to(torch.int8)
+
+    def slices(**kw):
+        plan = omni.Plan(level_dims, None, F, "ci8", "fp32", **kw)
+        plan.correlate(raw)
+        torch.cuda.synchronize()
+        return json.loads(plan.describe())["arrays"][0]["slices"]
+
+    cache = tmp_path / "tune.txt"
+    omni.Plan(level_dims, None, F, "ci8", "fp32", tune="search", tune_cache=str(cache))
+    key = cache.read_text().split()[0]
+    want = slices()
+    least = json.loads(omni.Plan(level_dims, None, F, "ci8", "fp32", host_only=True).describe())["arrays"][0]["wg_target"]
+    assert want * 8 * F > least  # long slices: more than the least target
+    cache.write_text(f"{key} 64 {least} 1.0\n")
+    assert slices(tune="cache", tune_cache=str(cache)) == want
+    cache.write_text(f"{key} 64 512 1.0\n")
+    assert slices(tune="cache", tune_cache=str(cache)) == 512 // (8 * F)
