@@ -166,6 +166,7 @@ struct ArrayPlan {
   int wg_most = 0, wg_samples = 0;  // sliced kernels: larger target while a slice keeps wg_samples samples (0: none),
   int wg_round = 1;                 // in whole rounds of wg_round work-groups
   int tb = 0;                // float32 block of the sliced kernels (0: the plan's time_block; autotuned)
+  int line_wg = 0;           // line kernel: work-groups the tuned slicing aims for (0: launch_general's own count)
   double tuned_ms = 0.0;     // best candidate's time in the autotuner (0: not tuned)
   // front mode: the first n_front axes are transformed by front passes over HBM
   int n_front = 0;
@@ -1030,7 +1031,8 @@ int launch_general(ArrayPlan& ap, const FusedSetup& fs, int fmt, const void* src
                                            std::max<int64_t>(1, 4 * (int64_t)ap.wg_target / per));
     double best = 1e300;
     int64_t ns = 1;
-    for (int64_t k = 1; k <= most; ++k) {
+    if (ap.line_wg > 0) ns = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(batches, ap.max_slices), ap.line_wg / per));
+    for (int64_t k = 1; ap.line_wg == 0 && k <= most; ++k) {
       const double cost = (double)((k * per + slots - 1) / slots) * ((double)((batches + k - 1) / k) + 1.5);
       if (cost < best) {
         best = cost;
@@ -1276,6 +1278,7 @@ std::string tune_key(const ArrayPlan& ap, omni_dtype dtype) {
   std::string k = "gfx950:";
   for (int v : ap.n) k += std::to_string(v) + "x";
   k += ":F" + std::to_string(ap.F) + ":t" + std::to_string((int)dtype) + ":k" + std::to_string(ap.kernel);
+  if (ap.fs.lines) k += "l";  // (the runtime-shape kernel's schedules are not the line kernel's)
   return k;
 }
 
@@ -1381,7 +1384,7 @@ int tune_sliced(omni_plan_s* p, ArrayPlan& ap) {
 int tune_array(omni_plan_s* p, ArrayPlan& ap) {
   if (sliced_kernel(ap.kernel)) return tune_sliced(p, ap);
   if (ap.kernel != 0 && ap.kernel != 3) return OMNI_OK;
-  const bool ct = ap.kernel == 3 || ap.fs.lines;  // fixed transforms: only the time slicing is tuned
+  const bool lines = ap.fs.lines, ct = ap.kernel == 3 || lines;  // fixed transforms: only the time slicing is tuned
   const std::string key = tune_key(ap, p->dtype);
   int lc = 0, wg = 0;
   const bool cached = p->tune == OMNI_TUNE_CACHE && tune_cache_lookup(p->tune_cache, key, &lc, &wg);
@@ -1403,9 +1406,10 @@ int tune_array(omni_plan_s* p, ArrayPlan& ap) {
   FusedSetup best_fs;
   int best_lc = ap.lcap, best_wg = ap.wg_target;
   const int lcaps[3] = {8, 16, 32};
-  const int wgts[3] = {512, 1024, 2048};
+  std::vector<int> wgts = {512, 1024, 2048};
+  if (lines) wgts = {0, 256, 512, 1024, 2048};  // 0: the count that launch_general finds best
   for (int li = 0; li < 3; ++li) {
-    for (int wi = 0; wi < 3; ++wi) {
+    for (size_t wi = 0; wi < wgts.size(); ++wi) {
       if (cached && (lcaps[li] != lc || wgts[wi] != wg)) continue;
       if (ct && lcaps[li] != ap.lcap) continue;
       FusedSetup fs;
@@ -1416,8 +1420,9 @@ int tune_array(omni_plan_s* p, ArrayPlan& ap) {
                                  ap.m.data() + ap.n_front)) {
         continue;
       }
-      const int keep_wg = ap.wg_target;
-      ap.wg_target = wgts[wi];
+      int& target = lines ? ap.line_wg : ap.wg_target;
+      const int keep_wg = target;
+      target = wgts[wi];
       float ms = 0.f;
       int slices = 1;
       int rc = OMNI_OK;
@@ -1429,8 +1434,8 @@ int tune_array(omni_plan_s* p, ArrayPlan& ap) {
         HIP_TRY(hipEventSynchronize(e1));
         HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
       }
-      ap.wg_target = keep_wg;
-      if (rc == OMNI_OK && ms < best) {
+      target = keep_wg;
+      if (rc == OMNI_OK && ms < (lines ? 0.97 : 1.0) * best) {  // (a target has to beat the kernel's own count by more than noise)
         best = ms;
         best_fs = std::move(fs);
         best_lc = lcaps[li];
@@ -1444,7 +1449,7 @@ int tune_array(omni_plan_s* p, ArrayPlan& ap) {
   if (best < 1e30) {
     ap.fs = std::move(best_fs);
     ap.lcap = best_lc;
-    ap.wg_target = best_wg;
+    (lines ? ap.line_wg : ap.wg_target) = best_wg;
     ap.tuned_ms = best;
     HIP_TRY(hipMemcpy(ap.d_kmap, ap.fs.kmap.data(), ap.fs.kmap.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     if (!cached) tune_cache_store(p->tune_cache, key, best_lc, best_wg, best);
@@ -2033,7 +2038,8 @@ int omni_plan_describe(omni_plan_t plan, char* buf, size_t len, size_t* needed) 
          ",\"cells_wg\":" + std::to_string(P.cells_wg) + ",\"cells_per_thread\":" + std::to_string(ap.fs.cpt) +
          ",\"lds_bytes\":" + std::to_string(ap.fs.lds) + ",\"max_slices\":" + std::to_string(ap.max_slices) +
          ",\"inverse_group\":" + std::to_string(ap.inv_group) + ",\"lcap\":" + std::to_string(ap.lcap) +
-         ",\"wg_target\":" + std::to_string(ap.wg_target) + ",\"slices\":" + std::to_string(ap.last_slices) +
+         ",\"wg_target\":" + std::to_string(ap.line_wg > 0 ? ap.line_wg : ap.wg_target) +
+         ",\"slices\":" + std::to_string(ap.last_slices) +
          ",\"block\":" + std::to_string(ap.tb > 0 ? ap.tb : plan->time_block) +
          ",\"tuned_ms\":" + std::to_string(ap.tuned_ms) + ",\"waits_for\":" + std::to_string(ap.waits_for) +
          ",\"axes\":[";

@@ -1079,3 +1079,34 @@ def test_tuned_schedule_may_be_the_default_policy(tmp_path):
     assert slices(tune="cache", tune_cache=str(cache)) == want
     cache.write_text(f"{key} 64 512 1.0\n")
     assert slices(tune="cache", tune_cache=str(cache)) == 512 // (8 * F)
+
+
+def test_autotuner_reaches_the_line_kernels_slices(tmp_path):
+    """A tuned work-group target of the general (line) kernel sets its slices, 0 stands for the kernel's own count, and
+    a schedule stored for the runtime-shape kernel of the same grid is not taken."""
+    import json
+
+    level_dims, F, T = [[16, 32]], 4, 500
+    gen = torch.Generator().manual_seed(13)
+    raw = random_raw("ci8", T, F, 512, gen).cuda()
+
+    def slices(**kw):
+        plan = omni.Plan(level_dims, None, F, "ci8", "fp32", **kw)
+        vis = plan.correlate(raw)
+        torch.cuda.synchronize()
+        return json.loads(plan.describe())["arrays"][0]["slices"], vis
+
+    cache = tmp_path / "tune.txt"
+    cache.write_text("gfx950:16x32x:F4:t1:k0 32 512 0.0001\n")  # a schedule of the runtime-shape kernel
+    own, ref = slices()
+    slices(tune="cache", tune_cache=str(cache))
+    lines = cache.read_text().split("\n")
+    assert len(lines) == 3 and lines[1].split()[0] != lines[0].split()[0]  # searched, stored beside it
+    key, lcap = lines[1].split()[:2]
+    for target in (0, 256, 1024):
+        cache.write_text(f"{key} {lcap} {target} 1.0\n")
+        got, vis = slices(tune="cache", tune_cache=str(cache))
+        say("line kernel target", target, got)
+        # (whole batches a slice: a few slices fewer than aimed for)
+        assert got == own if target == 0 else target // F // 2 < got <= target // F
+        assert rel_err(vis.cpu().numpy(), ref.cpu().numpy()) <= 1e-6
