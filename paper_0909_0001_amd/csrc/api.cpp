@@ -32,6 +32,7 @@ hipError_t launch_reduce_scatter(const double* partial, const int32_t* kmap, dou
 hipError_t launch_fill_f64(double* p, int64_t n, double v, hipStream_t st);
 hipError_t launch_inverse_axis(bool real_in, bool last, const void* src, void* dst, const double2* twi,
                                int64_t outer, int m, int n, int64_t inner, double scale, hipStream_t st);
+bool inverse_axis_tiled(int m, int64_t columns);
 hipError_t launch_inverse_group(int src_kind, const void* src, void* dst, const double2* twi, const uint16_t* tab,
                                 int64_t outer, int64_t inner, double scale, const InvP& P, size_t lds, hipStream_t st,
                                 const uint16_t* pair_tab = nullptr, int n_tiles = 0);
@@ -2029,7 +2030,20 @@ int omni_plan_describe(omni_plan_t plan, char* buf, size_t len, size_t* needed) 
                         : ap.kernel == 7 ? "grid64_mixed"
                         : ap.kernel == 8 ? "grid32_mixed"
                                          : "fused_fp32";
-    s += std::string("{\"kernel\":\"") + kname + "\",\"beams\":\"" +
+    // what the inverse's plain sums take: none (groups of axes, lines), tiles of columns in LDS, or one thread a lag
+    const char* inverse = "groups";
+    int64_t columns = ap.inv_group;  // (as run_inverse counts them)
+    for (const auto& g : ap.inv) {
+      int64_t inner = 1;
+      for (size_t k = (size_t)(g.axis0 + g.axes); k < ap.n.size(); ++k)
+        inner *= (int)k < (int)ap.n.size() - ap.nbeam ? ap.m[k] : ap.n[k];
+      if (g.direct)
+        inverse = omni::inverse_axis_tiled(ap.m[(size_t)g.axis0], columns * inner) ? "tiled" : "untiled";
+      for (int k = g.axis0; k < g.axis0 + g.axes; ++k) columns *= 2 * ap.n[(size_t)k] - 1;
+    }
+    s += std::string("{\"kernel\":\"") + kname + "\",\"schedule\":\"" +
+         (ap.kernel != 0 ? "fixed" : ap.fs.lines ? "lines" : "runtime") + "\",\"inverse\":\"" + inverse +
+         "\",\"beams\":\"" +
          (ap.beams ? (ap.beam_sub ? "subset" : "unpadded") : "no") + "\",\"mode\":\"" +
          (ap.n_front ? "front" : "direct") +
          "\",\"n_front\":" + std::to_string(ap.n_front) + ",\"chunk_T\":" + std::to_string(ap.chunk_T) +
