@@ -193,3 +193,30 @@ def test_hybrid_zero_lags_are_unbiased():
     bias = float(((got.real.astype(np.float64) - want) / want).mean())
     say(f"[hybrid] mean error of the zero lags {bias:.3g}")
     assert abs(bias) < 2e-8
+
+
+FLOAT_CASES = [
+    (4, 8, 4, 9, 2),
+    (4, 4, 16, 300, 1),  # two chunks of samples
+    (8, 4, 8, 17, 2),
+    (16, 2, 16, 33, 1),
+    (16, 8, 4, 5, 2),
+    (32, 4, 8, 12, 1),
+    (32, 2, 16, 7, 1),  # P n_y above 256: separate y-axis pass
+]
+
+
+@pytest.mark.parametrize("P,nx,ny,T,F", FLOAT_CASES)
+def test_hybrid_float_samples(P, nx, ny, T, F):
+    """Float samples keep the vector-unit pair stage at the shapes where integer samples use the matrix cores."""
+    N = P * nx * ny
+    gen = torch.Generator().manual_seed(N + 7 * T)
+    raw = random_raw("cf32", T, F, N, gen)
+    say(f"[hybrid float] case P={P} {nx}x{ny} T={T} F={F}")
+    h = omni.Hybrid(P, nx, ny, F, "cf32")
+    vis = h.correlate(raw.cuda())
+    torch.cuda.synchronize()
+    x = oracle.decode(raw.numpy(), "cf32", T, F, N)
+    err = pair_err(vis.cpu().numpy(), hybrid.tile_cross_correlations(x, P, nx, ny), nx, ny)
+    say(f"[hybrid float] P={P} {nx}x{ny}: err {err:.3g}")
+    assert err <= 1e-5
