@@ -479,29 +479,36 @@ int plan_fused_axes(const std::vector<int>& n, int F, int tw_base, bool single_s
     *why = "LDS working set exceeds 160 KiB";
     return OMNI_E_SHAPE;
   }
-  // Cell -> natural frequency index (row-major over these axes), for every split residue.
+  fs.kmap.clear();
+  return OMNI_OK;
+}
+
+// Cell -> natural frequency index (row-major over the kernel's axes), for every split residue: for the kernels that
+// run plan_fused_axes' schedule (the others have cell orders of their own).
+void fill_kmap(FusedSetup& fs) {
+  const FusedP& P = fs.fp;
   fs.kmap.assign((size_t)fs.M, 0);
-  std::vector<int64_t> nat_str(d);
+  std::vector<int64_t> nat_str(P.d);
   int64_t sst = 1;
-  for (int k = d - 1; k >= 0; --k) {
+  for (int k = P.d - 1; k >= 0; --k) {
     nat_str[k] = sst;
-    sst *= m[k];
+    sst *= P.ax[k].m;
   }
-  for (int c = 0; c < n_split; ++c) {
-    for (int64_t cell = 0; cell < cells; ++cell) {
+  for (int c = 0; c < P.n_split; ++c) {
+    for (int64_t cell = 0; cell < P.cells_wg; ++cell) {
       int64_t rem = cell, nat = 0;
-      for (int k = d - 1; k >= 0; --k) {
-        const int pos = (int)(rem % E[k]);
-        rem /= E[k];
-        const int i = pos / L[k], q = pos % L[k];
-        const int rho = (int)((c / split_div[k]) % split[k]) + i * step[k];
-        const int kappa = r[k] * q + rho;
+      for (int k = P.d - 1; k >= 0; --k) {
+        const AxisP& a = P.ax[k];
+        const int pos = (int)(rem % a.E);
+        rem /= a.E;
+        const int i = pos / a.L, q = pos % a.L;
+        const int rho = (c / a.split_div) % a.split + i * a.rho_step;
+        const int kappa = a.r * q + rho;
         nat += kappa * nat_str[k];
       }
-      fs.kmap[(size_t)(c * cells + cell)] = (int32_t)nat;
+      fs.kmap[(size_t)(c * (int64_t)P.cells_wg + cell)] = (int32_t)nat;
     }
   }
-  return OMNI_OK;
 }
 
 // Bytes of the two front workspaces for the plan's chunk: front pass k writes d_y[k % 2] (complex float32,
@@ -562,6 +569,7 @@ void plan_fused8x4(ArrayPlan& ap) {
   FusedP& P = ap.fs.fp;
   P.n_split = 8;
   P.cells_wg = 8192;
+  ap.fs.kmap.assign((size_t)ap.M, 0);
   ap.fs.cpt = 32;
   auto kap = [](int p) { return 2 * (p & 7) + (p >> 3); };
   for (int c = 0; c < 8; ++c) {
@@ -587,6 +595,7 @@ void plan_fused8x4_mixed(ArrayPlan& ap) {
   FusedP& P = ap.fs.fp;
   P.n_split = 2;
   P.cells_wg = 32768;
+  ap.fs.kmap.assign((size_t)ap.M, 0);
   ap.fs.cpt = 32;
   ap.fs.lds = 114688;
   for (int h = 0; h < 2; ++h) {
@@ -643,7 +652,10 @@ void plan_grid_small(ArrayPlan& ap, int kernel) {
 void plan_general(ArrayPlan& ap) {
   FusedSetup& fs = ap.fs;
   const int s = ap.n_front, d = (int)ap.n.size() - s;
-  if (!omni::plan_lines(d, ap.n.data() + s, ap.m.data() + s, 64, fs.ls)) return;
+  if (!omni::plan_lines(d, ap.n.data() + s, ap.m.data() + s, omni::kLineMaxBatch, fs.ls)) {
+    fill_kmap(fs);
+    return;
+  }
   fs.lines = true;
   fs.kmap = std::move(fs.ls.kmap);
   fs.fp.n_split = fs.ls.P.n_split;
@@ -769,7 +781,6 @@ int build_array_core(ArrayPlan& ap, int levels, const int32_t* dims, const doubl
   }
   // the fixed-shape kernels all assume zero-padded axes: a beam-space plan keeps the general kernel
   if (ap.nbeam > 0) {
-    plan_general(ap);
     ap.max_slices = (int)std::max<size_t>(1, std::min<size_t>(1024, kPartialBudget / ((size_t)ap.F * ap.M * 8)));
     ap.inv_group = (int)std::max<int64_t>(1, std::min<int64_t>(ap.F, (int64_t(1) << 30) / (ap.M * 8)));
     return OMNI_OK;
@@ -805,7 +816,7 @@ int build_array_core(ArrayPlan& ap, int levels, const int32_t* dims, const doubl
     plan_grid_small(ap, 7);
   if (form == OMNI_FORM_MIXED && dtype == OMNI_CI4 && ap.n_front == 0 && ap.n == std::vector<int>{32, 32})
     plan_grid_small(ap, 8);
-  if (ap.kernel == 0) plan_general(ap);
+  if (ap.kernel == 3) fill_kmap(ap.fs);
   if (sliced_kernel(ap.kernel)) {
     const WgTarget t = default_wg_target(ap.kernel);
     ap.wg_target = t.least;
@@ -827,7 +838,11 @@ int build_array_core(ArrayPlan& ap, int levels, const int32_t* dims, const doubl
 // axes; otherwise the general kernel transforms those axes without padding (a quarter of the cells).
 int build_array(ArrayPlan& ap, int levels, const int32_t* dims, const double* A, int32_t nchan, omni_form form,
                 omni_dtype dtype, bool beams) {
-  if (!beams) return build_array_core(ap, levels, dims, A, nchan, form, dtype, false);
+  const auto finish = [&](int rc) {  // the general kernel's schedule, once the route is known
+    if (rc == OMNI_OK && ap.kernel == 0) plan_general(ap);
+    return rc;
+  };
+  if (!beams) return finish(build_array_core(ap, levels, dims, A, nchan, form, dtype, false));
   if (levels < 2 || levels > omni::kMaxD / 2)
     return fail(OMNI_E_SHAPE, "a beam-space plan needs at least one level above the blocks");
   if (!dims) return fail(OMNI_E_INVAL, "dims is NULL");
@@ -848,7 +863,7 @@ int build_array(ArrayPlan& ap, int levels, const int32_t* dims, const double* A,
   }
   ap = ArrayPlan();
   ap.chunk_cap = cap;
-  rc = build_array_core(ap, levels, dims, A, nchan, form, dtype, true);
+  rc = finish(build_array_core(ap, levels, dims, A, nchan, form, dtype, true));
   ap.beams = true;
   return rc;
 }
@@ -1420,6 +1435,8 @@ int tune_array(omni_plan_s* p, ArrayPlan& ap) {
       } else if (plan_fused_axes(axes, Fk, 0, front ? true : ap.single_split, lcaps[li], fs, &why, nullptr, 0,
                                  ap.m.data() + ap.n_front)) {
         continue;
+      } else {
+        fill_kmap(fs);
       }
       int& target = lines ? ap.line_wg : ap.wg_target;
       const int keep_wg = target;

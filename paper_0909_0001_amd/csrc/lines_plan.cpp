@@ -12,7 +12,6 @@ namespace omni {
 namespace {
 
 constexpr size_t kLds = 160 * 1024;
-constexpr int kMaxBatch = 16;
 
 struct Stage {
   int axis;
@@ -249,69 +248,69 @@ bool plan_lines(int d, const int* n, const int* m, int max_batch, LineSetup& out
     for (const Stage& s : st) twiddled = twiddled || s.rem > 1;
     const Stage s0 = st[0];
     for (const bool pairs : {false, true}) {
-    const Layout L = make_layout(st, S, pairs);
-    if (L.order.empty()) continue;
-    bool small = true;  // eight waves a SIMD instead of four
-    for (const Unit& u : L.order) small = small && line_type_small(unit_type(st, u));
-    const int64_t n_tw = (twiddled || S > 1) && tw_all <= 1024 ? tw_all : 0;
-    const int64_t load_lines = N / s0.nin, k_out = s0.nout / S;
-    for (int NT = 256; NT <= 1024; NT *= 2) {
-      for (int B = 1; B <= std::min(kMaxBatch, std::max(1, max_batch)); B *= 2) {
-        const int Gmax = (int)std::max<int64_t>(1, std::min<int64_t>(B, NT / L.lines.back()));
-        for (int G = Gmax; G >= 1; G = G > 1 ? G / 2 : 0) {
-        const size_t lds = (size_t)(B * L.w_size * 8 + n_tw * 8 + G * L.cells * 4 + L.tab * 2);
-        if (lds > kLds) continue;
-        if (B * N >= 65536 && S == 1) continue;
-        if (S > 1 && B * load_lines * k_out >= 65536) continue;
-        bool ok = L.w_size < 65536;
-        double issue = 0, chain = 0;  // vector instructions of the work-group's waves; of its longest wave, with waits
-        auto add = [&](int64_t jobs, double instr) {
-          ok = ok && jobs < 65536;
-          issue += std::ceil(jobs / 64.0) * instr;
-          chain += std::ceil((double)jobs / NT) * instr * 3.7 + 990.0;
-        };
-        if (S == 1)
-          add(B * N, 12.0);
-        else
-          add(B * load_lines * k_out, 40.0 + 24.0 * s0.nin);  // direct sums with a load from HBM for every input
-        for (size_t p = 0; p < L.order.size(); ++p) {
-          const Unit& u = L.order[p];
-          const Stage& a = st[(size_t)u.a];
-          int nout = a.nout;
-          double instr = line_cost(a.nout) + (a.rem > 1 ? 8.0 * a.nout : 0.0);
-          if (u.b >= 0) {
-            const Stage& b = st[(size_t)u.b];
-            nout *= b.nout;
-            instr = 20.0 + a.nin * (line_cost(b.nout) - 20.0) + b.nout * (line_cost(a.nout) - 20.0);
-          }
-          if (p + 1 == L.order.size()) {
-            ok = ok && G * L.lines[p] < 65536;
-            const double each = std::ceil((double)B / G);
-            issue += std::ceil(G * L.lines[p] / 64.0) * (instr * each + 4.0 * nout);
-            chain += std::ceil((double)G * L.lines[p] / NT) *
-                         ((instr * each + 4.0 * nout) * 3.7 + (each - 1.0) * (u.b >= 0 ? 500.0 : 250.0)) +
-                     990.0;
-          } else {
-            add(B * L.lines[p], instr);
-          }
-        }
-        if (!ok) continue;
-        const double fit = std::max(1.0, std::min(std::floor((double)kLds / (double)lds), (small ? 2048.0 : 1024.0) / NT));
-        const double cost = (double)S / B * (1.12 * issue + chain / fit);
-        if (cost < best * 0.98) {
-          best = cost;
-          bS = S;
-          bB = B;
-          bNT = NT;
-          bG = G;
-          bfit = (int)fit;
-          bL = L;
-          bst = st;
-          bTw = twiddled || S > 1;
-        }
+      const Layout L = make_layout(st, S, pairs);
+      if (L.order.empty()) continue;
+      bool small = true;  // eight waves a SIMD instead of four
+      for (const Unit& u : L.order) small = small && line_type_small(unit_type(st, u));
+      const int64_t n_tw = (twiddled || S > 1) && tw_all <= 1024 ? tw_all : 0;
+      const int64_t load_lines = N / s0.nin, k_out = s0.nout / S;
+      std::vector<double> instr;  // vector instructions of a line of each pass
+      double last_sums = 0, last_wait = 0;
+      for (const Unit& u : L.order) {
+        const Stage& a = st[(size_t)u.a];
+        const double one = line_cost(a.nout);
+        instr.push_back(one + (a.rem > 1 ? 8.0 * a.nout : 0.0));
+        last_sums = 4.0 * a.nout;
+        last_wait = 250.0;
+        if (u.b >= 0) {
+          const Stage& b = st[(size_t)u.b];
+          instr.back() = 20.0 + a.nin * (line_cost(b.nout) - 20.0) + b.nout * (one - 20.0);
+          last_sums *= b.nout;
+          last_wait = 500.0;
         }
       }
-    }
+      for (int NT = 256; NT <= 1024; NT *= 2) {
+        for (int B = 1; B <= std::min(kLineMaxBatch, std::max(1, max_batch)); B *= 2) {
+          const int Gmax = (int)std::max<int64_t>(1, std::min<int64_t>(B, NT / L.lines.back()));
+          for (int G = Gmax; G >= 1; G = G > 1 ? G / 2 : 0) {
+            const size_t lds = (size_t)(B * L.w_size * 8 + n_tw * 8 + G * L.cells * 4 + L.tab * 2);
+            if (lds > kLds) continue;
+            if (B * N >= 65536 && S == 1) continue;
+            if (S > 1 && B * load_lines * k_out >= 65536) continue;
+            bool ok = L.w_size < 65536;
+            double issue = 0, chain = 0;  // vector instructions of the work-group's waves; of its longest wave, with waits
+            auto add = [&](int64_t jobs, double instr) {
+              ok = ok && jobs < 65536;
+              issue += std::ceil(jobs / 64.0) * instr;
+              chain += std::ceil((double)jobs / NT) * instr * 3.7 + 990.0;
+            };
+            if (S == 1)
+              add(B * N, 12.0);
+            else
+              add(B * load_lines * k_out, 40.0 + 24.0 * s0.nin);  // direct sums with a load from HBM for every input
+            for (size_t p = 0; p + 1 < L.order.size(); ++p) add(B * L.lines[p], instr[p]);
+            const int64_t jobs = G * L.lines.back();
+            ok = ok && jobs < 65536;
+            const double each = std::ceil((double)B / G), last = instr.back() * each + last_sums;
+            issue += std::ceil(jobs / 64.0) * last;
+            chain += std::ceil((double)jobs / NT) * (last * 3.7 + (each - 1.0) * last_wait) + 990.0;
+            if (!ok) continue;
+            const double fit = std::max(1.0, std::min(std::floor((double)kLds / (double)lds), (small ? 2048.0 : 1024.0) / NT));
+            const double cost = (double)S / B * (1.12 * issue + chain / fit);
+            if (cost < best * 0.98) {
+              best = cost;
+              bS = S;
+              bB = B;
+              bNT = NT;
+              bG = G;
+              bfit = (int)fit;
+              bL = L;
+              bst = st;
+              bTw = twiddled || S > 1;
+            }
+          }
+        }
+      }
     }
   }
   if (!bS) return false;

@@ -9,6 +9,8 @@
 
 namespace omni {
 
+constexpr int kLineMaxBatch = 16;  // samples transformed together at most
+
 struct LineSetup {
   LineP P{};                  // F, fmt, time_block and xcd_groups are set by the launch
   std::vector<uint16_t> tab;  // the passes' line offsets and twiddle steps
