@@ -61,9 +61,4 @@ constexpr int kLinePlain[] = {2, 3, 4, 5, 6, 7, 8, 11, 13, 16};
 // Pairs of zero-padded axes that are one pass, n1 >= n2.
 constexpr bool line_pair_ok(int n1, int n2) { return n1 >= n2 && n2 >= 2 && n1 <= 8 && n1 * n2 <= 16; }
 
-// Types whose transforms need at most 64 registers: a schedule of these only runs eight waves a SIMD instead of four.
-constexpr bool line_type_small(int type) {
-  return type >= 256 ? (type - 256) / 16 * (type & 15) <= 6 || type == 256 + 51 || type == 256 + 66 : (type & 31) <= 8;
-}
-
 }  // namespace omni

@@ -14,8 +14,10 @@
 // chain of divisions per job and sample.  A pass costs about 1000 cycles of waiting (table, line, barrier) besides its
 // instructions, which is why short axes are transformed two by two (n1 n2 values a thread): 5x3 / 3x3 / 3x3, 12
 // channels, T = 333: 635 -> 410 us, 2x2 / 16x16, 16 channels, T = 250: 130 -> 70 us, together with one round of
-// work-groups instead of a fixed count.  Vector units issue 30 to 40% of the cycles; more waves a SIMD alone (eight
-// instead of four) did not change the time, so the planner weighs work-groups per CU only through that waiting.
+// work-groups instead of a fixed count.  Vector units issue 30 to 40% of the cycles.  Eight waves a SIMD instead of four
+// (64 registers, for schedules of short transforms only) made most grids slower, for the schedules that the planner then
+// chose: 36x18, 8 channels, T = 500: 59 us for 46; 15x6, 32 channels, T = 1500: 45 for 38; 5x3/3x3/3x3: 418 for 400;
+// at best 126 for 135 (5x8/7x7, 8 channels, T = 200).
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -196,53 +198,47 @@ __device__ __forceinline__ void last_pass2(const LinePass p, const Ctx& c) {
   }
 }
 
-// Every type; the ones that need at most 64 registers (`SMALL` kernel: eight waves a SIMD) first.
-#define OMNI_LINE_TYPES(PASS, PASS2)                     \
-  switch (p.type) {                                      \
-    case 32 + 1: PASS(1, true);                          \
-    case 32 + 2: PASS(2, true);                          \
-    case 32 + 3: PASS(3, true);                          \
-    case 32 + 4: PASS(4, true);                          \
-    case 32 + 5: PASS(5, true);                          \
-    case 32 + 6: PASS(6, true);                          \
-    case 32 + 7: PASS(7, true);                          \
-    case 32 + 8: PASS(8, true);                          \
-    case 2: PASS(2, false);                              \
-    case 3: PASS(3, false);                              \
-    case 4: PASS(4, false);                              \
-    case 5: PASS(5, false);                              \
-    case 6: PASS(6, false);                              \
-    case 7: PASS(7, false);                              \
-    case 8: PASS(8, false);                              \
-    case 256 + 34: PASS2(2, 2);                          \
-    case 256 + 50: PASS2(3, 2);                          \
-    case 256 + 66: PASS2(4, 2);                          \
-    case 256 + 51: PASS2(3, 3);                          \
-    default:                                             \
-      if constexpr (!SMALL) {                            \
-        switch (p.type) {                                \
-          case 32 + 9: PASS(9, true);                    \
-          case 32 + 10: PASS(10, true);                  \
-          case 32 + 11: PASS(11, true);                  \
-          case 32 + 12: PASS(12, true);                  \
-          case 32 + 13: PASS(13, true);                  \
-          case 32 + 16: PASS(16, true);                  \
-          case 11: PASS(11, false);                      \
-          case 13: PASS(13, false);                      \
-          case 16: PASS(16, false);                      \
-          case 256 + 82: PASS2(5, 2);                    \
-          case 256 + 98: PASS2(6, 2);                    \
-          case 256 + 114: PASS2(7, 2);                   \
-          case 256 + 130: PASS2(8, 2);                   \
-          case 256 + 67: PASS2(4, 3);                    \
-          case 256 + 83: PASS2(5, 3);                    \
-          case 256 + 68: PASS2(4, 4);                    \
-          default: break;                                \
-        }                                                \
-      }                                                  \
+// Every type.
+#define OMNI_LINE_TYPES(PASS, PASS2) \
+  switch (p.type) {                  \
+    case 32 + 1: PASS(1, true);      \
+    case 32 + 2: PASS(2, true);      \
+    case 32 + 3: PASS(3, true);      \
+    case 32 + 4: PASS(4, true);      \
+    case 32 + 5: PASS(5, true);      \
+    case 32 + 6: PASS(6, true);      \
+    case 32 + 7: PASS(7, true);      \
+    case 32 + 8: PASS(8, true);      \
+    case 32 + 9: PASS(9, true);      \
+    case 32 + 10: PASS(10, true);    \
+    case 32 + 11: PASS(11, true);    \
+    case 32 + 12: PASS(12, true);    \
+    case 32 + 13: PASS(13, true);    \
+    case 32 + 16: PASS(16, true);    \
+    case 2: PASS(2, false);          \
+    case 3: PASS(3, false);          \
+    case 4: PASS(4, false);          \
+    case 5: PASS(5, false);          \
+    case 6: PASS(6, false);          \
+    case 7: PASS(7, false);          \
+    case 8: PASS(8, false);          \
+    case 11: PASS(11, false);        \
+    case 13: PASS(13, false);        \
+    case 16: PASS(16, false);        \
+    case 256 + 34: PASS2(2, 2);      \
+    case 256 + 50: PASS2(3, 2);      \
+    case 256 + 66: PASS2(4, 2);      \
+    case 256 + 51: PASS2(3, 3);      \
+    case 256 + 82: PASS2(5, 2);      \
+    case 256 + 98: PASS2(6, 2);      \
+    case 256 + 114: PASS2(7, 2);     \
+    case 256 + 130: PASS2(8, 2);     \
+    case 256 + 67: PASS2(4, 3);      \
+    case 256 + 83: PASS2(5, 3);      \
+    case 256 + 68: PASS2(4, 4);      \
+    default: break;                  \
   }
 
-template <bool SMALL>
 __device__ __forceinline__ void run_mid(const LinePass p, const Ctx& c) {
 #define OMNI_MID(N_, PAD_)  \
   mid_pass<N_, PAD_>(p, c); \
@@ -255,7 +251,6 @@ __device__ __forceinline__ void run_mid(const LinePass p, const Ctx& c) {
 #undef OMNI_MID2
 }
 
-template <bool SMALL>
 __device__ __forceinline__ void run_last(const LinePass p, const Ctx& c) {
 #define OMNI_LAST(N_, PAD_)  \
   last_pass<N_, PAD_>(p, c); \
@@ -269,11 +264,10 @@ __device__ __forceinline__ void run_last(const LinePass p, const Ctx& c) {
 }
 
 // Dynamic LDS: W [batch][w_size] float2, twiddles [n_tw] float2, power [groups][cells] float, table [n_tab] uint16.
-template <bool SMALL>
-__global__ __launch_bounds__(1024, SMALL ? 8 : 4) void lines_fp32_kernel(const void* __restrict__ src, int64_t T, int64_t tps,
-                                                          const float2* __restrict__ tw_glob,
-                                                          const uint16_t* __restrict__ tab_glob,
-                                                          double* __restrict__ partial, LineP P) {
+__global__ __launch_bounds__(1024, 4) void lines_fp32_kernel(const void* __restrict__ src, int64_t T, int64_t tps,
+                                                             const float2* __restrict__ tw_glob,
+                                                             const uint16_t* __restrict__ tab_glob,
+                                                             double* __restrict__ partial, LineP P) {
   extern __shared__ float2 smem[];
   Ctx c;
   c.W = smem;
@@ -350,10 +344,10 @@ __global__ __launch_bounds__(1024, SMALL ? 8 : 4) void lines_fp32_kernel(const v
     }
     __syncthreads();
     for (int pass = 0; pass < P.n_pass - 1; ++pass) {
-      run_mid<SMALL>(P.pass[pass], c);
+      run_mid(P.pass[pass], c);
       __syncthreads();
     }
-    run_last<SMALL>(P.pass[P.n_pass - 1], c);
+    run_last(P.pass[P.n_pass - 1], c);
     held += c.nb;
     if (held + P.batch > P.time_block || t + P.batch >= t1) {
       __syncthreads();
@@ -376,16 +370,11 @@ __global__ __launch_bounds__(1024, SMALL ? 8 : 4) void lines_fp32_kernel(const v
 hipError_t launch_lines_fp32(const void* src, int64_t T, int64_t tps, const float2* tw, const uint16_t* tab,
                              double* partial, const LineP& P, int grid, int threads, size_t lds, hipStream_t st) {
   if (P.n_pass < 1 || P.n_pass > kLineMaxPass || threads > 1024) return hipErrorInvalidValue;
-  bool small = true;
-  for (int i = 0; i < P.n_pass; ++i) small = small && line_type_small(P.pass[i].type);
-  const auto go = [&](auto* kernel) {
-    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3((unsigned)threads), lds, st, src, T, tps, tw, tab, partial,
-                       P);
-    return hipGetLastError();
-  };
-  return small ? go(lines_fp32_kernel<true>) : go(lines_fp32_kernel<false>);
+  hipError_t e = hipFuncSetAttribute((const void*)lines_fp32_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(lines_fp32_kernel, dim3((unsigned)grid), dim3((unsigned)threads), lds, st, src, T, tps, tw, tab,
+                     partial, P);
+  return hipGetLastError();
 }
 
 }  // namespace omni

@@ -250,8 +250,6 @@ bool plan_lines(int d, const int* n, const int* m, int max_batch, LineSetup& out
     for (const bool pairs : {false, true}) {
       const Layout L = make_layout(st, S, pairs);
       if (L.order.empty()) continue;
-      bool small = true;  // eight waves a SIMD instead of four
-      for (const Unit& u : L.order) small = small && line_type_small(unit_type(st, u));
       const int64_t n_tw = (twiddled || S > 1) && tw_all <= 1024 ? tw_all : 0;
       const int64_t load_lines = N / s0.nin, k_out = s0.nout / S;
       std::vector<double> instr;  // vector instructions of a line of each pass
@@ -295,7 +293,7 @@ bool plan_lines(int d, const int* n, const int* m, int max_batch, LineSetup& out
             issue += std::ceil(jobs / 64.0) * last;
             chain += std::ceil((double)jobs / NT) * (last * 3.7 + (each - 1.0) * last_wait) + 990.0;
             if (!ok) continue;
-            const double fit = std::max(1.0, std::min(std::floor((double)kLds / (double)lds), (small ? 2048.0 : 1024.0) / NT));
+            const double fit = std::max(1.0, std::min(std::floor((double)kLds / (double)lds), 1024.0 / NT));
             const double cost = (double)S / B * (1.12 * issue + chain / fit);
             if (cost < best * 0.98) {
               best = cost;
