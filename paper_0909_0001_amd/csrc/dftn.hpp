@@ -4,7 +4,12 @@
 // Cooley-Tukey (factor 4, then 2, then the smallest odd prime), odd primes p by the sums and differences of the
 // pairs (j, p - j), which need (p - 1)^2 real multiplications instead of 4 (p - 1)^2.  The twiddles are constants
 // of the instruction stream, evaluated in float64 at compile time (a Taylor series after exact reduction of the
-// angle to [0, pi/4]) and rounded to the values' precision once.
+// angle to [0, pi/4]) and rounded to the values' precision once.  In float32 a rounded twiddle is not of length one, and
+// a short transform uses few of them, so that the powers of all its outputs are off the same way (-2.1e-8 an axis of 3,
+// -4.1e-8 of 16).  Rotations therefore keep the smaller of cosine and sine in 24 bits and the other one, from it, in
+// 48: the angle is off by at most 2^-25, the length by nothing; the 3-point transform's one constant has 48 bits too.
+// 12 x 12, 32 channels: error against 64 bits 7.2e-8 -> 2.7e-8 of the visibilities' norm (direct sums with a rounded
+// table: 5.4e-8).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -66,6 +71,29 @@ struct Roots {
 template <int N>
 constexpr Roots<N> kRoots{};
 
+constexpr double root(double v) {  // square root of 0.5 <= v <= 1 (Newton's iteration)
+  double r = v;
+  for (int k = 0; k < 8; ++k) r = 0.5 * (r + v / r);
+  return r;
+}
+// The rotation by -2 pi q / N in float32: c - i s with c = c1 + c2, s = s1 + s2; one of c2 and s2 is zero.
+struct Turn {
+  float c1 = 0, c2 = 0, s1 = 0, s2 = 0;
+  constexpr Turn(double c, double s) {
+    c1 = (float)c;
+    s1 = (float)s;
+    if ((s < 0 ? -s : s) < (c < 0 ? -c : c)) {
+      const double e = root(1.0 - (double)s1 * s1) * (c < 0 ? -1.0 : 1.0);
+      c1 = (float)e;
+      c2 = (float)(e - c1);
+    } else {
+      const double e = root(1.0 - (double)c1 * c1) * (s < 0 ? -1.0 : 1.0);
+      s1 = (float)e;
+      s2 = (float)(e - s1);
+    }
+  }
+};
+
 __device__ __forceinline__ float2 pair(float x, float y) { return make_float2(x, y); }
 __device__ __forceinline__ double2 pair(double x, double y) { return make_double2(x, y); }
 __device__ __forceinline__ float mad(float a, float b, float c) { return fmaf(a, b, c); }
@@ -93,8 +121,14 @@ __device__ __forceinline__ V rot(V v, int q) {
   if (4 * q == N) return pair(v.y, -v.x);
   if (2 * q == N) return pair(-v.x, -v.y);
   if (4 * q == 3 * N) return pair(-v.y, v.x);
-  const S c = (S)R.c[q], s = (S)R.s[q];
-  return pair(mad(v.x, c, v.y * s), mad(v.y, c, -v.x * s));
+  if constexpr (sizeof(S) == sizeof(float)) {
+    const Turn t(R.c[q], R.s[q]);
+    if (t.s2 == 0.f) return pair(mad(v.x, t.c1, mad(v.y, t.s1, v.x * t.c2)), mad(v.y, t.c1, mad(-v.x, t.s1, v.y * t.c2)));
+    return pair(mad(v.y, t.s1, mad(v.x, t.c1, v.y * t.s2)), mad(-v.x, t.s1, mad(v.y, t.c1, -v.x * t.s2)));
+  } else {
+    const S c = R.c[q], s = R.s[q];
+    return pair(mad(v.x, c, v.y * s), mad(v.y, c, -v.x * s));
+  }
 }
 
 constexpr int first_factor(int n) {
@@ -141,6 +175,10 @@ __device__ __forceinline__ void dft(V (&x)[N]) {
         const S c = (S)R.c[(k * (j + 1)) % N], s = (S)R.s[(k * (j + 1)) % N];
         r = pair(mad(a[j].x, c, r.x), mad(a[j].y, c, r.y));
         i = pair(mad(b[j].x, s, i.x), mad(b[j].y, s, i.y));
+      }
+      if constexpr (N == 3 && sizeof(S) == sizeof(float)) {
+        constexpr float s1 = (float)R.s[1], s2 = (float)(R.s[1] - s1);
+        i = pair(mad(b[0].x, s1, b[0].x * s2), mad(b[0].y, s1, b[0].y * s2));
       }
       x[k] = pair(r.x + i.y, r.y - i.x);
       x[N - k] = pair(r.x - i.y, r.y + i.x);
