@@ -127,7 +127,7 @@ struct TraceRange {
 constexpr int kNT = 256;              // threads per fused work-group
 constexpr int kMaxCPT = 32;           // Fourier cells per thread
 constexpr int kCellsMax = kNT * kMaxCPT;
-constexpr size_t kLdsMax = 160 * 1024;
+constexpr size_t kLdsMax = omni::kMaxLds;
 constexpr int64_t kMaxN = int64_t(1) << 22;
 constexpr size_t kPartialBudget = size_t(512) << 20;
 

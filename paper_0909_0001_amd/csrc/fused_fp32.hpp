@@ -281,7 +281,8 @@ template <int FMT, int CPT>
 static hipError_t launch_fused_t(const void* src, int64_t T, int64_t tps, const float2* tw, double* partial,
                                  const FusedP& P, int grid, size_t lds, hipStream_t st) {
   auto k = fused_fp32_kernel<FMT, CPT, kFusedNT>;
-  hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  // (always the largest: the limit belongs to the process, and another thread may be launching another plan)
+  hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k, dim3(grid), dim3(kFusedNT), lds, st, src, T, tps, tw, partial, P);
   return hipGetLastError();

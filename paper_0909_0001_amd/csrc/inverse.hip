@@ -14,6 +14,7 @@
 
 #include "dftn.hpp"
 #include "inverse.hpp"
+#include "plan.hpp"
 
 namespace omni {
 namespace {
@@ -236,7 +237,8 @@ hipError_t launch_inverse_group(int src_kind, const void* src, void* dst, const 
                         inner != (int64_t)n_tiles * (n_tiles + 1) / 2))
     return hipErrorInvalidValue;
   const auto go = [&](auto* kernel) {
-    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    // (always the largest: the limit belongs to the process, and another thread may be launching another plan)
+    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3((unsigned)threads), lds, st, src, static_cast<float2*>(dst), twi,
                        tab, columns, inner, scale, P, pair_tab, n_tiles);

@@ -24,6 +24,7 @@
 
 #include "dftn.hpp"
 #include "lines.hpp"
+#include "plan.hpp"
 
 namespace omni {
 namespace {
@@ -370,7 +371,8 @@ __global__ __launch_bounds__(1024, 4) void lines_fp32_kernel(const void* __restr
 hipError_t launch_lines_fp32(const void* src, int64_t T, int64_t tps, const float2* tw, const uint16_t* tab,
                              double* partial, const LineP& P, int grid, int threads, size_t lds, hipStream_t st) {
   if (P.n_pass < 1 || P.n_pass > kLineMaxPass || threads > 1024) return hipErrorInvalidValue;
-  hipError_t e = hipFuncSetAttribute((const void*)lines_fp32_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  // (always the largest: the limit belongs to the process, and another thread may be launching another plan)
+  hipError_t e = hipFuncSetAttribute((const void*)lines_fp32_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(lines_fp32_kernel, dim3((unsigned)grid), dim3((unsigned)threads), lds, st, src, T, tps, tw, tab,
                      partial, P);

@@ -24,6 +24,7 @@ namespace omni {
 
 constexpr int kMaxD = 8;
 constexpr int kMaxL = 32;  // longest per-thread short DFT
+constexpr int kMaxLds = 160 * 1024;  // bytes of LDS a work-group can have
 
 struct AxisP {
   int32_t n;         // antennas along this axis
