@@ -2047,13 +2047,14 @@ int omni_plan_describe(omni_plan_t plan, char* buf, size_t len, size_t* needed) 
                         : ap.kernel == 7 ? "grid64_mixed"
                         : ap.kernel == 8 ? "grid32_mixed"
                                          : "fused_fp32";
-    // what the inverse's plain sums take: none (groups of axes, lines), tiles of columns in LDS, or one thread a lag
+    // the inverse: groups of axes; some axes a thread a line; some by plain sums, on tiles of columns or a thread a lag
     const char* inverse = "groups";
     int64_t columns = ap.inv_group;  // (as run_inverse counts them)
     for (const auto& g : ap.inv) {
       int64_t inner = 1;
       for (size_t k = (size_t)(g.axis0 + g.axes); k < ap.n.size(); ++k)
         inner *= (int)k < (int)ap.n.size() - ap.nbeam ? ap.m[k] : ap.n[k];
+      if (g.line) inverse = "lines";
       if (g.direct)
         inverse = omni::inverse_axis_tiled(ap.m[(size_t)g.axis0], columns * inner) ? "tiled" : "untiled";
       for (int k = g.axis0; k < g.axis0 + g.axes; ++k) columns *= 2 * ap.n[(size_t)k] - 1;
