@@ -1,13 +1,13 @@
 // Short complex DFTs of any small length with compile-time twiddles, in registers (gfx950).
 //
 // dft<N> transforms N float2 or double2 values in place, natural order, w_N = exp(-2 pi i / N): composite lengths by
-// Cooley-Tukey (factor 4, then 2, then the smallest odd prime), odd primes p by the sums and differences of the
-// pairs (j, p - j), which need (p - 1)^2 real multiplications instead of 4 (p - 1)^2.  The twiddles are constants
-// of the instruction stream, evaluated in float64 at compile time (a Taylor series after exact reduction of the
+// Cooley-Tukey (factor 4, then 2, then the smallest odd prime; without rotations between coprime factors), odd primes
+// p by the sums and differences of the pairs (j, p - j), which need (p - 1)^2 real multiplications instead of
+// 4 (p - 1)^2.  The twiddles are constants of the instruction stream, evaluated in float64 at compile time (a Taylor series after exact reduction of the
 // angle to [0, pi/4]) and rounded to the values' precision once.  In float32 a rounded twiddle is not of length one, and
 // a short transform uses few of them, so that the powers of all its outputs are off the same way (-2.1e-8 an axis of 3,
 // -4.1e-8 of 16).  Rotations therefore keep the smaller of cosine and sine in 24 bits and the other one, from it, in
-// 48: the angle is off by at most 2^-25, the length by nothing; the 3-point transform's one constant has 48 bits too.
+// 48: the angle is off by at most 2^-25, the length by nothing; the 3- and 5-point transforms' constants have 48 bits too.
 // 12 x 12, 32 channels: error against 64 bits 7.2e-8 -> 2.7e-8 of the visibilities' norm (direct sums with a rounded
 // table: 5.4e-8).
 #pragma once
@@ -170,18 +170,46 @@ __device__ __forceinline__ void dft(V (&x)[N]) {
 #pragma unroll
     for (int k = 1; k <= H; ++k) {
       V r = x0, i = pair((S)0, (S)0);
+      if constexpr (N == 5 && sizeof(S) == sizeof(float)) r = i;
+      if constexpr (N <= 5 && sizeof(S) == sizeof(float)) {  // what the constants' rounding leaves out
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+          const double c = R.c[(k * (j + 1)) % N], s = R.s[(k * (j + 1)) % N];
+          const S c2 = (S)(c - (S)c), s2 = (S)(s - (S)s);
+          if (N == 5) r = pair(mad(a[j].x, c2, r.x), mad(a[j].y, c2, r.y));
+          i = pair(mad(b[j].x, s2, i.x), mad(b[j].y, s2, i.y));
+        }
+      }
 #pragma unroll
       for (int j = 0; j < H; ++j) {
         const S c = (S)R.c[(k * (j + 1)) % N], s = (S)R.s[(k * (j + 1)) % N];
         r = pair(mad(a[j].x, c, r.x), mad(a[j].y, c, r.y));
         i = pair(mad(b[j].x, s, i.x), mad(b[j].y, s, i.y));
       }
-      if constexpr (N == 3 && sizeof(S) == sizeof(float)) {
-        constexpr float s1 = (float)R.s[1], s2 = (float)(R.s[1] - s1);
-        i = pair(mad(b[0].x, s1, b[0].x * s2), mad(b[0].y, s1, b[0].y * s2));
-      }
+      if constexpr (N == 5 && sizeof(S) == sizeof(float)) r = add(x0, r);
       x[k] = pair(r.x + i.y, r.y - i.x);
       x[N - k] = pair(r.x - i.y, r.y + i.x);
+    }
+  } else if constexpr (first_factor(N) % 2 == 0 && (N / first_factor(N)) % 2 == 1) {
+    // coprime factors (a power of two and an odd number): j = B j1 + A j2 mod N, kappa = k1 mod A and k2 mod B, no
+    // rotations between the two (Good's prime-factor map)
+    constexpr int A = first_factor(N), B = N / A;
+    V y[A][B];
+#pragma unroll
+    for (int j1 = 0; j1 < A; ++j1) {
+#pragma unroll
+      for (int j2 = 0; j2 < B; ++j2) y[j1][j2] = x[(B * j1 + A * j2) % N];
+      dft<B>(y[j1]);
+    }
+#pragma unroll
+    for (int k2 = 0; k2 < B; ++k2) {
+      V z[A];
+#pragma unroll
+      for (int j1 = 0; j1 < A; ++j1) z[j1] = y[j1][k2];
+      dft<A>(z);
+#pragma unroll
+      for (int k = 0; k < N; ++k)
+        if (k % B == k2) x[k] = z[k % A];
     }
   } else {
     // j = j1 + A j2, kappa = B k1 + k2:  w^{j kappa} = w_A^{j1 k1} w_N^{j1 k2} w_B^{j2 k2}

@@ -51,8 +51,19 @@ __device__ __forceinline__ float2 sample_at(const void* __restrict__ src, int64_
   return make_float2((float)(v >> 4), (float)((int8_t)(v << 4) >> 4));
 }
 
-// Outputs of one line: N values transformed (plain), or zero-padded to 2N: even outputs are DFT_N(x), odd outputs
-// DFT_N(x_j w_2N^j).
+// Inputs of the odd outputs of a zero-padded transform (2N outputs of N values): the even ones are DFT_N(x), output
+// 2q + 1 is DFT_N(x_j w_2N^j)[q], and for odd N output 2q + N mod 2N is DFT_N((-1)^j x_j)[q], without rotations.
+template <int N>
+__device__ __forceinline__ float2 odd_input(float2 v, int j) {
+  if constexpr (N % 2) return j & 1 ? make_float2(-v.x, -v.y) : v;
+  return dn::rot<2 * N>(v, j);
+}
+template <int N>
+constexpr int odd_output(int q) {
+  return N % 2 ? (2 * q + N) % (2 * N) : 2 * q + 1;
+}
+
+// Outputs of one line: N values transformed (plain), or zero-padded to 2N.
 template <int N, bool PAD, class Put>
 __device__ __forceinline__ void line_dft(const float2 (&x)[N], Put put) {
   float2 z[N];
@@ -63,10 +74,10 @@ __device__ __forceinline__ void line_dft(const float2 (&x)[N], Put put) {
   for (int q = 0; q < N; ++q) put(PAD ? 2 * q : q, z[q]);
   if constexpr (PAD) {
 #pragma unroll
-    for (int j = 0; j < N; ++j) z[j] = dn::rot<2 * N>(x[j], j);
+    for (int j = 0; j < N; ++j) z[j] = odd_input<N>(x[j], j);
     dft<N>(z);
 #pragma unroll
-    for (int q = 0; q < N; ++q) put(2 * q + 1, z[q]);
+    for (int q = 0; q < N; ++q) put(odd_output<N>(q), z[q]);
   }
 }
 
@@ -133,7 +144,7 @@ __device__ __forceinline__ void block_dft(Get get, Put put) {
   for (int i = 0; i < N1; ++i) {
     float2 t[N2];
 #pragma unroll
-    for (int j = 0; j < N2; ++j) t[j] = HALF ? dn::rot<2 * N2>(get(i, j), j) : get(i, j);
+    for (int j = 0; j < N2; ++j) t[j] = HALF ? odd_input<N2>(get(i, j), j) : get(i, j);
     dft<N2>(t);
 #pragma unroll
     for (int j = 0; j < N2; ++j) z[i * N2 + j] = t[j];
@@ -143,7 +154,7 @@ __device__ __forceinline__ void block_dft(Get get, Put put) {
     float2 v[N1];
 #pragma unroll
     for (int i = 0; i < N1; ++i) v[i] = z[i * N2 + q];
-    line_dft<N1, true>(v, [&](int k1, float2 y) OMNI_INLINE { put(k1, 2 * q + HALF, y); });
+    line_dft<N1, true>(v, [&](int k1, float2 y) OMNI_INLINE { put(k1, HALF ? odd_output<N2>(q) : 2 * q, y); });
   }
 }
 
