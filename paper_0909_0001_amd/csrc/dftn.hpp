@@ -122,9 +122,10 @@ __device__ __forceinline__ V rot(V v, int q) {
   if (2 * q == N) return pair(-v.x, -v.y);
   if (4 * q == 3 * N) return pair(-v.y, v.x);
   if constexpr (sizeof(S) == sizeof(float)) {
+    // (the small part goes with its own product: added to the other one, which may be exact, rounding would drop it)
     const Turn t(R.c[q], R.s[q]);
-    if (t.s2 == 0.f) return pair(mad(v.x, t.c1, mad(v.y, t.s1, v.x * t.c2)), mad(v.y, t.c1, mad(-v.x, t.s1, v.y * t.c2)));
-    return pair(mad(v.y, t.s1, mad(v.x, t.c1, v.y * t.s2)), mad(-v.x, t.s1, mad(v.y, t.c1, -v.x * t.s2)));
+    if (t.s2 == 0.f) return pair(mad(v.y, t.s1, mad(v.x, t.c1, v.x * t.c2)), mad(-v.x, t.s1, mad(v.y, t.c1, v.y * t.c2)));
+    return pair(mad(v.x, t.c1, mad(v.y, t.s1, v.y * t.s2)), mad(v.y, t.c1, mad(-v.x, t.s1, -v.x * t.s2)));
   } else {
     const S c = R.c[q], s = R.s[q];
     return pair(mad(v.x, c, v.y * s), mad(v.y, c, -v.x * s));
