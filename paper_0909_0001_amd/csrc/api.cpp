@@ -648,7 +648,7 @@ void plan_grid_small(ArrayPlan& ap, int kernel) {
 // prime factors are at most 13, cells divisible along the first axis into LDS-sized shares), else the runtime-shape
 // kernel's schedule that is already in ap.fs.  The line kernel is the faster one on every grid measured (kernel
 // times): 16 x 16 floats, one channel, T = 1024: 57 -> 12 us; 5x3 / 3x3 / 3x3 8-bit, 12 channels, T = 333:
-// 5459 -> 410 us; 2x2 / 16x16 8-bit, 16 channels, T = 250: 414 -> 70 us.
+// 5459 -> 390 us; 2x2 / 16x16 8-bit, 16 channels, T = 250: 414 -> 72 us.
 void plan_general(ArrayPlan& ap) {
   FusedSetup& fs = ap.fs;
   const int s = ap.n_front, d = (int)ap.n.size() - s;

@@ -6,7 +6,7 @@
 // axis) comes from two front passes (front.hip).  The pair stage here is the
 // X-engine over Fourier cells: for every channel f and cell kappa,
 //   S_pq[kappa] += sum_t Y_p[t][kappa] conj(Y_q[t][kappa]),   all ordered (p, q),
-// which the inverse transform (finalize.hip) turns into the cross-correlation
+// which the inverse transform (inverse.hip) turns into the cross-correlation
 // of tiles p and q over index differences (C_pp is tile p's own hypercube).
 //
 // Only the Hermitian half of the pairs is summed: S_qp[kappa] =

@@ -13,7 +13,7 @@
 // batched until a pass fills the work-group; job addresses come from a table in LDS (one 2-byte read) instead of a
 // chain of divisions per job and sample.  A pass costs about 1000 cycles of waiting (table, line, barrier) besides its
 // instructions, which is why short axes are transformed two by two (n1 n2 values a thread): 5x3 / 3x3 / 3x3, 12
-// channels, T = 333: 635 -> 410 us, 2x2 / 16x16, 16 channels, T = 250: 130 -> 70 us, together with one round of
+// channels, T = 333: 635 -> 390 us, 2x2 / 16x16, 16 channels, T = 250: 130 -> 72 us, together with one round of
 // work-groups instead of a fixed count.  Vector units issue 30 to 40% of the cycles.  Eight waves a SIMD instead of four
 // (64 registers, for schedules of short transforms only) made most grids slower, for the schedules that the planner then
 // chose: 36x18, 8 channels, T = 500: 59 us for 46; 15x6, 32 channels, T = 1500: 45 for 38; 5x3/3x3/3x3: 418 for 400;
