@@ -128,6 +128,7 @@ constexpr int kNT = 256;              // threads per fused work-group
 constexpr int kMaxCPT = 32;           // Fourier cells per thread
 constexpr int kCellsMax = kNT * kMaxCPT;
 constexpr size_t kLdsMax = omni::kMaxLds;
+constexpr const char* kWhyLds = "LDS working set exceeds 160 KiB";
 constexpr int64_t kMaxN = int64_t(1) << 22;
 constexpr size_t kPartialBudget = size_t(512) << 20;
 
@@ -476,7 +477,7 @@ int plan_fused_axes(const std::vector<int>& n, int F, int tw_base, bool single_s
   }
   fs.lds = (size_t)P.w_elems * 8 + (size_t)cpt * kNT * 4 + (size_t)P.n_tw * 8;
   if (fs.lds > kLdsMax) {
-    *why = "LDS working set exceeds 160 KiB";
+    *why = kWhyLds;
     return OMNI_E_SHAPE;
   }
   fs.kmap.clear();
@@ -675,11 +676,12 @@ void plan_general(ArrayPlan& ap) {
 // axis needs a power-of-two padded length of at most 64 (short DFTs of <= 32).
 bool front_axis_ok(int n) { return is_pow2(2 * n) && 2 * n <= 64; }
 
-int plan_front(ArrayPlan& ap, std::string* why) {
+// With `any` the front axes may have any length (passes by plain sums): the way out for grids that nothing else divides.
+int plan_front(ArrayPlan& ap, std::string* why, bool any = false) {
   const int d = (int)ap.n.size();
   int64_t MS = 1, NS = 1;
   for (int s = 1; s < d; ++s) {
-    if (s - 1 >= d - ap.nbeam || !front_axis_ok(ap.n[s - 1])) break;
+    if (s - 1 >= d - ap.nbeam || (!any && !front_axis_ok(ap.n[s - 1]))) break;
     MS *= 2 * ap.n[s - 1];
     NS *= ap.n[s - 1];
     std::vector<int> rest(ap.n.begin() + s, ap.n.end());
@@ -694,7 +696,7 @@ int plan_front(ArrayPlan& ap, std::string* why) {
       ap.n_front = s;
       ap.front_tw_base = tw_base;
       ap.front_r.assign(s, 1);
-      for (int k = 0; k < s; ++k) ap.front_r[k] = std::max(1, 2 * ap.n[k] / 16);
+      for (int k = 0; k < s; ++k) ap.front_r[k] = front_axis_ok(ap.n[k]) ? std::max(1, 2 * ap.n[k] / 16) : 0;
       // time chunk: the largest front output (after the last front pass) <= kFrontBytes
       const int64_t per_t = (int64_t)ap.F * MS * (ap.N / NS) * (int64_t)sizeof(float2);
       ap.chunk_T = std::max<int64_t>(1, std::min<int64_t>(kChunkMax, kFrontBytes / per_t));
@@ -776,8 +778,10 @@ int build_array_core(ArrayPlan& ap, int levels, const int32_t* dims, const doubl
   if (rc) {
     // last resort: residue splits along several axes (correct, repeats early passes)
     rc = plan_fused_axes(ap.n, ap.F, 0, false, ap.lcap, ap.fs, &why, nullptr, 0, ap.m.data());
+    ap.single_split = rc != OMNI_OK;
+    // the cells can be divided, but the inputs of the axes behind the first exceed LDS
+    if (rc && why == kWhyLds) rc = plan_front(ap, &why2, true);
     if (rc) return fail(rc, why + "; " + why2);
-    ap.single_split = false;
   }
   // the fixed-shape kernels all assume zero-padded axes: a beam-space plan keeps the general kernel
   if (ap.nbeam > 0) {
@@ -804,10 +808,12 @@ int build_array_core(ArrayPlan& ap, int levels, const int32_t* dims, const doubl
   }
   if (form == OMNI_FORM_FP32 && eight4) plan_fused8x4(ap);
   if (form == OMNI_FORM_MIXED && eight4 && dtype != OMNI_CF32) plan_fused8x4_mixed(ap);
-  if (form == OMNI_FORM_MIXED && dtype != OMNI_CF32 && ap.n_front == 1 &&
+  // (the matrix-core kernels take float16 operands, which only the register front passes write)
+  const bool front16 = std::find(ap.front_r.begin(), ap.front_r.end(), 0) == ap.front_r.end();
+  if (form == OMNI_FORM_MIXED && dtype != OMNI_CF32 && ap.n_front == 1 && front16 &&
       std::vector<int>(ap.n.begin() + 1, ap.n.end()) == std::vector<int>{16, 16, 16})
     plan_mixed_behind_front(ap, 4);
-  if (form == OMNI_FORM_MIXED && dtype != OMNI_CF32 && ap.n_front == 2 &&
+  if (form == OMNI_FORM_MIXED && dtype != OMNI_CF32 && ap.n_front == 2 && front16 &&
       std::vector<int>(ap.n.begin() + 2, ap.n.end()) == std::vector<int>{8, 8, 4, 4})
     plan_mixed_behind_front(ap, 5);
   if (form == OMNI_FORM_MIXED && dtype == OMNI_CI4 && ap.n_front == 0 && ap.n == std::vector<int>{128, 128})

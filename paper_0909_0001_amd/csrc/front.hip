@@ -323,13 +323,81 @@ hipError_t launch_front2_16x16(int fmt, const void* src, void* dst, const float2
   return hipGetLastError();
 }
 
+// The same pass for any length, by plain sums: a thread forms 8 outputs of one column, consecutive threads take
+// consecutive inner indices.  For grids that nothing else can divide (5x16/16x16): n multiply-adds an output where the
+// kernel above takes about log2 m of them.
+template <int FMT>
+__global__ __launch_bounds__(256) void front_axis_any_kernel(const void* __restrict__ src, float2* __restrict__ dst,
+                                                             const float2* __restrict__ twm, int64_t total,
+                                                             int64_t outer, int n, int m, int64_t inner,
+                                                             int64_t src_tile, int64_t dst_tile) {
+  constexpr int K = 8;
+  const int blocks = (m + K - 1) / K;
+  for (int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; idx < total;
+       idx += (int64_t)gridDim.x * blockDim.x) {
+    int64_t rest = idx / inner;
+    const int64_t in = idx - rest * inner;
+    const int k0 = (int)(rest % blocks) * K;
+    rest /= blocks;
+    const int64_t o = rest % outer, tile = rest / outer;
+    const int64_t sbase = tile * src_tile + o * n * inner + in;
+    float2 acc[K];
+    int e[K];  // (k0 + i) j mod m
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      acc[i] = make_float2(0.f, 0.f);
+      e[i] = 0;
+    }
+    for (int j = 0; j < n; ++j) {
+      const float2 v = fr::load<FMT>(src, sbase + j * inner);
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        const float2 w = twm[e[i]];
+        acc[i].x = fmaf(v.x, w.x, fmaf(-v.y, w.y, acc[i].x));
+        acc[i].y = fmaf(v.x, w.y, fmaf(v.y, w.x, acc[i].y));
+        e[i] += k0 + i < m ? k0 + i : 0;
+        if (e[i] >= m) e[i] -= m;
+      }
+    }
+    float2* d = dst + tile * dst_tile + (o * m + k0) * inner + in;
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+      if (k0 + i < m) d[i * inner] = acc[i];
+  }
+}
+
+static hipError_t launch_front_axis_any(int fmt, const void* src, void* dst, const float2* twm, int64_t tiles,
+                                        int64_t outer, int n, int m, int64_t inner, int64_t src_tile, int64_t dst_tile,
+                                        hipStream_t st) {
+  const int64_t total = tiles * outer * ((m + 7) / 8) * inner;
+  if (total < 1) return total == 0 ? hipSuccess : hipErrorInvalidValue;
+  const dim3 grid((unsigned)std::min<int64_t>((total + 255) / 256, 65536)), block(256);
+  const auto go = [&](auto* kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, src, static_cast<float2*>(dst), twm, total, outer, n, m, inner,
+                       src_tile, dst_tile);
+    return hipGetLastError();
+  };
+  switch (fmt) {
+    case 0: return go(front_axis_any_kernel<0>);
+    case 1: return go(front_axis_any_kernel<1>);
+    case 2: return go(front_axis_any_kernel<2>);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 // fmt: 0 float32 complex, 1 ci8, 2 ci4, 3 float16 planar blocks (the H16 output of a front pass).
 // half16: float16 planar output scaled by `scale` (see H16 above); else float32 complex.
+// r: fold modulus; 0: any length, by plain sums, float32 output.
 hipError_t launch_front_axis(int fmt, const void* src, void* dst, const float2* twm, int64_t tiles, int64_t outer,
                              int n, int m, int r, int64_t inner, int64_t src_tile, int64_t dst_tile, hipStream_t st,
                              bool half16, float scale) {
+  if (m != 2 * n) return hipErrorInvalidValue;
+  if (r == 0) {
+    if (half16) return hipErrorInvalidValue;
+    return launch_front_axis_any(fmt, src, dst, twm, tiles, outer, n, m, inner, src_tile, dst_tile, st);
+  }
   const int L = m / r;
-  if (m != 2 * n || L * r != m) return hipErrorInvalidValue;
+  if (L * r != m) return hipErrorInvalidValue;
   // packed integer samples: four inner indices per thread when the word loads stay aligned
   const int V = (fmt != 0 && L <= 16 && inner % 2 == 0 && src_tile % 2 == 0 &&
                  (reinterpret_cast<uintptr_t>(src) & 3) == 0)

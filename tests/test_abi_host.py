@@ -344,10 +344,16 @@ def test_log_level_controls_stderr():
     assert len(plans) == 1 and '"arrays"' in plans[0]
 
 
-def test_grid_beyond_every_working_set_is_refused():
-    """A grid whose first axis can neither be divided further nor be transformed by a front pass, and whose other axes'
-    inputs exceed the LDS working array, has no schedule: planning says so."""
-    with pytest.raises(omni.OmniError):
-        omni.Plan([[17, 17], [16, 16]], None, 1, "ci8", "fp32", host_only=True)
+def test_grids_that_no_division_fits_take_front_passes():
+    """A grid whose first axis has no register front pass and whose other axes' inputs exceed the LDS working array is
+    planned with front passes by plain sums; sides with an odd factor above 31 stay refused."""
+    import json
+
+    for dims, fronts in (([[17, 17], [16, 16]], 2), ([[5, 16], [16, 16]], 1), ([[3, 3], [16, 16], [4, 4]], 2)):
+        a = json.loads(omni.Plan(dims, None, 1, "ci8", "mixed", host_only=True).describe())["arrays"][0]
+        assert a["mode"] == "front" and a["n_front"] == fronts and not a["kernel"].endswith("mixed")
     # the same tiles on a grid that leaves room for them
-    omni.Plan([[3, 16], [16, 16]], None, 1, "ci8", "fp32", host_only=True)
+    assert json.loads(omni.Plan([[3, 16], [16, 16]], None, 1, "ci8", host_only=True).describe())["arrays"][0]["n_front"] == 0
+    for dims in ([[39, 17], [16, 16]], [[5, 39], [16, 16]]):
+        with pytest.raises(omni.OmniError):
+            omni.Plan(dims, None, 1, "ci8", "fp32", host_only=True)

@@ -1110,3 +1110,25 @@ def test_autotuner_reaches_the_line_kernels_slices(tmp_path):
         # (whole batches a slice: a few slices fewer than aimed for)
         assert got == own if target == 0 else target // F // 2 < got <= target // F
         assert rel_err(vis.cpu().numpy(), ref.cpu().numpy()) <= 1e-6
+
+
+@pytest.mark.parametrize(
+    "level_dims,dtype,form,T,F,chunk_T",
+    [
+        ([[5, 16], [16, 16]], "ci8", "mixed", 10, 2, 4),  # before the (16, 16, 16) float32 kernel; three chunks
+        ([[3, 3], [16, 16], [4, 4]], "ci4", "fp32", 5, 1, 0),  # two passes, the first reads 4-bit samples
+        ([[17, 17], [16, 16]], "cf32", "fp32", 3, 1, 2),  # 34 outputs: a last block of two
+    ],
+)
+def test_front_passes_of_any_length(level_dims, dtype, form, T, F, chunk_T):
+    """Grids that no division among work-groups fits: front passes by plain sums over axes of any length."""
+    N = math.prod(dims_of(level_dims))
+    gen = torch.Generator().manual_seed(N)
+    raw = random_raw(dtype, T, F, N, gen)
+    say("front passes of any length", level_dims, dtype)
+    plan = omni.Plan(level_dims, None, F, dtype, form, chunk_T=chunk_T)
+    assert '"mode":"front"' in plan.describe()
+    vis = plan.correlate(raw.cuda())
+    torch.cuda.synchronize()
+    x = oracle.decode(raw.numpy(), dtype, T, F, N)
+    check_cells(vis.cpu().numpy(), x, dims_of(level_dims), "fp32", 256, 9, f"any front {level_dims}")
